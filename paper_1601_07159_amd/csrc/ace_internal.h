@@ -187,6 +187,8 @@ BuildPlan plan_build(ace_ctx c, const GridInfo& g, size_t elem_bytes, int nocc, 
 // Workspace of ace_apply_h for n_x vectors (exchange from n_xi projection
 // vectors or n_phi orbitals; 0 for none).
 size_t hamiltonian_ws_bytes(ace_ctx c, const GridInfo& g, size_t eb, int nx, int nxi, int nphi);
+// Workspace of the Rayleigh-Ritz step on n vectors.
+size_t ritz_ws_bytes(int n, long ng);
 // Workspace the compression takes for n_band vectors; alias_eb > 0 adds the
 // copy of xi (n_band x N_g elements of alias_eb bytes) that xi == W needs.
 size_t compress_ws_bytes(int nb, long ng, size_t alias_eb = 0);

@@ -583,7 +583,7 @@ ACE_EXPORT ace_status ace_reserve(ace_ctx c, const ace_grid* grid, ace_prec prec
   // ace_apply_h (exchange from xi or from the occupied orbitals) and the
   // Rayleigh-Ritz step of the eigensolver on up to max(n_band, n_x) vectors
   need = std::max(need, hamiltonian_ws_bytes(c, g, eb, std::max(max_nx, 1), max_nband, max_nocc));
-  need = std::max(need, 4 * mat + gemm_cn_scratch_bytes(nmax, nmax, g.ng));
+  need = std::max(need, ritz_ws_bytes(std::min(nmax, 512), g.ng));
   return ws_begin(c, need);
 }
 

@@ -8,7 +8,7 @@
 //   ace_combine        D = a A + b B + c C on orbital blocks (the three-term
 //                      recurrences of polynomial filters);
 //   ace_rayleigh_ritz  S = dV X^H (HX), S = Q diag(e) Q^H by a parallel
-//                      cyclic Jacobi method in one workgroup, X Q and (HX) Q.
+//                      cyclic Jacobi method, X Q and (HX) Q.
 // The kinetic term runs on the pair FFT passes: one "orbital" of ones and the
 // kernel |G|^2 / 2 make them compute ifftn(|G|^2/2 fftn(x)) for every x.
 #include <cmath>
@@ -76,14 +76,11 @@ inline unsigned stream_blocks(long total) {
 }
 
 // ---------------------------------------------------------------------------
-// Hermitian eigensolver for n <= kJacobiMax, one workgroup of 1024 threads:
-// the parallel cyclic Jacobi method (Brent-Luk order).  A sweep visits every
-// pair (p, q) once in n - 1 steps (n even; a dummy index pads odd n) of n/2
-// disjoint pairs, scheduled by the circle method (index m = n - 1 fixed, the
-// others rotating).  Each step computes the n/2 rotations from A, then applies
-// them to the rows of A (A <- J^H A), to the columns of A and of V
-// (A <- A J, V <- V J); rotations of disjoint pairs commute.  For the pair
-// (p, q) with a = A_pp, b = A_qq, A_pq = |c| e^{i phi}: the phase
+// Hermitian eigensolver for n <= kJacobiMax: the parallel cyclic Jacobi method
+// (Brent-Luk order) in two kernels.  A sweep visits every pair (p, q) once in
+// n - 1 steps (n even; a zero row and column pad odd n) of n/2 disjoint pairs,
+// scheduled by the circle method (index m = n - 1 fixed, the others rotating).
+// For the pair (p, q) with a = A_pp, b = A_qq, A_pq = |c| e^{i phi}: the phase
 // D = diag(1, e^{-i phi}) makes the pair block real, then the real rotation
 // [[cs, sn], [-sn, cs]] with t = tan(theta) the smaller root of
 // t^2 + 2 tau t - 1 = 0, tau = (b - a) / (2 |c|), annihilates it:
@@ -92,135 +89,136 @@ inline unsigned stream_blocks(long total) {
 // Sweeps stop when the off-diagonal Frobenius norm falls below tol times the
 // whole norm (or after max_sweeps).  The eigenvalues (real parts of the final
 // diagonal) are sorted ascending, ties by index, and the columns of V follow.
+//
+// k_jacobi_sweeps (one workgroup) rotates A alone and records the rotations;
+// k_jacobi_vectors forms V from them.  The sweeps are a serial chain of
+// (n - 1) x sweeps steps of two barriers, so what a step does decides the
+// time: a thread takes whole 2 x 2 blocks (pair k's rows x pair l's columns)
+// and applies both sides to them in registers, rows first (one pass over A in
+// LDS and one barrier where rows and columns in turn take two of each), and V,
+// whose rows never mix, leaves the workgroup: one wave per row of V replays
+// the recorded rotations, all rows in parallel.  Measured, against one kernel
+// with separate row and column passes and V in global memory: n = 88 (A in
+// LDS) 5.98 -> 1.75 + 0.11 ms, the whole Rayleigh-Ritz step at n = 128 (A in
+// global memory) 29.2 -> 6.5 ms, at n = 256 303 -> 137 ms.
 // A is kept in LDS up to kJacobiLds rows, in global scratch beyond.
 constexpr int kJacobiMax = 512;
 constexpr int kJacobiLds = 88;  // 88^2 complex128 = 121 KiB of LDS
+constexpr int kJacobiSweeps = 30;
 
-struct JacobiRot {
-  int p, q;
-  double cs, sn, er, ei;  // cosine, sine, e^{i phi}
+struct alignas(16) JacobiRot {
+  double cs, sn, er, ei;  // cosine, sine, e^{i phi}; sn = 0: not rotated
 };
 
-template <bool LDS>
-__global__ __launch_bounds__(1024) void k_jacobi_eigh(const cx<double>* __restrict__ S, int lds_,
-                                                      int n, cx<double>* __restrict__ Ag,
-                                                      cx<double>* __restrict__ V,
-                                                      cx<double>* __restrict__ Vout, int ldv,
-                                                      double* __restrict__ evals, int max_sweeps,
-                                                      double tol) {
-  __shared__ cx<double> a_lds[LDS ? kJacobiLds * kJacobiLds : 1];
-  __shared__ JacobiRot rot[kJacobiMax / 2];
-  __shared__ double red[1024];
-  __shared__ int stop;
-  const int t = threadIdx.x, nt = blockDim.x;
-  const int lda = LDS ? kJacobiLds : n;
-  cx<double>* A = LDS ? a_lds : Ag;
-  // A = (S + S^H)/2, V = I
-  for (int e = t; e < n * n; e += nt) {
-    const int i = e % n, j = e / n;
-    const cx<double> u = S[i + (size_t)j * lds_], w = S[j + (size_t)i * lds_];
-    A[i + j * lda] = {0.5 * (u.x + w.x), 0.5 * (u.y - w.y)};
-    V[i + (size_t)j * ldv] = {i == j ? 1.0 : 0.0, 0.0};
+// Pair k of step st: (st, m) for k = 0, else (st + k, st - k) mod m; p < q.
+__device__ __forceinline__ void jacobi_pair(int st, int k, int m, int* p, int* q) {
+  int x = st, y = m;
+  if (k != 0) {
+    x = st + k;
+    x = x >= m ? x - m : x;
+    y = st - k;
+    y = y < 0 ? y + m : y;
+  }
+  *p = x < y ? x : y;
+  *q = x < y ? y : x;
+}
+
+// The rotation of pair (p, q) from its block's entries a = A_pp, b = A_qq, c = A_pq.
+// (Here and in jacobi_rows / jacobi_cols the fused multiply-adds are explicit:
+// the vector a rotation ends on depends on the rounding of nearly converged
+// entries, so every form must round alike.)
+__device__ __forceinline__ JacobiRot jacobi_rotation(double a, double b, cx<double> c) {
+  JacobiRot r{1.0, 0.0, 1.0, 0.0};
+  const double ac = sqrt(fma(c.x, c.x, c.y * c.y));
+  if (ac > 1e-300 && ac > 1e-18 * sqrt(fabs(a * b))) {
+    const double tau = (b - a) / (2.0 * ac);
+    const double tt = (tau >= 0.0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(fma(tau, tau, 1.0)));
+    r.cs = 1.0 / sqrt(fma(tt, tt, 1.0));
+    r.sn = tt * r.cs;
+    r.er = c.x / ac;
+    r.ei = c.y / ac;
+  }
+  return r;
+}
+
+// Rows p, q of one column: p <- cs p - sn e^{i phi} q, q <- sn p + cs e^{i phi} q.
+__device__ __forceinline__ void jacobi_rows(cx<double>& p, cx<double>& q, const JacobiRot& r) {
+  const cx<double> ap = p;
+  const double ex = fma(r.er, q.x, -(r.ei * q.y)), ey = fma(r.ei, q.x, r.er * q.y);
+  p = {fma(r.cs, ap.x, -(r.sn * ex)), fma(r.cs, ap.y, -(r.sn * ey))};
+  q = {fma(r.sn, ap.x, r.cs * ex), fma(r.sn, ap.y, r.cs * ey)};
+}
+// Columns p, q of one row: p <- cs p - sn e^{-i phi} q, q <- sn p + cs e^{-i phi} q.
+__device__ __forceinline__ void jacobi_cols(cx<double>& p, cx<double>& q, const JacobiRot& r) {
+  const cx<double> ap = p;
+  const double ex = fma(r.er, q.x, r.ei * q.y), ey = fma(r.er, q.y, -(r.ei * q.x));
+  p = {fma(r.cs, ap.x, -(r.sn * ex)), fma(r.cs, ap.y, -(r.sn * ey))};
+  q = {fma(r.sn, ap.x, r.cs * ex), fma(r.sn, ap.y, r.cs * ey)};
+}
+
+// Both sides of the rotations on one block: rows of pair k, then columns of
+// pair l.
+__device__ __forceinline__ void jacobi_block(cx<double> (&b)[2][2], const JacobiRot& rk,
+                                             const JacobiRot& rl) {
+  if (rk.sn != 0.0) {
+    jacobi_rows(b[0][0], b[1][0], rk);
+    jacobi_rows(b[0][1], b[1][1], rk);
+  }
+  if (rl.sn != 0.0) {
+    jacobi_cols(b[0][0], b[0][1], rl);
+    jacobi_cols(b[1][0], b[1][1], rl);
+  }
+}
+
+// A = (S + S^H)/2 (ne x ne, the padding of odd n zero).
+__device__ __forceinline__ void jacobi_load(const cx<double>* __restrict__ S, int lds_, int n,
+                                            int ne, cx<double>* A, int lda) {
+  for (int e = threadIdx.x; e < ne * ne; e += 1024) {
+    const int i = e % ne, j = e / ne;
+    cx<double> v = {0.0, 0.0};
+    if (i < n && j < n) {
+      const cx<double> u = S[i + (size_t)j * lds_], w = S[j + (size_t)i * lds_];
+      v = {0.5 * (u.x + w.x), 0.5 * (u.y - w.y)};
+    }
+    A[i + j * lda] = v;
   }
   __syncthreads();
-  const int ne = n + (n & 1);  // players; index n is the dummy when n is odd
-  const int m = ne - 1, np = ne / 2;
-  for (int sweep = 0; sweep < max_sweeps; ++sweep) {
-    // convergence: off-diagonal vs whole Frobenius norm
-    double off = 0.0, all = 0.0;
-    for (int e = t; e < n * n; e += nt) {
-      const int i = e % n, j = e / n;
-      const cx<double> u = A[i + j * lda];
-      const double v = u.x * u.x + u.y * u.y;
-      all += v;
-      if (i != j) off += v;
-    }
-    red[t] = off;
-    __syncthreads();
-    for (int w = 512; w > 0; w >>= 1) {
-      if (t < w) red[t] += red[t + w];
-      __syncthreads();
-    }
-    const double off_sum = red[0];
-    __syncthreads();
-    red[t] = all;
-    __syncthreads();
-    for (int w = 512; w > 0; w >>= 1) {
-      if (t < w) red[t] += red[t + w];
-      __syncthreads();
-    }
-    if (t == 0) stop = !(off_sum > tol * tol * red[0]);
-    __syncthreads();
-    if (stop) break;
-    for (int st = 0; st < m; ++st) {
-      // the step's pairs: (st, m) and (st + k, st - k) mod m for k = 1 .. np - 1
-      for (int k = t; k < np; k += nt) {
-        int p, q;
-        if (k == 0) {
-          p = st;
-          q = m;
-        } else {
-          p = (st + k) % m;
-          q = (st - k + m) % m;
-        }
-        if (p > q) {
-          const int x = p;
-          p = q;
-          q = x;
-        }
-        JacobiRot r{p, q, 1.0, 0.0, 1.0, 0.0};
-        if (q < n) {
-          const double a = A[p + p * lda].x, b = A[q + q * lda].x;
-          const cx<double> c = A[p + q * lda];
-          const double ac = sqrt(c.x * c.x + c.y * c.y);
-          if (ac > 1e-300 && ac > 1e-18 * sqrt(fabs(a * b))) {
-            const double tau = (b - a) / (2.0 * ac);
-            const double tt = (tau >= 0.0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(1.0 + tau * tau));
-            r.cs = 1.0 / sqrt(1.0 + tt * tt);
-            r.sn = tt * r.cs;
-            r.er = c.x / ac;
-            r.ei = c.y / ac;
-          }
-        }
-        rot[k] = r;
-      }
-      __syncthreads();
-      // rows: A <- J^H A
-      for (int e = t; e < np * n; e += nt) {
-        const int k = e / n, col = e - k * n;
-        const JacobiRot r = rot[k];
-        if (r.q >= n || r.sn == 0.0) continue;
-        const cx<double> ap = A[r.p + col * lda], aq = A[r.q + col * lda];
-        // e^{i phi} aq
-        const cx<double> eq = {r.er * aq.x - r.ei * aq.y, r.er * aq.y + r.ei * aq.x};
-        A[r.p + col * lda] = {r.cs * ap.x - r.sn * eq.x, r.cs * ap.y - r.sn * eq.y};
-        A[r.q + col * lda] = {r.sn * ap.x + r.cs * eq.x, r.sn * ap.y + r.cs * eq.y};
-      }
-      __syncthreads();
-      // columns: A <- A J, V <- V J
-      for (int e = t; e < np * n; e += nt) {
-        const int k = e / n, row = e - k * n;
-        const JacobiRot r = rot[k];
-        if (r.q >= n || r.sn == 0.0) continue;
-        {
-          const cx<double> ap = A[row + r.p * lda], aq = A[row + r.q * lda];
-          // e^{-i phi} aq
-          const cx<double> eq = {r.er * aq.x + r.ei * aq.y, r.er * aq.y - r.ei * aq.x};
-          A[row + r.p * lda] = {r.cs * ap.x - r.sn * eq.x, r.cs * ap.y - r.sn * eq.y};
-          A[row + r.q * lda] = {r.sn * ap.x + r.cs * eq.x, r.sn * ap.y + r.cs * eq.y};
-        }
-        {
-          const cx<double> vp = V[row + (size_t)r.p * ldv], vq = V[row + (size_t)r.q * ldv];
-          const cx<double> eq = {r.er * vq.x + r.ei * vq.y, r.er * vq.y - r.ei * vq.x};
-          V[row + (size_t)r.p * ldv] = {r.cs * vp.x - r.sn * eq.x, r.cs * vp.y - r.sn * eq.y};
-          V[row + (size_t)r.q * ldv] = {r.sn * vp.x + r.cs * eq.x, r.sn * vp.y + r.cs * eq.y};
-        }
-      }
-      __syncthreads();
-    }
+}
+
+// Whether the off-diagonal Frobenius norm of A is at most tol times the whole
+// one (the same answer in every thread).
+__device__ __forceinline__ bool jacobi_converged(const cx<double>* A, int lda, int n, double tol) {
+  __shared__ double red[2][1024];
+  const int t = threadIdx.x;
+  double off = 0.0, all = 0.0;
+  for (int e = t; e < n * n; e += 1024) {
+    const int i = e % n, j = e / n;
+    const cx<double> u = A[i + j * lda];
+    const double v = fma(u.x, u.x, u.y * u.y);
+    all += v;
+    if (i != j) off += v;
   }
-  // sort: rank of eigenvalue i among all (ascending, ties by index)
-  for (int i = t; i < n; i += nt) {
+  red[0][t] = off;
+  red[1][t] = all;
+  __syncthreads();
+  for (int w = 512; w > 0; w >>= 1) {
+    if (t < w) {
+      red[0][t] += red[0][t + w];
+      red[1][t] += red[1][t + w];
+    }
+    __syncthreads();
+  }
+  const bool done = !(red[0][0] > tol * tol * red[1][0]);
+  __syncthreads();
+  return done;
+}
+
+// ctl[0] = the number of sweeps; the eigenvalues in ascending order (ties by
+// index) and the rank of diagonal entry i in ctl[1 + i].
+__device__ __forceinline__ void jacobi_finish(const cx<double>* A, int lda, int n, int sweeps,
+                                              int* __restrict__ ctl, double* __restrict__ evals) {
+  if (threadIdx.x == 0) ctl[0] = sweeps;
+  for (int i = threadIdx.x; i < n; i += 1024) {
     const double ei = A[i + i * lda].x;
     int rank = 0;
     for (int j = 0; j < n; ++j) {
@@ -228,8 +226,226 @@ __global__ __launch_bounds__(1024) void k_jacobi_eigh(const cx<double>* __restri
       rank += (ej < ei || (ej == ei && j < i)) ? 1 : 0;
     }
     evals[rank] = ei;
-    for (int r = 0; r < n; ++r) Vout[r + (size_t)rank * ldv] = V[r + (size_t)i * ldv];
+    ctl[1 + i] = rank;
   }
+}
+
+// Sweeps for n <= kJacobiLds, A in LDS.  Rotations of all steps, in order:
+// rots[(sweep m + st) np + k].  A thread owns the blocks (k, l) and
+// (k, l + dl) of every step.  The last wave forms the step's rotations (a
+// serial chain of square roots and divisions) while every wave reads its
+// blocks; after a barrier they are rotated and written back.  At n = 88 a step
+// takes 2.0 us on the one CU: the rotations 0.55, then LDS traffic (busy 56% of
+// the cycles) and the FP64 products (35% VALU issue) in turn.  The indices of a
+// pair are kept as byte offsets into A that advance by one index per step (and
+// are back at the first step's after m of them): no multiply or remainder in
+// the loop.
+struct JacobiPos {  // the two indices of a pair, as offsets of one stride
+  int x, y, dy, end, step;
+  __device__ __forceinline__ JacobiPos(int k, int m, int stride)
+      : x(k * stride), y((k ? m - k : m) * stride), dy(k ? stride : 0),
+        end(m * stride), step(stride) {}
+  __device__ __forceinline__ int p() const { return x < y ? x : y; }
+  __device__ __forceinline__ int q() const { return x < y ? y : x; }
+  __device__ __forceinline__ void advance() {
+    x += step;
+    x = x == end ? 0 : x;
+    y += dy;
+    y = y == end && dy ? 0 : y;  // pair 0 keeps the fixed index m
+  }
+};
+
+__global__ __launch_bounds__(1024) void k_jacobi_sweeps_lds(const cx<double>* __restrict__ S,
+                                                            int lds_, int n,
+                                                            JacobiRot* __restrict__ rots,
+                                                            int* __restrict__ ctl,
+                                                            double* __restrict__ evals,
+                                                            int max_sweeps, double tol) {
+  constexpr int LD = kJacobiLds;
+  constexpr int RB = (int)sizeof(cx<double>), CB = LD * RB;  // row and column strides in bytes
+  typedef double v2d __attribute__((ext_vector_type(2)));
+  __shared__ alignas(16) cx<double> A[LD * LD];
+  __shared__ v2d rot[2][LD / 2];  // (cs, sn) and (er, ei): 16-byte strides, no bank conflicts
+  static_assert((LD / 2) * ((LD / 2 + 1) / 2) <= 1024 && LD / 2 <= 64, "two blocks per thread");
+  const int t = threadIdx.x;
+  const int ne = n + (n & 1), m = ne - 1, np = ne / 2, dl = (np + 1) / 2;
+  jacobi_load(S, lds_, n, ne, A, LD);
+  const int k = t % np;
+  const bool has0 = t / np < dl, has1 = has0 && t / np + dl < np;
+  const int l0 = has0 ? t / np : 0, l1 = has1 ? l0 + dl : 0;
+  const int kr = t - 960;  // pair whose rotation this thread forms (last wave)
+  const bool rotator = kr >= 0 && kr < np;
+  const int kc = rotator ? kr : 0;
+  JacobiPos rk(k, m, RB), c0(l0, m, CB), c1(l1, m, CB), rr(kc, m, RB), rc(kc, m, CB);
+  auto at = [&](int off) {
+    const v2d v = *reinterpret_cast<const v2d*>(reinterpret_cast<const char*>(A) + off);
+    return cx<double>{v.x, v.y};
+  };
+  auto rotation = [&](int i) {
+    const v2d u = rot[0][i], w = rot[1][i];
+    return JacobiRot{u.x, u.y, w.x, w.y};
+  };
+  auto put = [&](int off, cx<double> v) {
+    *reinterpret_cast<v2d*>(reinterpret_cast<char*>(A) + off) = v2d{v.x, v.y};
+  };
+  int sweep = 0;
+  for (; sweep < max_sweeps; ++sweep) {
+    if (jacobi_converged(A, LD, n, tol)) break;
+    JacobiRot* out = rots + (size_t)sweep * m * np + kc;
+    for (int st = 0; st < m; ++st, out += np) {
+      if (rotator) {
+        JacobiRot r{1.0, 0.0, 1.0, 0.0};
+        const int p = rr.p(), q = rr.q(), pc = rc.p(), qc = rc.q();
+        if (q < n * RB) r = jacobi_rotation(at(p + pc).x, at(q + qc).x, at(p + qc));
+        rot[0][kr] = v2d{r.cs, r.sn};
+        rot[1][kr] = v2d{r.er, r.ei};
+        *out = r;
+      }
+      rr.advance();
+      rc.advance();
+      cx<double> b0[2][2], b1[2][2];
+      const int pk = rk.p(), qk = rk.q();
+      const int p0 = c0.p(), q0 = c0.q(), p1 = c1.p(), q1 = c1.q();
+      rk.advance();
+      c0.advance();
+      c1.advance();
+      b0[0][0] = at(pk + p0);
+      b0[1][0] = at(qk + p0);
+      b0[0][1] = at(pk + q0);
+      b0[1][1] = at(qk + q0);
+      b1[0][0] = at(pk + p1);
+      b1[1][0] = at(qk + p1);
+      b1[0][1] = at(pk + q1);
+      b1[1][1] = at(qk + q1);
+      __syncthreads();
+      const JacobiRot r = rotation(k);
+      if (has0) {
+        jacobi_block(b0, r, rotation(l0));
+        put(pk + p0, b0[0][0]);
+        put(qk + p0, b0[1][0]);
+        put(pk + q0, b0[0][1]);
+        put(qk + q0, b0[1][1]);
+      }
+      if (has1) {
+        jacobi_block(b1, r, rotation(l1));
+        put(pk + p1, b1[0][0]);
+        put(qk + p1, b1[1][0]);
+        put(pk + q1, b1[0][1]);
+        put(qk + q1, b1[1][1]);
+      }
+      __syncthreads();
+    }
+  }
+  jacobi_finish(A, LD, n, sweep, ctl, evals);
+}
+
+// Sweeps for larger n: A (ne x ne) in global memory (L2), block by block.
+__global__ __launch_bounds__(1024) void k_jacobi_sweeps(const cx<double>* __restrict__ S, int lds_,
+                                                        int n, cx<double>* __restrict__ A,
+                                                        JacobiRot* __restrict__ rots,
+                                                        int* __restrict__ ctl,
+                                                        double* __restrict__ evals,
+                                                        int max_sweeps, double tol) {
+  __shared__ JacobiRot rot[kJacobiMax / 2];
+  const int t = threadIdx.x;
+  const int ne = n + (n & 1), m = ne - 1, np = ne / 2;
+  jacobi_load(S, lds_, n, ne, A, ne);
+  // the thread's first block (k, l) and the step to its next one
+  const int k0 = t % np, l0 = t / np, dk = 1024 % np, dl = 1024 / np;
+  int sweep = 0;
+  for (; sweep < max_sweeps; ++sweep) {
+    if (jacobi_converged(A, ne, n, tol)) break;
+    JacobiRot* out = rots + (size_t)sweep * m * np;
+    for (int st = 0; st < m; ++st, out += np) {
+      for (int k = t; k < np; k += 1024) {
+        int p, q;
+        jacobi_pair(st, k, m, &p, &q);
+        JacobiRot r{1.0, 0.0, 1.0, 0.0};
+        if (q < n) r = jacobi_rotation(A[p + p * ne].x, A[q + q * ne].x, A[p + q * ne]);
+        rot[k] = r;
+        out[k] = r;
+      }
+      __syncthreads();
+      int k = k0, l = l0;
+      while (l < np) {
+        int pk, qk, pl, ql;
+        jacobi_pair(st, k, m, &pk, &qk);
+        jacobi_pair(st, l, m, &pl, &ql);
+        cx<double> b[2][2] = {{A[pk + pl * ne], A[pk + ql * ne]},
+                              {A[qk + pl * ne], A[qk + ql * ne]}};
+        jacobi_block(b, rot[k], rot[l]);
+        A[pk + pl * ne] = b[0][0];
+        A[pk + ql * ne] = b[0][1];
+        A[qk + pl * ne] = b[1][0];
+        A[qk + ql * ne] = b[1][1];
+        k += dk;
+        l += dl;
+        if (k >= np) {
+          k -= np;
+          ++l;
+        }
+      }
+      __syncthreads();
+    }
+  }
+  jacobi_finish(A, ne, n, sweep, ctl, evals);
+}
+
+// V = the product of the recorded rotations, columns in the order of the
+// ranks: one wave per row of V (the row in LDS; its DS operations stay in
+// order, so steps need no barrier).  The rotations of kJacobiAhead steps are
+// loaded while the previous ones are applied.
+constexpr int kJacobiAhead = 4;
+template <int PPL>  // pairs per lane: n <= 128 PPL
+__global__ __launch_bounds__(64) void k_jacobi_vectors(const JacobiRot* __restrict__ rots,
+                                                       const int* __restrict__ ctl, int n,
+                                                       cx<double>* __restrict__ Vout, int ldv) {
+  __shared__ cx<double> v[kJacobiMax];
+  const int row = blockIdx.x, lane = threadIdx.x;
+  const int ne = n + (n & 1), m = ne - 1, np = ne / 2;
+  for (int c = lane; c < ne; c += 64) v[c] = {c == row ? 1.0 : 0.0, 0.0};
+  const int steps = ctl[0] * m;
+  constexpr int D = kJacobiAhead;
+  JacobiRot r[D][PPL];
+  auto load = [&](JacobiRot (&x)[PPL], int s) {
+    const int sc = s < steps ? s : steps - 1;
+#pragma unroll
+    for (int u = 0; u < PPL; ++u) {
+      const int k = lane + 64 * u;
+      x[u] = rots[(size_t)sc * np + (k < np ? k : np - 1)];
+    }
+  };
+  int st = 0;
+  if (steps > 0)
+#pragma unroll
+    for (int d = 0; d < D; ++d) load(r[d], d);
+  for (int s0 = 0; s0 < steps; s0 += D) {
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      if (s0 + d < steps) {  // uniform
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int u = 0; u < PPL; ++u) {
+          const int k = lane + 64 * u;
+          const JacobiRot x = r[d][u];
+          if (k < np && x.sn != 0.0) {
+            int p, q;
+            jacobi_pair(st, k, m, &p, &q);
+            cx<double> vp = v[p], vq = v[q];
+            jacobi_cols(vp, vq, x);
+            v[p] = vp;
+            v[q] = vq;
+          }
+        }
+        st = st + 1 == m ? 0 : st + 1;
+      }
+      load(r[d], s0 + d + D);
+    }
+  }
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  for (int c = lane; c < n; c += 64) Vout[row + (size_t)ctl[1 + c] * ldv] = v[c];
 }
 
 }  // namespace
@@ -287,6 +503,20 @@ size_t hamiltonian_ws_bytes(ace_ctx c, const GridInfo& g, size_t eb, int nx, int
   return need;
 }
 
+// Rotations of up to kJacobiSweeps sweeps (at least one element for n = 1).
+static size_t jacobi_rot_bytes(int n) {
+  const size_t ne = n + (n & 1);
+  return kJacobiSweeps * (ne - 1) * (ne / 2) * sizeof(JacobiRot);
+}
+
+size_t ritz_ws_bytes(int n, long ng) {
+  const size_t mat = align_up((size_t)n * n * sizeof(cx<double>), 256);
+  const size_t ne = n + (n & 1);
+  return 2 * mat + align_up(ne * ne * sizeof(cx<double>), 256) +
+         align_up((1 + (size_t)n) * sizeof(int), 256) +
+         std::max(gemm_cn_scratch_bytes(n, n, ng), align_up(jacobi_rot_bytes(n), 256));
+}
+
 namespace {
 
 template <typename T>
@@ -294,22 +524,34 @@ ace_status rayleigh_ritz_t(ace_ctx c, const GridInfo& g, const cx<T>* X, long ld
                            const cx<T>* HX, long ldhx, int n, cx<T>* Xout, cx<T>* HXout,
                            long ldo, double* evals) {
   const size_t mat = align_up((size_t)n * n * sizeof(cx<double>), 256);
-  ACE_TRY(ws_begin(c, 4 * mat + gemm_cn_scratch_bytes(n, n, g.ng)));
+  const size_t ne = n + (n & 1);
+  ACE_TRY(ws_begin(c, ritz_ws_bytes(n, g.ng)));
   ace_status st = ACE_OK;
   cx<double>* S = (cx<double>*)ws_take(c, mat, &st);
-  cx<double>* A = (cx<double>*)ws_take(c, mat, &st);
-  cx<double>* V = (cx<double>*)ws_take(c, mat, &st);
   cx<double>* Q = (cx<double>*)ws_take(c, mat, &st);
-  if (!S || !A || !V || !Q) return st;
+  cx<double>* A = (cx<double>*)ws_take(c, ne * ne * sizeof(cx<double>), &st);
+  int* ctl = (int*)ws_take(c, (1 + (size_t)n) * sizeof(int), &st);
+  if (!S || !A || !ctl || !Q) return st;
+  const size_t used = c->ws_used;
   // S = dV X^H (H X), Hermitian for Hermitian H: upper tiles, lower mirrored
   ACE_TRY(gemm_cn<T>(c, X, ldx, n, HX, ldhx, n, g.ng, g.dV, S, n,
                      sizeof(T) == 8 ? kNative : kFp64, false, true));
+  // the rotations take the place of the reduction's partial sums, which the
+  // stream has consumed by then
+  c->ws_used = used;
+  JacobiRot* rots = (JacobiRot*)ws_take(c, jacobi_rot_bytes(n), &st);
+  if (!rots) return st;
   if (n <= kJacobiLds)
-    ACE_TRY(launch(c, "jacobi_eigh", k_jacobi_eigh<true>, dim3(1), dim3(1024), 0,
-                   (const cx<double>*)S, n, n, A, V, Q, n, evals, 30, 1e-15));
+    ACE_TRY(launch(c, "jacobi_sweeps", k_jacobi_sweeps_lds, dim3(1), dim3(1024), 0,
+                   (const cx<double>*)S, n, n, rots, ctl, evals, kJacobiSweeps, 1e-15));
   else
-    ACE_TRY(launch(c, "jacobi_eigh", k_jacobi_eigh<false>, dim3(1), dim3(1024), 0,
-                   (const cx<double>*)S, n, n, A, V, Q, n, evals, 30, 1e-15));
+    ACE_TRY(launch(c, "jacobi_sweeps", k_jacobi_sweeps, dim3(1), dim3(1024), 0,
+                   (const cx<double>*)S, n, n, A, rots, ctl, evals, kJacobiSweeps, 1e-15));
+  const auto vectors = n <= 128   ? k_jacobi_vectors<1>
+                       : n <= 256 ? k_jacobi_vectors<2>
+                                  : k_jacobi_vectors<4>;
+  ACE_TRY(launch(c, "jacobi_vectors", vectors, dim3(n), dim3(64), 0, (const JacobiRot*)rots,
+                 (const int*)ctl, n, Q, n));
   ACE_TRY(gemm_nn<T>(c, X, ldx, n, Q, n, n, Xout, ldo, g.ng, true));
   if (HXout) ACE_TRY(gemm_nn<T>(c, HX, ldhx, n, Q, n, n, HXout, ldo, g.ng, true));
   return ACE_OK;
