@@ -180,7 +180,8 @@ struct BuildPlan {
   int symblk;     // 0: the whole occupied triangle is one chunk; else block size
   bool merged;    // triangle and the extra bands' rectangle form one chunk
   size_t pairs_alloc;
-  size_t bytes;
+  size_t orb_bytes;  // transposed orbitals of a slab pass on split lines, or 0
+  size_t bytes;      // of everything
 };
 BuildPlan plan_build(ace_ctx c, const GridInfo& g, size_t elem_bytes, int nocc, int nband,
                      bool psi_starts_with_phi);
@@ -239,6 +240,22 @@ ace_status persist_run(ace_ctx c, int n, size_t eb, bool accq, const ace_plaunch
 // pair machinery with one "orbital" of ones and the kernel |G|^2 / 2 gives
 // ifftn(|G|^2/2 fftn(x)) (scale -1).
 constexpr int kKindKinetic = 2;
+
+// Slab and plane passes on split lines (split.hip), and the orbitals that the
+// slab pass takes: orbital b at b n^3 with its values in the order
+// [x0][x2][x1].  Spectra as for the other forms.
+// Compiled for the sizes that take them (fft_passes.hip).
+template <typename R>
+constexpr int kSplitSlabN = sizeof(R) == 8 ? 40 : 72;
+template <typename R>
+constexpr int kSplitPlaneN = sizeof(R) == 8 ? 40 : 64;
+template <typename R>
+ace_status split_slab(ace_ctx c, int n, const cx<R>* phi, const cx<R>* psi, cx<R>* buf, int mode,
+                      int i0, int A, int j0, long p0, int np);
+template <typename R>
+ace_status split_plane(ace_ctx c, int n, cx<R>* buf, const ace_kspec& ks, int np);
+template <typename V>
+ace_status orbital_transpose(ace_ctx c, int n, const V* x, long ldx, int count, V* y);
 
 // Pair FFT stages (fft_passes.hip).
 // W = scale * (*dscale if dscale else 1) * V_X[phi] psi   (accumulate: W += ...)

@@ -313,7 +313,7 @@ ace_status batched_persistent(ace_ctx c, int n_inst, const ace_instance* inst,
       const BuildPlan bp = plan_build(c, plan[k].g, ebs[k], in.n_occ, in.n_band,
                                       in.psi == in.phi && in.ld_psi == in.ld_phi);
       bk.off.push_back(bk.total);
-      bk.bytes.push_back(align_up(bp.bytes, 256));
+      bk.bytes.push_back(align_up(bp.bytes - bp.orb_bytes, 256));
       bk.total += bk.bytes.back();
     }
     c->budget_cap = 0;

@@ -28,6 +28,23 @@ template <typename T>
 __device__ __forceinline__ cx<T> cmul(cx<T> a, cx<T> b) {
   return {a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x};
 }
+// a b with the rounding written out: each part rounds one of its two products
+// by itself and fuses the other into the sum (re: a.y b.y is the rounded one,
+// with RE a.x b.x; im: a.y b.x, with IM a.x b.y).  The compiler's own choice
+// for cmul depends on the code around it.
+template <bool RE, bool IM, typename T>
+__device__ __forceinline__ cx<T> cmul_fma(cx<T> a, cx<T> b) {
+  return {RE ? fma(-a.y, b.y, a.x * b.x) : fma(a.x, b.x, -(a.y * b.y)),
+          IM ? fma(a.y, b.x, a.x * b.y) : fma(a.x, b.y, a.y * b.x)};
+}
+// conj(a) b likewise
+template <typename T>
+__device__ __forceinline__ cx<T> cmulc_fma(cx<T> a, cx<T> b) {
+  return {fma(a.x, b.x, a.y * b.y), fma(a.x, b.y, -(a.y * b.x))};
+}
+// Keeps a product out of the multiply-adds of what follows.
+__device__ __forceinline__ void keep_rounded(cx<float>& v) { asm("" : "+v"(v.x), "+v"(v.y)); }
+__device__ __forceinline__ void keep_rounded(cx<double>&) {}
 // conj(a) * b
 template <typename T>
 __device__ __forceinline__ cx<T> cmulc(cx<T> a, cx<T> b) {
@@ -109,7 +126,11 @@ __device__ __forceinline__ cx<T> root(int q) {
 // roots (1 +- i)/sqrt(2) cost no multiply or two, not the four of a general
 // complex product (a product by an exact 1 or 0 is not removed by the
 // compiler, since x * 0 is not 0 for every x in IEEE arithmetic).
-template <int N, int SIGN, typename T>
+//
+// PIN: the rounding of the products written out (cmul_fma), so that the value
+// does not depend on the surrounding code; for the lines of 9 and 16 it is the
+// rounding that the quad forms' lines of 18 and 16 were compiled to.
+template <int N, int SIGN, typename T, bool PIN = false>
 __device__ __forceinline__ cx<T> twiddle(cx<T> v, int q) {
   if (q == 0) return v;
   if (4 * q == N) return mul_si<SIGN>(v);
@@ -123,6 +144,13 @@ __device__ __forceinline__ cx<T> twiddle(cx<T> v, int q) {
     const T ci = (m == 1 || m == 3) ? T(SIGN) : T(-SIGN);
     // (cr + i ci)(x + i y) = (cr x - ci y) + i (cr y + ci x)
     return cx<T>{r * (cr * v.x - ci * v.y), r * (cr * v.y + ci * v.x)};
+  }
+  if constexpr (PIN) {
+    const cx<T> w = root<N, SIGN, T>(q);
+    const bool right = 4 * q < N || 4 * q > 3 * N;  // w in the right half plane
+    if constexpr (N == 16)
+      return right ? cmul_fma<(SIGN < 0), true>(v, w) : cmul_fma<(SIGN > 0), false>(v, w);
+    return right ? cmul_fma<false, (SIGN < 0)>(v, w) : cmul_fma<(SIGN < 0), (SIGN < 0)>(v, w);
   }
   return cmul(v, root<N, SIGN, T>(q));
 }
@@ -246,7 +274,7 @@ template <> struct Plan<96>  { template <template <int...> class F> using apply 
 // One Stockham stage of radix R when the sub-transforms already done have
 // length Ns: butterflies read stride N/R, apply exp(SIGN 2 pi i (j mod Ns) r /
 // (Ns R)), and scatter to (j / Ns) Ns R + (j mod Ns) + r Ns.
-template <int N, int S, int Ns, int R, typename T>
+template <int N, int S, int Ns, int R, typename T, bool PIN>
 __device__ __forceinline__ void stockham_stage(const cx<T>* in, cx<T>* out) {
 #pragma unroll
   for (int j = 0; j < N / R; ++j) {
@@ -256,7 +284,12 @@ __device__ __forceinline__ void stockham_stage(const cx<T>* in, cx<T>* out) {
     const int k = j % Ns;
     if (Ns > 1) {
 #pragma unroll
-      for (int r = 1; r < R; ++r) v[r] = twiddle<N, S, T>(v[r], (k * r * (N / (Ns * R))) % N);
+      for (int r = 1; r < R; ++r) {
+        const int q = (k * r * (N / (Ns * R))) % N;
+        v[r] = twiddle<N, S, T, PIN>(v[r], q);
+        // of two eighth roots that are added, the first is fused
+        if (PIN && r == 3 && 8 * q % N == 0) keep_rounded(v[r]);
+      }
     }
     SmallDft<R, S, T>::run(v);
     const int d = (j / Ns) * Ns * R + k;
@@ -265,21 +298,21 @@ __device__ __forceinline__ void stockham_stage(const cx<T>* in, cx<T>* out) {
   }
 }
 
-template <int N, int S, typename T, int Ns, int R, int... Rest>
+template <int N, int S, typename T, bool PIN, int Ns, int R, int... Rest>
 __device__ __forceinline__ void stockham_run(cx<T>* a, cx<T>* b) {
-  stockham_stage<N, S, Ns, R, T>(a, b);
+  stockham_stage<N, S, Ns, R, T, PIN>(a, b);
   if constexpr (sizeof...(Rest) > 0) {
-    stockham_run<N, S, T, Ns * R, Rest...>(b, a);
+    stockham_run<N, S, T, PIN, Ns * R, Rest...>(b, a);
   }
 }
 
 template <int... Rs>
 struct RadixList {
   static constexpr int count = sizeof...(Rs);
-  template <int N, int S, typename T>
+  template <int N, int S, typename T, bool PIN>
   __device__ __forceinline__ static void run(cx<T>* v) {
     cx<T> tmp[N];
-    stockham_run<N, S, T, 1, Rs...>(v, tmp);
+    stockham_run<N, S, T, PIN, 1, Rs...>(v, tmp);
     if constexpr (count % 2 == 1) {
 #pragma unroll
       for (int q = 0; q < N; ++q) v[q] = tmp[q];
@@ -309,10 +342,10 @@ constexpr int inv_mod(int a, int m) {
   return 1;
 }
 
-template <int N, int S, typename T>
+template <int N, int S, typename T, bool PIN = false>
 __device__ __forceinline__ void fft_line(cx<T>* v);
 
-template <int N, int S, typename T>
+template <int N, int S, typename T, bool PIN>
 __device__ __forceinline__ void fft_pfa(cx<T>* v) {
   constexpr int N1 = PfaSplit<N>::n1, N2 = PfaSplit<N>::n2;
   static_assert(N1 * N2 == N, "PFA split");
@@ -324,14 +357,14 @@ __device__ __forceinline__ void fft_pfa(cx<T>* v) {
 #pragma unroll
     for (int n1 = 0; n1 < N1; ++n1) a[n2][n1] = v[(n1 * N2 + n2 * N1) % N];
 #pragma unroll
-  for (int n2 = 0; n2 < N2; ++n2) fft_line<N1, S, T>(a[n2]);
+  for (int n2 = 0; n2 < N2; ++n2) fft_line<N1, S, T, PIN>(a[n2]);
   cx<T> b[N1][N2];
 #pragma unroll
   for (int k1 = 0; k1 < N1; ++k1)
 #pragma unroll
     for (int n2 = 0; n2 < N2; ++n2) b[k1][n2] = a[n2][k1];
 #pragma unroll
-  for (int k1 = 0; k1 < N1; ++k1) fft_line<N2, S, T>(b[k1]);
+  for (int k1 = 0; k1 < N1; ++k1) fft_line<N2, S, T, PIN>(b[k1]);
 #pragma unroll
   for (int k1 = 0; k1 < N1; ++k1)
 #pragma unroll
@@ -339,14 +372,14 @@ __device__ __forceinline__ void fft_pfa(cx<T>* v) {
 }
 
 // In-place length-N DFT of a register array.
-template <int N, int S, typename T>
+template <int N, int S, typename T, bool PIN>
 __device__ __forceinline__ void fft_line(cx<T>* v) {
   if constexpr (N == 1) {
     (void)v;
   } else if constexpr (PfaSplit<N>::n1 > 0) {
-    fft_pfa<N, S, T>(v);
+    fft_pfa<N, S, T, PIN>(v);
   } else {
-    Plan<N>::template apply<RadixList>::template run<N, S, T>(v);
+    Plan<N>::template apply<RadixList>::template run<N, S, T, PIN>(v);
   }
 }
 
@@ -542,6 +575,190 @@ __device__ __forceinline__ void fft_quad_b2d(cx<T>* v, int h) {
 // block position of value k on lane h
 __device__ __forceinline__ int quad_block_index(int k, int M, int h) {
   return k + M * (((h >> 1) | ((h & 1) << 1)));
+}
+
+// ---------------------------------------------------------------------------
+// Lines split over T lanes 64 / T apart (T = 1, 2, 4; N = T M), so that 64 / T
+// consecutive lanes hold the same part of as many consecutive lines and a
+// global access of theirs is one contiguous run.  Part h of a line holds
+//   decimated  x[h + T m],           m = 0..M-1
+//   split      X[split_pos(r, h)],   r = 0..M-1
+// and N = T x M: an M-point DFT per lane, twiddles exp(S 2 pi i h k / N), then
+// the T-point DFTs over the parts.  For those the values are transposed
+// between T registers and T lanes (the gfx950 permlane swaps exchange two
+// registers between lane halves in one instruction, one per value and level),
+// after which each lane owns whole T-point DFTs: k = T j + h of its register
+// group j, outputs X[T j + h + M q] in register T j + q.  Against butterflies
+// across lanes (fft_quad_*: a swap and a multiply-add per component and level)
+// this saves half of the exchange instructions.  Registers past the last whole
+// group (M mod T of them) keep the butterfly form and the block positions.
+template <int N, int T>
+struct Split {
+  static_assert(N % T == 0 && (T == 1 || T == 2 || T == 4), "split lines");
+  static constexpr int M = N / T;
+  static constexpr int D = 64 / T;         // lane distance of the parts
+  static constexpr int kGrouped = M - M % T;
+};
+
+// Position of register r of part h; kp(h) as for quads.
+template <int N, int T>
+__device__ __forceinline__ int split_pos(int r, int h) {
+  using P = Split<N, T>;
+  if constexpr (T == 1) return r;
+  if (r < P::kGrouped) return r - r % T + P::M * (r % T) + h;
+  return r + P::M * (T == 2 ? h : ((h >> 1) | ((h & 1) << 1)));
+}
+
+__device__ __forceinline__ void lane_swap16(float& a, float& b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, a),
+                                                  __builtin_bit_cast(unsigned, b), false, false);
+  a = __builtin_bit_cast(float, (unsigned)r[0]);
+  b = __builtin_bit_cast(float, (unsigned)r[1]);
+}
+__device__ __forceinline__ void lane_swap32(float& a, float& b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, a),
+                                                  __builtin_bit_cast(unsigned, b), false, false);
+  a = __builtin_bit_cast(float, (unsigned)r[0]);
+  b = __builtin_bit_cast(float, (unsigned)r[1]);
+}
+template <int D>
+__device__ __forceinline__ void lane_swap(float& a, float& b) {
+  if constexpr (D == 16)
+    lane_swap16(a, b);
+  else
+    lane_swap32(a, b);
+}
+template <int D>
+__device__ __forceinline__ void lane_swap(double& a, double& b) {
+  const unsigned long long u = __builtin_bit_cast(unsigned long long, a);
+  const unsigned long long w = __builtin_bit_cast(unsigned long long, b);
+  float al = __builtin_bit_cast(float, (unsigned)u), ah = __builtin_bit_cast(float, (unsigned)(u >> 32));
+  float bl = __builtin_bit_cast(float, (unsigned)w), bh = __builtin_bit_cast(float, (unsigned)(w >> 32));
+  lane_swap<D>(al, bl);
+  lane_swap<D>(ah, bh);
+  a = __builtin_bit_cast(double, ((unsigned long long)__builtin_bit_cast(unsigned, ah) << 32) |
+                                     __builtin_bit_cast(unsigned, al));
+  b = __builtin_bit_cast(double, ((unsigned long long)__builtin_bit_cast(unsigned, bh) << 32) |
+                                     __builtin_bit_cast(unsigned, bl));
+}
+template <int D, typename R>
+__device__ __forceinline__ void lane_swap(cx<R>& a, cx<R>& b) {
+  lane_swap<D>(a.x, b.x);
+  lane_swap<D>(a.y, b.y);
+}
+
+// v[q] of part h <-> v[h] of part q, q, h < T.
+template <int T, typename R>
+__device__ __forceinline__ void split_transpose(cx<R>* v) {
+  if constexpr (T == 2) {
+    lane_swap<32>(v[0], v[1]);
+  } else if constexpr (T == 4) {
+    lane_swap<16>(v[0], v[1]);
+    lane_swap<16>(v[2], v[3]);
+    lane_swap<32>(v[0], v[2]);
+    lane_swap<32>(v[1], v[3]);
+  }
+}
+
+// Twiddles exp(S 2 pi i h k / N), stored [k][h] ([0]: S = -1, [1]: S = +1).
+template <int N, int T, typename R>
+struct SplitRoots {
+  cx<R> w[2][N];
+  constexpr SplitRoots() : w() {
+    for (int k = 0; k < N / T; ++k)
+      for (int h = 0; h < T; ++h) {
+        const cs_pair p = ce_unit_root((long)h * k, N);
+        const bool one = h * k == 0;
+        w[0][T * k + h] = one ? cx<R>{R(1), R(0)} : cx<R>{R(p.c), R(-1 * p.s)};
+        w[1][T * k + h] = one ? cx<R>{R(1), R(0)} : cx<R>{R(p.c), R(p.s)};
+      }
+  }
+};
+template <int N, int T, typename R>
+__constant__ constexpr SplitRoots<N, T, R> kSplitRoots{};
+
+// Rounding of the twiddle products between the line and the exchange, chosen so
+// that FP32 values are those of the quad forms as they were compiled: the
+// product with the root's imaginary part is fused (kIm), the same but for the
+// registers that fft_line<M> leaves as plain sums (kImSums), or the one with
+// its real part (kRe).
+enum class TwRound { kIm, kImSums, kRe };
+
+// The lane's twiddles, from the tables in LDS (in registers they cost 2 M of
+// them, from memory a load each).
+template <int N, int T, typename R>
+struct SplitTw {
+  const cx<R>* s;
+  __device__ __forceinline__ SplitTw(int h, const cx<R>* lds) : s(lds + h) {}
+  template <int S, TwRound F>
+  __device__ __forceinline__ void apply(cx<R>* v) const {
+    if constexpr (T > 1) {
+#pragma unroll
+      for (int k = 1; k < N / T; ++k) {
+        const cx<R> w = s[(S > 0 ? N : 0) + T * k];
+        const bool sum = N / T % 3 == 0 ? k % 3 == 0 : 2 * k == N / T;
+        v[k] = F == TwRound::kRe || (F == TwRound::kImSums && sum)
+                   ? cmul_fma<false, false>(v[k], w)
+                   : cmul_fma<false, true>(v[k], w);
+      }
+    }
+  }
+};
+
+// The part's own line: with pinned rounding where FP32 results are to be those
+// of the quad forms.
+template <int N, int T, int S, typename R>
+__device__ __forceinline__ void split_line(cx<R>* v) {
+  fft_line<N / T, S, R, sizeof(R) == 4 && (N / T == 16 || N / T == 18)>(v);
+}
+
+// decimated -> split positions
+template <int N, int T, int S, TwRound F, typename R>
+__device__ __forceinline__ void fft_split(cx<R>* v, int h, const SplitTw<N, T, R>& tw) {
+  using P = Split<N, T>;
+  split_line<N, T, S, R>(v);
+  if constexpr (T > 1) {
+    tw.template apply<S, F>(v);
+#pragma unroll
+    for (int g = 0; g < P::kGrouped; g += T) {
+      split_transpose<T>(v + g);
+      SmallDft<T, S, R>::run(v + g);
+    }
+    if constexpr (P::kGrouped < P::M) {
+      static_assert(T == 4, "leftover registers only with four parts");
+      const bool hi = (h >> 1) != 0, odd = (h & 1) != 0;
+      const R sg_hi = hi ? R(-1) : R(1), sg_odd = odd ? R(-1) : R(1);
+#pragma unroll
+      for (int k = P::kGrouped; k < P::M; ++k) {
+        v[k] = xor_bfly<32>(v[k], sg_hi);
+        v[k] = xor_bfly<16>(hi && odd ? mul_si<S>(v[k]) : v[k], sg_odd);
+      }
+    }
+  }
+}
+
+// split positions -> decimated
+template <int N, int T, int S, TwRound F, typename R>
+__device__ __forceinline__ void fft_unsplit(cx<R>* v, int h, const SplitTw<N, T, R>& tw) {
+  using P = Split<N, T>;
+  if constexpr (T > 1) {
+#pragma unroll
+    for (int g = 0; g < P::kGrouped; g += T) {
+      SmallDft<T, S, R>::run(v + g);
+      split_transpose<T>(v + g);
+    }
+    if constexpr (P::kGrouped < P::M) {
+      const bool hi = (h >> 1) != 0, odd = (h & 1) != 0;
+      const R sg_hi = hi ? R(-1) : R(1), sg_odd = odd ? R(-1) : R(1);
+#pragma unroll
+      for (int k = P::kGrouped; k < P::M; ++k) {
+        v[k] = xor_bfly<16>(v[k], sg_odd);
+        v[k] = xor_bfly<32>(hi && odd ? mul_si<S>(v[k]) : v[k], sg_hi);
+      }
+    }
+    tw.template apply<S, F>(v);
+  }
+  split_line<N, T, S, R>(v);
 }
 
 // ---------------------------------------------------------------------------

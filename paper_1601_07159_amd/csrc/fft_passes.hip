@@ -19,8 +19,8 @@
 // The 1/N_g of the inverse transform, the minus sign and the caller's scale are
 // folded into the scaled kernel K'(G) = -scale K(G) / N_g, evaluated on the fly
 // in the plane pass from the per-axis factors (2 pi / L_a)^2 (no N_g table).
+#include <algorithm>
 #include <cmath>
-
 #include <vector>
 
 #include "ace_internal.h"
@@ -837,6 +837,47 @@ __global__ __launch_bounds__(1024) void k_sum_scaled(const double* __restrict__ 
 
 size_t default_pair_budget() { return (size_t)4 << 30; }
 
+// Line shape asked for (knob, else an autotuned one): 0 automatic.
+int line_shape(ace_ctx c, int n, int eb) {
+  if (c->fft_shape) return c->fft_shape;
+  const auto* t = tuned_for(c, n, eb);
+  return t ? t->shape : 0;
+}
+
+// The sizes from which the passes run on split lines (split_passes.h), measured
+// whole builds at 8 to 48 orbitals against the former forms: in FP64 from
+// N = 40 (one thread per line there: 637 -> 571 us at 32 orbitals; quads at
+// 64^3: 2,509 -> 2,199 us), where at N = 32 and 24 the two are within 5 % of
+// each other in either direction; in FP32 the plane pass from N = 64, the slab
+// pass at N = 72 (quads: 1,512 -> 1,267 us at 24 orbitals).  Below, one thread
+// per line runs at the copy rate already.  (kSplitSlabN, kSplitPlaneN)
+
+// Bytes of the transposed orbitals that a slab pass over `pairs` pairs takes on
+// split lines; 0: another form is used, because of the size or because the
+// copies (8 to 16 us at the smallest sizes) outweigh the pairs.
+size_t slab_split_bytes(const GridInfo& g, size_t eb, long pairs, long orbitals) {
+  if (g.n < (eb == sizeof(cx<double>) ? kSplitSlabN<double> : kSplitSlabN<float>)) return 0;
+  return pairs >= 4 * orbitals ? align_up((size_t)orbitals * g.ng * eb, 256) : 0;
+}
+
+// Whether split lines may be used: no other line shape is asked for, and the
+// passes are not recorded for the persistent runner.
+bool split_allowed(ace_ctx c, int n, size_t eb) {
+  return !c->record && line_shape(c, n, (int)eb) == 0;
+}
+
+// Workspace with room for `copies` bytes of transposed orbitals when those are
+// used (*split) and can be had: where the device memory, or a workspace that
+// may not grow, has no room for them the pass does without.
+ace_status split_ws_begin(ace_ctx c, size_t bytes, size_t copies, bool* split) {
+  if (*split) {
+    const ace_status st = ws_begin(c, bytes + copies);
+    if (st == ACE_OK || (st != ACE_E_NOMEM && st != ACE_E_CAPTURE)) return st;
+    *split = false;
+  }
+  return ws_begin(c, bytes);
+}
+
 }  // namespace
 
 size_t default_pair_budget_bytes() { return default_pair_budget(); }
@@ -852,7 +893,8 @@ long energy_chunk(ace_ctx c, const GridInfo& g, size_t eb, int nocc) {
 size_t energy_direct_ws_bytes(ace_ctx c, const GridInfo& g, size_t eb, int nocc) {
   const long total = (long)nocc * (nocc + 1) / 2;
   const long tiles = ((long)g.n * g.n + 63) / 64;
-  return align_up(((size_t)total * tiles + kSumBlocks) * sizeof(double), 256) +
+  return slab_split_bytes(g, eb, total, nocc) +
+         align_up(((size_t)total * tiles + kSumBlocks) * sizeof(double), 256) +
          align_up((size_t)energy_chunk(c, g, eb, nocc) * g.ng * eb, 256);
 }
 
@@ -915,7 +957,11 @@ BuildPlan plan_build(ace_ctx c, const GridInfo& g, size_t eb, int nocc, int nban
   pl.B = B;
   pl.A = (int)std::max<long>(1, std::min<long>(nocc, maxpairs / B));
   pl.pairs_alloc = std::max<size_t>((size_t)pl.A * pl.B, (size_t)sym_alloc);
-  pl.bytes = align_up(pl.pairs_alloc * pair_bytes, 256);
+  // transposed copies of psi, which holds phi too, or of both
+  pl.orb_bytes = slab_split_bytes(
+      g, eb, pl.sym ? tri + (long)nocc * (nband - nocc) : (long)nocc * nband,
+      psi_starts_with_phi ? nband : (long)nocc + nband);
+  pl.bytes = align_up(pl.pairs_alloc * pair_bytes, 256) + pl.orb_bytes;
   return pl;
 }
 
@@ -939,6 +985,7 @@ BuildPlan plan_build_real(ace_ctx c, const GridInfo& g, size_t cx_bytes, int noc
   if (maxunits < 1) maxunits = 1;
   pl.symblk = 0;
   pl.merged = false;
+  pl.orb_bytes = 0;
   const long sym_units = real_tri_units(nocc) + (long)((nocc + 1) / 2) * (nband - nocc);
   if (c->use_symmetry && psi_starts_with_phi && nocc >= 2 && jblock == 0 &&
       sym_units <= maxunits) {
@@ -978,33 +1025,26 @@ ace_kspec kspec_of(const GridInfo& g, double coef, const double* dscale = nullpt
 }
 
 // Line shape of the slab and plane passes: one thread per line (1), a lane
-// quad per line with DPP exchanges (4), an octet (8), or a line split over
-// lanes 16 apart with permlane exchanges (16).  Defaults from timings on the
-// MI355X: slab pass quad from N = 72 (FP32) or 64 (FP64), plane pass quad from
-// N = 64 (FP32) or 48 (FP64), one thread per line below.  The split form keeps
-// 16-lane accesses contiguous but pays two VALU instructions per exchanged
-// word where a DPP quad permutation rides on the consuming instruction: at
-// N = 72 it measured slower (slab 2.07 -> 2.72 ms, plane 2.3 -> 3.7 ms per
-// 1,146 pairs), at N = 48 too, so it is used only when asked for.  The tuning
-// knob ACE_TUNE_FFT_SHAPE overrides both passes, else an autotuned shape for
-// this grid size and element size.
-int line_shape(ace_ctx c, int n, int eb) {
-  if (c->fft_shape) return c->fft_shape;
-  const auto* t = tuned_for(c, n, eb);
-  return t ? t->shape : 0;
-}
-
+// quad per line with DPP exchanges (4), an octet (8), a line split over lanes
+// 16 apart with permlane exchanges and staged rows (16), or split lines without
+// staging (2, split_passes.h; the slab pass takes it by slab_split).  The tuning
+// knob ACE_TUNE_FFT_SHAPE (1, 4, 8, 16) overrides both passes, else an
+// autotuned shape for this grid size and element size.
 template <int N, typename T>
 constexpr bool kOctOk = N % 8 == 0 && N >= 16;
 
-// Form of the slab (plane_pass false) or plane pass: 1, 4, 8 or 16 as above.
+// Form of the slab pass on natural orbitals (plane_pass false) or of the plane
+// pass: 1, 2 (plane pass), 4, 8 or 16 as above.  The plane pass on split lines
+// against the former defaults: 72^3 FP32 1.79 against 2.39 ms (quads) per 1,146
+// pairs, 64^3 FP32 1.31 against 1.37 ms per 1,800; 40^3 FP64 0.55 against
+// 0.80 ms (one thread per line) per 1,353 pairs.
 template <int N, typename T>
 int pass_form(ace_ctx c, bool plane_pass) {
   const int sh = line_shape(c, N, (int)sizeof(cx<T>));
   if (sh == 8) return kOctOk<N, T> ? 8 : 4;
   if (sh == 1 || sh == 4 || sh == 16) return sh;
-  if (sizeof(T) == 8) return (plane_pass ? N >= 48 : N >= 64) ? 4 : 1;
-  return (plane_pass ? N >= 64 : N >= 72) ? 4 : 1;
+  if (plane_pass) return N >= kSplitPlaneN<T> ? 2 : 1;
+  return N >= (sizeof(T) == 8 ? 64 : 72) ? 4 : 1;
 }
 
 // Octet lines (N a multiple of 8 from 16) only on request (knob value 8):
@@ -1066,6 +1106,8 @@ ace_status plane(ace_ctx c, cx<T>* buf, const ace_kspec& ks, int np) {
   }
   const dim3 grid(xcd_pad((long)N * np));
   const int form = pass_form<N, T>(c, true);
+  if constexpr (N >= kSplitPlaneN<T>)
+    if (form == 2) return split_plane<T>(c, N, buf, ks, np);
   if constexpr (kOctOk<N, T>)
     if (form == 8)
       return launch(c, "plane_kernel", k_plane_kernel_oct<N, T>, grid, dim3(8 * N), 0, buf, ks,
@@ -1140,17 +1182,37 @@ ace_status build_W_n(ace_ctx c, const GridInfo& g, const cx<T>* phi, int nocc, l
   const bool sym = pl.sym;
   const size_t pairs_alloc = pl.pairs_alloc;
   ace_status st;
-  if ((st = ws_begin(c, pl.bytes)) != ACE_OK) return st;
+  bool split = pl.orb_bytes && split_allowed(c, N, sizeof(cx<T>));
+  if ((st = split_ws_begin(c, pl.bytes - pl.orb_bytes, pl.orb_bytes, &split)) != ACE_OK) return st;
   cx<T>* buf = (cx<T>*)ws_take(c, pairs_alloc * pair_bytes, &st);
   if (!buf) return st;
   if (c->record && dscale) return fail(c, ACE_E_UNSUPPORTED, "recorded build with a device scale");
   const ace_kspec ks = kspec_of(g, -scale / (double)g.ng, dscale);
+  // slab pass of a chunk, on the natural or the transposed orbitals; own: the
+  // bands come from psi (else from phi)
+  const cx<T>*phi_t = phi, *psi_t = psi;
+  if (split) {
+    cx<T>* orb = (cx<T>*)ws_take(c, pl.orb_bytes, &st);
+    if (!orb) return st;
+    if ((st = orbital_transpose<cx<T>>(c, N, psi, ldpsi, nband, orb)) != ACE_OK) return st;
+    psi_t = phi_t = orb;
+    if (!(psi == phi && ldpsi == ldphi)) {
+      phi_t = orb + (size_t)nband * g.ng;
+      if ((st = orbital_transpose<cx<T>>(c, N, phi, ldphi, nocc, orb + (size_t)nband * g.ng)) !=
+          ACE_OK)
+        return st;
+    }
+  }
+  auto slab = [&](bool own, int mode, int i0, int Ac, int j0, int np) {
+    if (split)
+      return split_slab<T>(c, N, phi_t, own ? psi_t : phi_t, buf, mode, i0, Ac, j0, 0L, np);
+    return fwd_slab<N, T>(c, phi, ldphi, own ? psi : phi, own ? ldpsi : ldphi, buf, mode, i0, Ac, j0,
+                          0L, np);
+  };
   int jstart = 0;
   if (pl.merged) {
     const long all = (long)nocc * (nocc + 1) / 2 + (long)nocc * (nband - nocc);
-    if ((st = fwd_slab<N, T>(c, phi, ldphi, psi, ldpsi, buf, 3, 0, nocc, nocc, 0L,
-                             (int)all)) != ACE_OK)
-      return st;
+    if ((st = slab(true, 3, 0, nocc, nocc, (int)all)) != ACE_OK) return st;
     if ((st = plane<N, T>(c, buf, ks, (int)all)) != ACE_OK) return st;
     return accum<N, T>(c, phi, ldphi, buf, W, ldW, 0, nocc, 0, nband, acc0, 3);
   }
@@ -1158,9 +1220,7 @@ ace_status build_W_n(ace_ctx c, const GridInfo& g, const cx<T>* phi, int nocc, l
     // occupied block: the triangle i <= j of pair spectra, every column j < n_occ
     // accumulates all i from it (u_ij = conj(u_ji))
     const long tri = (long)nocc * (nocc + 1) / 2;
-    if ((st = fwd_slab<N, T>(c, phi, ldphi, phi, ldphi, buf, 1, 0, 1, 0, 0L, (int)tri)) !=
-        ACE_OK)
-      return st;
+    if ((st = slab(false, 1, 0, 1, 0, (int)tri)) != ACE_OK) return st;
     if ((st = plane<N, T>(c, buf, ks, (int)tri)) != ACE_OK) return st;
     if ((st = accum<N, T>(c, phi, ldphi, buf, W, ldW, 0, nocc, 0, nocc, acc0, 1)) != ACE_OK)
       return st;
@@ -1176,9 +1236,7 @@ ace_status build_W_n(ace_ctx c, const GridInfo& g, const cx<T>* phi, int nocc, l
         const int j0 = J * b, nj = std::min(b, nocc - j0);
         if (I == J) {
           const int np = ni * (ni + 1) / 2;
-          if ((st = fwd_slab<N, T>(c, phi, ldphi, phi, ldphi, buf, 1, i0, 1, i0, 0L, np)) !=
-              ACE_OK)
-            return st;
+          if ((st = slab(false, 1, i0, 1, i0, np)) != ACE_OK) return st;
           if ((st = plane<N, T>(c, buf, ks, np)) != ACE_OK) return st;
           if ((st = accum<N, T>(c, phi, ldphi, buf, W, ldW, i0, ni, i0, ni, (int)started[I], 1)) !=
               ACE_OK)
@@ -1186,9 +1244,7 @@ ace_status build_W_n(ace_ctx c, const GridInfo& g, const cx<T>* phi, int nocc, l
           started[I] = 1;
         } else {
           const int np = ni * nj;
-          if ((st = fwd_slab<N, T>(c, phi, ldphi, phi, ldphi, buf, 0, i0, ni, j0, 0L, np)) !=
-              ACE_OK)
-            return st;
+          if ((st = slab(false, 0, i0, ni, j0, np)) != ACE_OK) return st;
           if ((st = plane<N, T>(c, buf, ks, np)) != ACE_OK) return st;
           // bands of J from the orbitals of I, then bands of I from those of J
           if ((st = accum<N, T>(c, phi, ldphi, buf, W, ldW, i0, ni, j0, nj, (int)started[J], 0)) !=
@@ -1208,9 +1264,7 @@ ace_status build_W_n(ace_ctx c, const GridInfo& g, const cx<T>* phi, int nocc, l
     for (int i0 = 0; i0 < nocc; i0 += A) {
       const int Ac = std::min(A, nocc - i0);
       const int np = Ac * Bc;
-      if ((st = fwd_slab<N, T>(c, phi, ldphi, psi, ldpsi, buf, 0, i0, Ac, j0, 0L, np)) !=
-          ACE_OK)
-        return st;
+      if ((st = slab(true, 0, i0, Ac, j0, np)) != ACE_OK) return st;
       if ((st = plane<N, T>(c, buf, ks, np)) != ACE_OK) return st;
       if ((st = accum<N, T>(c, phi, ldphi, buf, W, ldW, i0, Ac, j0, Bc, (i0 > 0 || accumulate) ? 1 : 0, 0)) !=
           ACE_OK)
@@ -1277,16 +1331,26 @@ ace_status energy_direct_n(ace_ctx c, const GridInfo& g, const cx<T>* phi, int n
   const long chunk = energy_chunk(c, g, sizeof(cx<T>), nocc);
   const size_t part_bytes = align_up(((size_t)total * TILES + kSumBlocks) * sizeof(double), 256);
   ace_status st;
-  if ((st = ws_begin(c, energy_direct_ws_bytes(c, g, sizeof(cx<T>), nocc))) != ACE_OK) return st;
+  const size_t copies = slab_split_bytes(g, sizeof(cx<T>), total, nocc);
+  bool split = copies && split_allowed(c, N, sizeof(cx<T>));
+  if ((st = split_ws_begin(c, energy_direct_ws_bytes(c, g, sizeof(cx<T>), nocc) - copies, copies,
+                           &split)) != ACE_OK)
+    return st;
   double* partial = (double*)ws_take(c, part_bytes, &st);
   cx<T>* buf = (cx<T>*)ws_take(c, (size_t)chunk * pair_bytes, &st);
   if (!partial || !buf) return st;
   const ace_kspec ks = kspec_of(g, 1.0);
+  cx<T>* orb = nullptr;
+  if (split) {
+    orb = (cx<T>*)ws_take(c, copies, &st);
+    if (!orb) return st;
+    if ((st = orbital_transpose<cx<T>>(c, N, phi, ldphi, nocc, orb)) != ACE_OK) return st;
+  }
   for (long p0 = 0; p0 < total; p0 += chunk) {
     const int np = (int)std::min(chunk, total - p0);
-    if ((st = fwd_slab<N, T>(c, phi, ldphi, phi, ldphi, buf, 1, 0, 1, 0, p0,
-                             np)) != ACE_OK)
-      return st;
+    st = orb ? split_slab<T>(c, N, orb, orb, buf, 1, 0, 1, 0, p0, np)
+             : fwd_slab<N, T>(c, phi, ldphi, phi, ldphi, buf, 1, 0, 1, 0, p0, np);
+    if (st != ACE_OK) return st;
     if ((st = launch(c, "pencil_energy", k_pencil_energy<N, T>, dim3(np * TILES), dim3(256), 0,
                      (const cx<T>*)buf, ks, p0, partial)) != ACE_OK)
       return st;

@@ -1,0 +1,89 @@
+"""The slab and plane passes on split lines (every size and precision that takes
+them) against the quad forms, which have the oracle tests: runs of pairs with
+every kind of remainder, the symmetric, rectangular and blocked plans, orbitals
+with a larger leading dimension, the direct energy, and a captured call whose
+workspace has no room for the transposed orbitals."""
+import pytest
+
+from paper_1601_07159_amd import synth
+from tests._helpers import ggrid, to_gpu
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n,prec,nocc,nband", [
+    (40, "fp64", 29, 33),   # runs of 8 (slab) and 4 (plane) and their remainders
+    (40, "fp64", 8, 8),     # the fewest pairs that take it, one per workgroup
+    (40, "fp64", 7, 7),     # one below
+    (48, "fp64", 17, 18),   # runs of 3
+    (64, "fp64", 12, 13),   # runs of 2
+    (72, "fp64", 11, 14),
+    (72, "fp32", 22, 25),   # runs of 8; a last wave half filled
+    (72, "fp32", 9, 9),
+    (64, "fp32", 17, 20),   # plane pass only
+])
+def test_split_lines_equal_quads(n, prec, nocc, nband):
+    import torch
+    from paper_1601_07159_amd import ace
+    print(f"split lines n={n} prec={prec} nocc={nocc} nband={nband}", flush=True)
+    L = 0.43 * n
+    gg = ggrid(n, L, "erfc", 0.2)
+    base = to_gpu(synth.smooth_orbitals(n, L, 6, seed=n), prec)
+    gen = torch.Generator(device="cuda").manual_seed(nband)
+    mix = torch.randn(nband, 6, dtype=base.dtype, device="cuda", generator=gen)
+    x = torch.zeros(nband, 2, n, n, n, dtype=base.dtype, device="cuda")[:, 0]
+    for b in range(nband):
+        for k in range(6):
+            x[b] += mix[b, k] * base[k]
+    pair = n ** 3 * base.element_size()
+    out = []
+    for shape in (0, 4):
+        ctx = ace.Context()
+        ctx.set_tuning("fft_shape", shape)
+        ctx.set_tuning("accum_shape", 16)
+        r = [ctx.build_W(x[:nocc], x, gg, prec), ctx.build_W(x[:nocc].clone(), x, gg, prec),
+             ctx.exchange_energy(x[:nocc].contiguous(), gg, prec)]
+        ctx.set_tuning("pair_budget", 37 * pair)
+        r += [ctx.build_W(x[:nocc], x, gg, prec), ctx.exchange_energy(x[:nocc].contiguous(), gg, prec)]
+        ctx.close()
+        out.append(r)
+    # FP64: some 3 log2(n) roundings per value on each of the two transforms,
+    # 40 eps = 9e-15 of the largest value; FP32 likewise 40 eps =
+    # 5e-6
+    for a, b in zip(*out):
+        err = float((a - b).abs().max() / b.abs().max())
+        assert err <= (1e-14 if prec == "fp64" else 5e-6), err
+
+
+def test_captured_without_room_for_copies():
+    import torch
+    from paper_1601_07159_amd import ace
+    n, nocc, nband = 40, 12, 14
+    print("split lines: captured without room for the copies", flush=True)
+    gg = ggrid(n, 0.43 * n)
+    x = to_gpu(synth.smooth_orbitals(n, 0.43 * n, nband, seed=5), "fp64")
+    ref = ace.Context()
+    ctx = ace.Context()
+    W = torch.zeros_like(x)
+    ctx.set_tuning("fft_shape", 4)       # takes no copies
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        ctx.build_W(x[:nocc], x, gg, "fp64", out=W)
+    torch.cuda.current_stream().wait_stream(side)
+    torch.cuda.synchronize()
+    ctx.set_tuning("fft_shape", 0)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        ctx.build_W(x[:nocc], x, gg, "fp64", out=W)
+    for rep in range(3):
+        x.mul_(1.0 + rep)
+        W.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        want = ref.build_W(x[:nocc], x, gg, "fp64")
+        # 40 eps of the largest value, as above
+        assert float((W - want).abs().max() / want.abs().max()) <= 1e-14
+    del graph
+    ctx.close()
+    ref.close()
