@@ -8,8 +8,8 @@
 // consecutive complex grid values (re0, im0, re1, im1) of its row; every real
 // becomes one K slot, so Re(conj(a) b) accumulates a_s b_s and Im(conj(a) b)
 // accumulates a_s b''_s with b'' = (im0, -re0, im1, -re1).  For the expansion
-// the K slots are orbitals: the streaming kernel forms Re y = ar cr - ai ci,
-// Im y = ar ci + ai cr (four real products), the resident one three real
+// the K slots are orbitals: the streaming kernel (more orbitals than fit) forms Re y = ar cr - ai ci,
+// Im y = ar ci + ai cr (four real products), the resident ones three real
 // products P1 = ar cr, P2 = ai ci, P3 = (ar + ai)(cr + ci) with Re y = P1 - P2,
 // Im y = P3 - P1 - P2 (Gauss).
 //
@@ -545,23 +545,15 @@ constexpr int kNnResA = 80;
 // workgroup: 256 orbitals x 64 columns x 8 bytes = 128 KiB of LDS.
 constexpr int kNnResA2 = 256;
 
-// upper: C is upper triangular (C[a][b] = 0 for a > b), so a step of four
-// orbitals past the last column of a 16-column block adds nothing to it and
-// its MFMAs are skipped (the triangular products xi = W L^{-H} and the
-// orthonormalisation's X R^{-1} do about 60% of the full work).
 template <typename TIn, typename TAcc, int NBB, int ACAP>
 __global__ __launch_bounds__(512) void k_nn_mfma_res(const cx<TIn>* __restrict__ A, long lda,
                                                      int na, const cx<double>* __restrict__ C,
                                                      int ldc, int nb, cx<TIn>* __restrict__ Y,
-                                                     long ldy, long K, int upper) {
+                                                     long ldy, long K) {
   typedef typename Acc4<TAcc>::type acc_t;
   constexpr int XB = NnShape<TAcc>::XB;
   constexpr int NBC = 16 * NBB;
   constexpr int R = sizeof(TIn) == 8 ? 4 : 8;  // grid-row loads in flight
-  // With 3 or 4 column blocks the skip branches make the register allocator
-  // spill the accumulators (hundreds of spills); there the zero blocks of an
-  // upper-triangular C are multiplied instead.
-  constexpr bool kSkip = NBB != 3 && NBB != 4;
   __shared__ TAcc cs_re[ACAP][NBC];
   __shared__ TAcc cs_im[ACAP][NBC];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -631,7 +623,6 @@ __global__ __launch_bounds__(512) void k_nn_mfma_res(const cx<TIn>* __restrict__
         if (st < nsteps) {
 #pragma unroll
           for (int y = 0; y < NBB; ++y) {
-            if (kSkip && upper && 4 * st > b0 + 16 * y + 15) continue;  // wave-uniform
             const TAcc cr = cb[j & 1][y][0], ci = cb[j & 1][y][1];
 #pragma unroll
             for (int x = 0; x < XB; ++x) {
@@ -670,7 +661,210 @@ __global__ __launch_bounds__(512) void k_nn_mfma_res(const cx<TIn>* __restrict__
   }
 }
 
+// ---------------------------------------------------------------------------
+// Expansion product with FP64 accumulation.  One workgroup of 8 waves per CU
+// keeps a slice of C's columns in LDS for the whole launch (up to kSliceElems
+// values; an upper triangular C needs only the rows above the slice's last
+// column) and its waves walk the 16-row tiles of Y.  The workgroups are dealt
+// out to the slices in proportion to their matrix work, and those of every
+// slice sweep the grid rows in the same order, so that A is read from HBM
+// about once.  Three real products (Gauss, as above).  C is the first operand
+// of the MFMAs: a lane's results belong to one grid row, and 16 lanes store 16
+// consecutive rows of a column.
+//
+// Bound by the FP64 matrix cores (64 cycles an MFMA), which are busy 70 % of
+// the time; the former kernel staged C again for every 64 rows and multiplied
+// four real products.  136 columns x 64^3 rows of FP32, triangular: 728 -> 334
+// us; 256 x 72^3: 2,008 -> 1,357 us (53 TFLOP/s of real products); 80 x 48^3:
+// 97 -> 68 us.
+constexpr int kSliceElems = 9728;  // 152 KiB of LDS
+constexpr int kSliceBlocks = 5;    // 16-column blocks: 120 accumulator registers
+constexpr int kMaxSlices = 32;
+struct NnSlices {
+  int n;
+  int wg0[kMaxSlices + 1];  // first workgroup of every slice
+  int b0[kMaxSlices + 1];   // first column of every slice
+};
+
+// XB tiles of 16 grid rows at a time: narrow slices take several, so that the
+// loads of three steps ahead cover the memory latency.
+template <typename TIn, int NBB>
+__device__ __forceinline__ void nn_slice_body(double2* cs, const cx<TIn>* __restrict__ A, long lda,
+                                              int na, const cx<double>* __restrict__ C, int ldc,
+                                              int b0, int nb, cx<TIn>* __restrict__ Y, long ldy,
+                                              long K, int upper, int wg, int nwg) {
+  constexpr int W = 16 * NBB, XB = NBB == 1 ? 4 : NBB == 2 ? 2 : 1;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int r16 = lane & 15, kq = lane >> 4;
+  const int rows = upper && b0 + W < na ? b0 + W : na;
+  const int groups = (rows + 15) / 16;  // of 16 orbitals: four MFMA steps
+  for (int e = threadIdx.x; e < 16 * groups * W; e += 512) {
+    const int bb = e / (16 * groups), aa = e - bb * (16 * groups);  // down the columns of C
+    double2 v = {0.0, 0.0};
+    if (aa < na && b0 + bb < nb) {
+      const cx<double> cv = C[aa + (size_t)(b0 + bb) * ldc];
+      v = {cv.x, cv.y};
+    }
+    cs[aa * W + bb] = v;
+  }
+  __syncthreads();
+  const long ntiles = (K + 16 * XB - 1) / (16 * XB), stride = (long)nwg * 8;
+  const int steps = 4 * groups;
+  // Unconditional loads from clamped addresses, three steps ahead and from one
+  // tile into the next: an orbital past n_a meets zero rows of C, a grid row
+  // past K is not stored.  C is read from LDS one step ahead; the scheduling
+  // barriers keep the compiler from reading further ahead than the registers
+  // reach.
+  cx<TIn> x[4][XB];
+  long row[XB], row_next[XB];
+  auto rows_of = [&](long (&rw)[XB], long tile) {
+#pragma unroll
+    for (int q = 0; q < XB; ++q) {
+      const long r = (tile * XB + q) * 16 + r16;
+      rw[q] = r < K ? r : K - 1;
+    }
+  };
+  auto load = [&](cx<TIn> (&v)[XB], int st) {
+    const bool here = st < steps;  // wave-uniform
+    const int o = 4 * (here ? st : st - steps) + kq;
+    const cx<TIn>* a = A + (size_t)(o < na ? o : na - 1) * lda;
+#pragma unroll
+    for (int q = 0; q < XB; ++q) v[q] = a[here ? row[q] : row_next[q]];
+  };
+  long tile = (long)wg * 8 + wave;
+  if (tile >= ntiles) return;
+  rows_of(row, tile);
+  rows_of(row_next, tile + stride);
+#pragma unroll
+  for (int u = 0; u < 3; ++u) load(x[u], u);
+  for (; tile < ntiles; tile += stride) {
+    v4d p1[XB][NBB], p2[XB][NBB], p3[XB][NBB];
+#pragma unroll
+    for (int q = 0; q < XB; ++q)
+#pragma unroll
+      for (int y = 0; y < NBB; ++y) p1[q][y] = p2[q][y] = p3[q][y] = v4d{0, 0, 0, 0};
+    double2 c[2][NBB];
+    auto loadc = [&](auto first, double2 (&cv)[NBB], int st) {
+      constexpr int F = decltype(first)::value;
+      const double2* p = cs + (4 * st + kq) * W + r16;
+#pragma unroll
+      for (int y = F; y < NBB; ++y) cv[y] = p[16 * y];
+    };
+    // the four steps of group g on blocks F..NBB-1
+    auto run = [&](auto first, int g) {
+      constexpr int F = decltype(first)::value;
+      loadc(first, c[0], 4 * g);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        load(x[(u + 3) & 3], 4 * g + u + 3);
+        if (u < 3) loadc(first, c[(u + 1) & 1], 4 * g + u + 1);
+#pragma unroll
+        for (int q = 0; q < XB; ++q) {
+          const double xr = (double)x[u][q].x, xi = (double)x[u][q].y, xs = xr + xi;
+#pragma unroll
+          for (int y = F; y < NBB; ++y) {
+            const double2 cv = c[u & 1][y];
+            p1[q][y] = mfma4(cv.x, xr, p1[q][y]);
+            p2[q][y] = mfma4(cv.y, xi, p2[q][y]);
+            p3[q][y] = mfma4(cv.x + cv.y, xs, p3[q][y]);
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    // an upper triangular C: block y ends with the orbitals of its own columns
+    const int whole = upper && b0 / 16 + 1 < groups ? b0 / 16 + 1 : groups;
+    for (int g = 0; g < whole; ++g) run(std::integral_constant<int, 0>{}, g);
+    if constexpr (NBB > 1)
+      if (whole < groups) run(std::integral_constant<int, 1>{}, whole);
+    if constexpr (NBB > 2)
+      if (whole + 1 < groups) run(std::integral_constant<int, 2>{}, whole + 1);
+    if constexpr (NBB > 3)
+      if (whole + 2 < groups) run(std::integral_constant<int, 3>{}, whole + 2);
+    if constexpr (NBB > 4)
+      if (whole + 3 < groups) run(std::integral_constant<int, 4>{}, whole + 3);
+#pragma unroll
+    for (int q = 0; q < XB; ++q) {
+      const bool in = (tile * XB + q) * 16 + r16 < K;
+#pragma unroll
+      for (int y = 0; y < NBB; ++y)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int b = b0 + 16 * y + mfma_row<double>(lane, v);
+          if (b < nb && in)
+            Y[(size_t)b * ldy + row[q]] = {(TIn)(p1[q][y][v] - p2[q][y][v]),
+                                           (TIn)(p3[q][y][v] - p1[q][y][v] - p2[q][y][v])};
+        }
+      row[q] = row_next[q];
+    }
+    rows_of(row_next, tile + 2 * stride);
+  }
+}
+
+template <typename TIn>
+__global__ __launch_bounds__(512) void k_nn_f64(const cx<TIn>* __restrict__ A, long lda, int na,
+                                                const cx<double>* __restrict__ C, int ldc,
+                                                cx<TIn>* __restrict__ Y, long ldy, long K,
+                                                int upper, NnSlices sl) {
+  __shared__ double2 cs[kSliceElems];
+  int q = 0;
+  while (q + 1 < sl.n && (int)blockIdx.x >= sl.wg0[q + 1]) ++q;
+  const int wg = (int)blockIdx.x - sl.wg0[q], nwg = sl.wg0[q + 1] - sl.wg0[q];
+  const int b0 = sl.b0[q], nb = sl.b0[q + 1];
+#define ACE_BODY(NBBV)                                                                     \
+  nn_slice_body<TIn, NBBV>(cs, A, lda, na, C, ldc, b0, nb, Y, ldy, K, upper, wg, nwg)
+  switch ((nb - b0 + 15) / 16) {
+    case 1: ACE_BODY(1); break;
+    case 2: ACE_BODY(2); break;
+    case 3: ACE_BODY(3); break;
+    case 4: ACE_BODY(4); break;
+    case 5: ACE_BODY(5); break;
+  }
+#undef ACE_BODY
+}
+
 }  // namespace
+
+// Column slices of an expansion product in FP64 and the workgroups of each;
+// false when n_a is too large for a slice of 16 columns in LDS or the slices
+// are too many.
+static bool nn_slices(int na, int nb, long K, bool upper, NnSlices* s, unsigned* grid) {
+  double work[kMaxSlices], total = 0;
+  s->n = 0;
+  for (int b0 = 0; b0 < nb;) {
+    if (s->n == kMaxSlices) return false;
+    const int left = (nb - b0 + 15) / 16;
+    int w = left < kSliceBlocks ? left : kSliceBlocks;
+    auto groups = [&](int blocks) {
+      const int rows = upper && b0 + 16 * blocks < na ? b0 + 16 * blocks : na;
+      return (rows + 15) / 16;
+    };
+    while (w > 0 && 256 * groups(w) * w > kSliceElems) --w;
+    if (w == 0) return false;
+    const int even = (left + w - 1) / w;  // slices still to come, of like widths
+    w = (left + even - 1) / even;
+    double wk = 3;  // a tile's stores, in groups of MFMAs
+    for (int y = 0; y < w; ++y) wk += groups(upper ? y + 1 : w);
+    work[s->n] = wk;
+    total += wk;
+    s->b0[s->n++] = b0;
+    b0 += 16 * w;
+  }
+  s->b0[s->n] = nb;
+  const long most = ((K + 15) / 16 + 7) / 8;  // one tile per wave
+  int at = 0;
+  double sum = 0;
+  for (int q = 0; q < s->n; ++q) {
+    s->wg0[q] = at;
+    sum += work[q];
+    int to = (int)(256 * sum / total + 0.5);  // workgroups of the slices so far
+    if (to < at + 1) to = at + 1;
+    at = (int)(to - at < most ? to : at + most);
+  }
+  s->wg0[s->n] = at;
+  *grid = (unsigned)at;
+  return true;
+}
 
 // Workgroup shape and K split of a reduction product: TA x TB waves per
 // workgroup, at most max_waves (16 for the FP32 kernel, 12 for the BF16-split
@@ -803,6 +997,15 @@ template <typename TIn, typename TAcc>
 static ace_status nn_dispatch(ace_ctx c, const char* name, const cx<TIn>* A, long lda, int na,
                               const cx<double>* C, int ldc, int nb, cx<TIn>* Y, long ldy,
                               long K, bool c_upper) {
+  // In FP64 slices of C in LDS, up to 608 orbitals and 32 slices; past that C is
+  // staged chunk by chunk.
+  if constexpr (sizeof(TAcc) == 8) {
+    NnSlices sl;
+    unsigned grid;
+    if (nn_slices(na, nb, K, c_upper, &sl, &grid))
+      return launch(c, name, k_nn_f64<TIn>, dim3(grid), dim3(512), 0, A, lda, na, C, ldc, Y, ldy,
+                    K, c_upper ? 1 : 0, sl);
+  }
   const int nbb = nb <= 16 ? 1 : nb <= 32 ? 2 : nb <= 48 ? 3 : nb <= 80 && nb > 64 ? 5 : 4;
   const dim3 block(256);
   const bool resident = na <= kNnResA;
@@ -815,13 +1018,15 @@ static ace_status nn_dispatch(ace_ctx c, const char* name, const cx<TIn>* A, lon
     const long cap = (256 + gy - 1) / gy;                                                      \
     if (gx > cap) gx = cap;                                                                    \
     return launch(c, name, k_nn_mfma_res<TIn, TAcc, NBBV, CAP>, dim3((unsigned)gx, gy),        \
-                  dim3(512), 0, A, lda, na, C, ldc, nb, Y, ldy, K, c_upper ? 1 : 0);           \
+                  dim3(512), 0, A, lda, na, C, ldc, nb, Y, ldy, K);                            \
   }
 #define ACE_NN(NBBV)                                                                           \
   case NBBV: {                                                                                 \
-    if (resident) ACE_NN_RES(NBBV, kNnResA)                                                    \
-    if constexpr (sizeof(TAcc) == 4 && NBBV <= 4)                                              \
-      if (resident2) ACE_NN_RES(NBBV, kNnResA2)                                                \
+    if constexpr (sizeof(TAcc) == 4) {                                                         \
+      if (resident) ACE_NN_RES(NBBV, kNnResA)                                                  \
+      if constexpr (NBBV <= 4)                                                                 \
+        if (resident2) ACE_NN_RES(NBBV, kNnResA2)                                              \
+    }                                                                                          \
     const long rows = NnShape<TAcc>::ROWS;                                                    \
     const dim3 grid((unsigned)((K + rows - 1) / rows), gy);                                    \
     return launch(c, name, k_nn_mfma<TIn, TAcc, NBBV>, grid, block, 0, A, lda, na, C, ldc, nb, Y, \

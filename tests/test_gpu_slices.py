@@ -1,0 +1,48 @@
+"""The FP64 expansion product (Y = A C with C's columns in LDS slices) at its
+edges: one column, every slice width, a cut last block, slices of different
+widths, orbital counts that are no multiple of 16, the largest count whose
+slices fit and the first one past it, and grids whose last tile is cut."""
+import numpy as np
+import pytest
+
+import oracle as O
+from paper_1601_07159_amd import synth
+from tests._helpers import ggrid, ogrid, to_gpu, to_np
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n,nb,nx", [(12, 1, 1), (8, 17, 33), (12, 80, 81), (12, 97, 48), (16, 136, 64),
+                                     (8, 145, 96), (16, 256, 70), (16, 304, 40), (16, 608, 17),
+                                     (16, 609, 17)])
+def test_apply_products(n, nb, nx):
+    from paper_1601_07159_amd import ace
+    print(f"expansion products n={n} nb={nb} nx={nx}", flush=True)
+    L = 0.43 * n
+    g, gg = ogrid(n, L), ggrid(n, L)
+    rng = np.random.default_rng(nb)
+    xi = rng.standard_normal((nb, n ** 3)) + 1j * rng.standard_normal((nb, n ** 3))
+    X = rng.standard_normal((nx, n ** 3)) + 1j * rng.standard_normal((nx, n ** 3))
+    Y = to_np(ace.apply(to_gpu(xi.reshape(nb, n, n, n), "fp64"), to_gpu(X.reshape(nx, n, n, n), "fp64"),
+                        gg, "fp64")).reshape(nx, -1)
+    ref = -g.dV * (xi.conj() @ X.T).T @ xi
+    # sums over N_g and then nb: sqrt(4096 + 609) eps = 1.5e-14 of the largest
+    # value, ten times that
+    assert np.max(np.abs(Y - ref)) <= 1.5e-13 * np.max(np.abs(ref))
+
+
+@pytest.mark.parametrize("n,nb", [(8, 1), (12, 15), (16, 80), (16, 81), (16, 136), (16, 257)])
+def test_triangular_products(n, nb):
+    from paper_1601_07159_amd import ace
+    print(f"triangular products n={n} nb={nb}", flush=True)
+    L = 0.43 * n
+    g = ogrid(n, L)
+    rng = np.random.default_rng(nb)
+    X = rng.standard_normal((nb, n ** 3)) + 1j * rng.standard_normal((nb, n ** 3))
+    Q = to_np(ace.orthonormalize(to_gpu(X.reshape(nb, n, n, n), "fp64"), ggrid(n, L), "fp64"))
+    Q = Q.reshape(nb, -1)
+    assert np.max(np.abs(g.dV * (Q.conj() @ Q.T) - np.eye(nb))) <= 1e-12
+    # Q spans X in order: R = <Q, X> is upper triangular
+    R = g.dV * (Q.conj() @ X.T)
+    assert np.max(np.abs(np.tril(R, -1))) <= 1e-12 * np.max(np.abs(R))
+    assert np.max(np.abs(R.T @ Q - X)) <= 1e-12 * np.max(np.abs(X))
