@@ -17,6 +17,7 @@
 // l/16] and B[k group l/16][col l%16]; the 16x16 result sits in 4 registers of
 // column l%16: rows 4(l/16)+v for the FP32-result instructions, rows l/16+4v
 // for the FP64 one (measured on gfx950).
+#include <algorithm>
 #include <type_traits>
 
 #include "ace_internal.h"
@@ -375,9 +376,10 @@ __global__ __launch_bounds__(1024) void k_reduce_partials2(const cx<P>* __restri
   const int el = threadIdx.x & 63, g = threadIdx.x >> 6;
   const int idx = blockIdx.x * 64 + el;
   const int a = idx % na, b = idx / na;
-  // Hermitian mode: tiles below the diagonal were not computed; the entries
-  // of the tiles above it are written twice, the second time conjugated
-  const bool live = idx < na * nb && !(herm && a / 32 > b / 32);
+  // Hermitian mode (herm: the side of a tile): tiles below the diagonal were not
+  // computed; the entries of the tiles above it are written twice, the second
+  // time conjugated
+  const bool live = idx < na * nb && !(herm && a / herm > b / herm);
   double sr = 0.0, si = 0.0;
   if (live) {
     const cx<P>* p = partial + idx;
@@ -414,7 +416,145 @@ __global__ __launch_bounds__(1024) void k_reduce_partials2(const cx<P>* __restri
   if (g == 0 && live) {
     const double re = alpha * red[0][0][el], im = real_part ? 0.0 : alpha * red[1][0][el];
     C[a + (size_t)b * ldc] = {re, im};
-    if (herm && a / 32 < b / 32) C[b + (size_t)a * ldc] = {re, -im};
+    if (herm && a / herm < b / herm) C[b + (size_t)a * ldc] = {re, -im};
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Reduction product in FP64 of 49 rows and more: the 16 x 16 blocks of the
+// output (only those on and above the diagonal in the Hermitian case) are
+// dealt out evenly to the 8 waves of a workgroup, up to kGramBlocks each, and
+// to as many workgroup rows as that takes; K is split over blockIdx.y, one
+// workgroup per CU.  The rows of both operands come to LDS in chunks by loads
+// that write LDS directly, one chunk ahead.  A row's 16-byte segments are
+// permuted by its number (exclusive or), so that 16 rows read at one segment
+// touch all banks once.  Three real products (Gauss): with P1 = ar br, P2 =
+// ai bi, P3 = (ar - ai)(br + bi), Re = P1 + P2 and Im = P3 - P1 + P2; P3 is
+// left out where the real part is all that is asked for.
+//
+// Bound by the FP64 matrix cores (65 % busy) and the conversions and sums that
+// share the FP64 units with them, so a wave's blocks share a column of B where
+// they can.  136 rows x 64^3 points of FP32: 568 -> 342 us (tiles of 32 with
+// four products, two unequal workgroup rows); 256 x 72^3: 2,031 -> 1,522 us.
+// Converting to FP64 on the way to LDS doubled the LDS reads: 364, 1,943 us.
+constexpr int kGramBlocks = 8;           // 192 accumulator registers
+constexpr int kGramBuffer = 76 * 1024;   // bytes of one of two chunks
+struct GramShape {
+  int gx, per;      // workgroup rows, blocks of each
+  int lseg;         // 2^lseg segments of 16 bytes per row and chunk
+  int same, herm;   // one operand; upper blocks only
+  long ks, kchunk;  // K split
+};
+
+__device__ __forceinline__ void gram_block(int q, int ta, int herm, int& x, int& y) {
+  if (herm) {  // column by column of the upper triangle
+    y = 0;
+    while (q > y) q -= ++y;
+    x = q;
+  } else {
+    y = q / ta;
+    x = q - y * ta;
+  }
+}
+
+template <typename T, int NBW, bool REAL>
+__global__ __launch_bounds__(512) void k_cn_f64(const cx<T>* __restrict__ A, long lda, int na,
+                                                const cx<T>* __restrict__ B, long ldb, int nb,
+                                                long K, cx<double>* __restrict__ partial,
+                                                GramShape g) {
+  constexpr int PT = 16 / sizeof(cx<T>);  // points of a segment
+  __shared__ __align__(16) char lds[2][kGramBuffer];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int r16 = lane & 15, kq = lane >> 4;
+  const int ta = (na + 15) / 16, tb = (nb + 15) / 16;
+  const int total = g.herm ? tb * (tb + 1) / 2 : ta * tb;
+  const int q0 = blockIdx.x * g.per, q1 = q0 + g.per < total ? q0 + g.per : total;
+  if (q0 >= q1) return;
+  // blocks of this wave, most of them in one column, and the rows that the
+  // workgroup reads
+  const int first_q = q0 + NBW * wave, count = q1 - first_q;  // of NBW
+  int bx[NBW], by[NBW];
+#pragma unroll
+  for (int i = 0; i < NBW; ++i)
+    gram_block(first_q + i < q1 ? first_q + i : q1 - 1, ta, g.herm, bx[i], by[i]);
+  int fx, fy, lx, ly;
+  gram_block(q0, ta, g.herm, fx, fy);
+  gram_block(q1 - 1, ta, g.herm, lx, ly);
+  const int ra = 16 * (g.herm ? ly + 1 : ta);      // rows of A: from 0
+  const int rb = g.same ? 0 : 16 * (ly - fy + 1);  // rows of B: from 16 fy
+  const int seg = 1 << g.lseg, swz = seg - 1 < 15 ? seg - 1 : 15;
+  const int loads = (ra + rb) * seg / 64;          // wave loads of 1 KiB
+  const long kbeg = (long)blockIdx.y * g.kchunk;
+  const long kend = kbeg + g.kchunk < K ? kbeg + g.kchunk : K;
+  auto stage = [&](char* dst, long k0) {
+    for (int e = wave; e < loads; e += 8) {
+      const int slot = 64 * e + lane, row = slot >> g.lseg;
+      const int sg = (slot & (seg - 1)) ^ (row & swz);
+      const bool first = row < ra;
+      const int r = first ? row : 16 * fy + row - ra, lim = (first ? na : nb) - 1;
+      const cx<T>* src =
+          (first ? A : B) + (size_t)(r < lim ? r : lim) * (first ? lda : ldb) + k0 + (long)sg * PT;
+      __builtin_amdgcn_global_load_lds(
+          (const __attribute__((address_space(1))) void*)src,
+          (__attribute__((address_space(3))) void*)(dst + (size_t)e * 1024), 16, 0, 0);
+    }
+  };
+  v4d p1[NBW], p2[NBW], p3[REAL ? 1 : NBW];
+#pragma unroll
+  for (int i = 0; i < NBW; ++i) p1[i] = p2[i] = v4d{0, 0, 0, 0};
+#pragma unroll
+  for (int i = 0; i < (REAL ? 1 : NBW); ++i) p3[i] = v4d{0, 0, 0, 0};
+  const int boff = g.same ? 0 : ra - 16 * fy;  // LDS row of B's row 0
+  typedef T seg_t __attribute__((ext_vector_type(16 / sizeof(T))));
+  const long step = (long)seg * PT;
+  stage(lds[0], kbeg);
+  int buf = 0;
+  for (long k0 = kbeg; k0 < kend; k0 += step, buf ^= 1) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (k0 + step < kend) stage(lds[buf ^ 1], k0 + step);
+    for (int t = 0; t < seg; t += 4) {
+      const char* base = lds[buf] + (((r16 << g.lseg) + ((t + kq) ^ (r16 & swz))) << 4);
+      double br[PT], bi[PT], bs[PT];
+#pragma unroll
+      for (int i = 0; i < NBW; ++i) {
+        if (i >= count) break;  // wave-uniform, as the next
+        const seg_t a = *(const seg_t*)(base + ((16 * bx[i]) << (g.lseg + 4)));
+        if (i == 0 || by[i] != by[i - 1]) {
+          const seg_t b = *(const seg_t*)(base + ((16 * by[i] + boff) << (g.lseg + 4)));
+#pragma unroll
+          for (int h = 0; h < PT; ++h) {
+            br[h] = (double)b[2 * h];
+            bi[h] = (double)b[2 * h + 1];
+            bs[h] = br[h] + bi[h];
+          }
+        }
+#pragma unroll
+        for (int h = 0; h < PT; ++h) {
+          const double ar = (double)a[2 * h], ai = (double)a[2 * h + 1];
+          p1[i] = mfma4(ar, br[h], p1[i]);
+          if constexpr (REAL) {
+            p1[i] = mfma4(ai, bi[h], p1[i]);
+          } else {
+            p2[i] = mfma4(ai, bi[h], p2[i]);
+            p3[i] = mfma4(ar - ai, bs[h], p3[i]);
+          }
+        }
+      }
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < NBW; ++i) {
+    if (i >= count) break;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int x = 16 * bx[i] + mfma_row<double>(lane, v), y = 16 * by[i] + r16;
+      if (x < na && y < nb)
+        partial[((size_t)blockIdx.y * nb + y) * na + x] =
+            REAL ? cx<double>{p1[i][v], 0.0}
+                 : cx<double>{p1[i][v] + p2[i][v], p3[REAL ? 0 : i][v] - p1[i][v] + p2[i][v]};
+    }
   }
 }
 
@@ -694,7 +834,8 @@ __device__ __forceinline__ void nn_slice_body(double2* cs, const cx<TIn>* __rest
                                               int b0, int nb, cx<TIn>* __restrict__ Y, long ldy,
                                               long K, int upper, int wg, int nwg) {
   constexpr int W = 16 * NBB, XB = NBB == 1 ? 4 : NBB == 2 ? 2 : 1;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r16 = lane & 15, kq = lane >> 4;
   const int rows = upper && b0 + W < na ? b0 + W : na;
   const int groups = (rows + 15) / 16;  // of 16 orbitals: four MFMA steps
@@ -919,6 +1060,73 @@ static bool herm_shape(int n, long K, int max_waves, int cu_waves, CnShape* s) {
   return true;
 }
 
+// Shape of an FP64 product for k_cn_f64.  False below 8 blocks, which leave
+// waves without work (k_cn_mfma's tiles of 32 then do: 48 rows), where a
+// chunk's rows exceed the LDS buffer, and where K is no multiple of a chunk.
+static bool gram_shape(int na, int nb, long K, size_t data_bytes, bool same, bool herm,
+                       GramShape* s) {
+  const int ta = (na + 15) / 16, tb = (nb + 15) / 16;
+  const int total = herm ? tb * (tb + 1) / 2 : ta * tb;
+  if (total < 8) return false;
+  s->herm = herm;
+  s->same = same;
+  s->gx = (total + 8 * kGramBlocks - 1) / (8 * kGramBlocks);
+  s->per = (total + s->gx - 1) / s->gx;
+  // rows of the workgroup with the most of them
+  int rows = 0;
+  for (int x = 0; x < s->gx; ++x) {
+    const int q0 = x * s->per, q1 = std::min(q0 + s->per, total);
+    if (q0 >= q1) break;
+    int y0 = 0, y1 = 0;
+    if (herm) {
+      while ((y0 + 1) * (y0 + 2) / 2 <= q0) ++y0;
+      while ((y1 + 1) * (y1 + 2) / 2 <= q1 - 1) ++y1;
+    } else {
+      y0 = q0 / ta;
+      y1 = (q1 - 1) / ta;
+    }
+    rows = std::max(rows, 16 * ((herm ? y1 + 1 : ta) + (same ? 0 : y1 - y0 + 1)));
+  }
+  s->lseg = 5;
+  const long pt = 16 / (long)data_bytes;
+  while (s->lseg >= 3 &&
+         ((rows << (s->lseg + 4)) > kGramBuffer || K % (pt << s->lseg) != 0))
+    --s->lseg;
+  if (s->lseg < 3) return false;
+  const long step = pt << s->lseg;
+  long ks = std::max(1, 256 / s->gx);
+  s->kchunk = ((K + ks - 1) / ks + step - 1) / step * step;
+  s->ks = (K + s->kchunk - 1) / s->kchunk;
+  return true;
+}
+
+// K splits of an FP64 product, whichever kernel takes it.
+static long gram_splits(int na, int nb, long K, size_t data_bytes, bool herm) {
+  long ks = 0;
+  for (int same = 0; same < 2; ++same) {
+    GramShape g;
+    if (gram_shape(na, nb, K, data_bytes, same != 0, herm, &g) && g.ks > ks) ks = g.ks;
+  }
+  return ks;
+}
+
+template <typename T, bool REAL>
+static ace_status launch_gram(ace_ctx c, const char* name, const GramShape& g, const cx<T>* A,
+                              long lda, int na, const cx<T>* B, long ldb, int nb, long K,
+                              cx<double>* partial) {
+  const dim3 grid((unsigned)g.gx, (unsigned)g.ks), block(512);
+  switch ((g.per + 7) / 8) {
+#define ACE_GRAM(N)                                                                              \
+  case N:                                                                                        \
+    return launch(c, name, k_cn_f64<T, N, REAL>, grid, block, 0, A, lda, na, B, ldb, nb, K,      \
+                  partial, g);
+    ACE_GRAM(1) ACE_GRAM(2) ACE_GRAM(3) ACE_GRAM(4)
+    ACE_GRAM(5) ACE_GRAM(6) ACE_GRAM(7) ACE_GRAM(8)
+#undef ACE_GRAM
+  }
+  return fail(c, ACE_E_ARG, "internal: blocks per wave");
+}
+
 size_t gemm_cn_scratch_bytes(int na, int nb, long K) {
   CnShape s32 = cn_shape(na, nb, K, 16, 16), s16 = cn_shape(na, nb, K, kBf16Waves, kBf16Waves);
   CnShape s64 = cn_shape(na, nb, K, 8, 12);
@@ -929,6 +1137,9 @@ size_t gemm_cn_scratch_bytes(int na, int nb, long K) {
     if (herm_shape(na, K, kBf16Waves, kBf16Waves, &h) && h.ks > k32) k32 = h.ks;
     if (herm_shape(na, K, 8, 12, &h) && h.ks > k64) k64 = h.ks;
   }
+  for (size_t eb : {sizeof(cx<float>), sizeof(cx<double>)})
+    for (int herm = 0; herm < (na == nb ? 2 : 1); ++herm)
+      k64 = std::max(k64, gram_splits(na, nb, K, eb, herm != 0));
   const size_t b32 = (size_t)k32 * na * nb * sizeof(cx<float>);
   const size_t b64 = (size_t)k64 * na * nb * sizeof(cx<double>);
   return align_up(b32 > b64 ? b32 : b64, 256);
@@ -941,6 +1152,7 @@ size_t gemm_cn_partial_bytes(int na, int nb, long K, size_t data_bytes, CnMode m
   const int cu_waves = f64 ? 12 : bf16_split ? kBf16Waves : 16;
   CnShape s = cn_shape(na, nb, K, max_waves, cu_waves);
   if (herm && na == nb) herm_shape(na, K, max_waves, cu_waves, &s);
+  if (f64) s.ks = std::max(s.ks, gram_splits(na, nb, K, data_bytes, herm && na == nb));
   const size_t part_eb = f64 ? sizeof(cx<double>) : sizeof(cx<float>);
   return align_up((size_t)s.ks * na * nb * part_eb, 256);
 }
@@ -950,16 +1162,35 @@ ace_status gemm_cn(ace_ctx c, const cx<T>* A, long lda, int na, const cx<T>* B, 
                    long K, double alpha, cx<double>* C, int ldc, CnMode mode,
                    bool real_part, bool herm) {
   const bool bf16_split = std::is_same<T, float>::value && mode == kBf16Split;
-  const bool f64 = sizeof(T) == 8 || mode == kFp64;
+  const bool f64 = sizeof(T) == 8 || mode == kFp64 || mode == kFp64Four;
   // the BF16-split kernel addresses a tile's 32 rows through a buffer
   // resource with 32-bit byte offsets
   if (bf16_split && (lda > (1L << 31) / 256 || ldb > (1L << 31) / 256))
     return fail(c, ACE_E_UNSUPPORTED, "leading dimension too large for the BF16-split product");
+  // Loads of 16 bytes: rows must start at multiples of that.
+  GramShape gs;
+  const bool aligned = ((uintptr_t)A | (uintptr_t)B | (uintptr_t)(lda * sizeof(cx<T>)) |
+                        (uintptr_t)(ldb * sizeof(cx<T>))) % 16 == 0;
+  if (f64 && aligned && mode != kFp64Four &&
+      gram_shape(na, nb, K, sizeof(cx<T>), A == B && lda == ldb && na == nb, herm && na == nb,
+                 &gs)) {
+    ace_status st;
+    cx<double>* part =
+        (cx<double>*)ws_take(c, (size_t)gs.ks * na * nb * sizeof(cx<double>), &st);
+    if (!part) return st;
+    const char* name = sizeof(T) == 8 ? "cn_mfma_f64" : "cn_mfma_f32in_f64";
+    st = real_part ? launch_gram<T, true>(c, name, gs, A, lda, na, B, ldb, nb, K, part)
+                   : launch_gram<T, false>(c, name, gs, A, lda, na, B, ldb, nb, K, part);
+    if (st != ACE_OK) return st;
+    return launch(c, "reduce_partials", k_reduce_partials2<double>, dim3((na * nb + 63) / 64),
+                  dim3(1024), 0, (const cx<double>*)part, (int)gs.ks, na, nb, alpha, C, ldc,
+                  real_part ? 1 : 0, gs.herm ? 16 : 0);
+  }
   const int max_waves = f64 ? 8 : bf16_split ? kBf16Waves : 16;
   const int cu_waves = f64 ? 12 : bf16_split ? kBf16Waves : 16;
   CnShape s = cn_shape(na, nb, K, max_waves, cu_waves);
   herm = herm && na == nb && herm_shape(na, K, max_waves, cu_waves, &s);
-  const int hm = herm ? 1 : 0;
+  const int hm = herm ? 32 : 0;
   ace_status st;
   const size_t part_eb = f64 ? sizeof(cx<double>) : sizeof(cx<float>);
   void* partial = ws_take(c, (size_t)s.ks * na * nb * part_eb, &st);

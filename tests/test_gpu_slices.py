@@ -1,7 +1,10 @@
-"""The FP64 expansion product (Y = A C with C's columns in LDS slices) at its
-edges: one column, every slice width, a cut last block, slices of different
+"""The FP64 products of the compression.  The expansion (Y = A C with C's columns
+in LDS slices) at its edges: one column, every slice width, a cut last block, slices of different
 widths, orbital counts that are no multiple of 16, the largest count whose
-slices fit and the first one past it, and grids whose last tile is cut."""
+slices fit and the first one past it, and grids whose last tile is cut.  The
+reduction (16 x 16 blocks dealt out to waves): the first size that takes it, one
+to several workgroup rows, cut blocks, real orbitals, rows that start at no
+multiple of 16 bytes."""
 import numpy as np
 import pytest
 
@@ -46,3 +49,31 @@ def test_triangular_products(n, nb):
     R = g.dV * (Q.conj() @ X.T)
     assert np.max(np.abs(np.tril(R, -1))) <= 1e-12 * np.max(np.abs(R))
     assert np.max(np.abs(R.T @ Q - X)) <= 1e-12 * np.max(np.abs(X))
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp64", "real32", "real64"])
+@pytest.mark.parametrize("n,nb,pad", [(12, 48, 0), (12, 49, 0), (16, 81, 1), (16, 136, 0),
+                                      (16, 193, 0), (16, 257, 2)])
+def test_gram_products(prec, n, nb, pad):
+    import torch
+    from paper_1601_07159_amd import ace
+    print(f"gram products prec={prec} n={n} nb={nb} pad={pad}", flush=True)
+    L = 0.43 * n
+    g = ogrid(n, L)
+    rng = np.random.default_rng(nb)
+    X = rng.standard_normal((nb, n ** 3)) + 1j * rng.standard_normal((nb, n ** 3))
+    x = to_gpu(X, prec)
+    pad *= 2 if prec.startswith("real") else 1     # real rows hold pairs
+    rows = torch.zeros(nb, n ** 3 + pad, dtype=x.dtype, device="cuda")
+    rows[:, :n ** 3] = x
+    # pad 1: rows of FP32 data start between multiples of 16 bytes
+    x = rows[:, :n ** 3]
+    Q = to_np(ace.orthonormalize(x, ggrid(n, L), prec)).reshape(nb, -1)
+    # FP64 sums; Q is stored in the data type: eps sqrt(N_g) / sqrt(N_g) per
+    # entry of the Gram matrix of unit vectors, ten times that
+    eps = 6e-8 if prec.endswith("32") else 1.1e-16
+    tol = 10 * eps if prec.endswith("32") else 1e-12
+    S = g.dV * (Q.conj() @ Q.T)
+    if prec.startswith("real"):
+        S = S.real
+    assert np.max(np.abs(S - np.eye(nb))) <= tol
