@@ -10,27 +10,6 @@ namespace ace {
 
 namespace {
 
-// ---------------------------------------------------------------------------
-// Factorisation of a Hermitian matrix, one workgroup:
-//   A = s (M + M^H)/2  (lower triangle),  A = L L^H  (Cholesky),
-//   optional copy of L,  and with do_inverse C = L^{-H} (upper triangular).
-// This form serves n above kCholRegMax (the register form below covers the
-// smaller ones), with A in global scratch.  Blocked in panels of kCholNB
-// columns so that only a few workgroup barriers are needed per panel:
-//   Cholesky  the diagonal block is factored by wave 0 alone (lanes of one
-//             wave stay ordered without barriers), the rows below solve
-//             x L_kk^H = a one thread per row, the trailing lower triangle is
-//             updated with kCholNB-term dot products.
-//   inverse   (n > kCholPanelRows; below, k_tri_inv_wave follows instead)
-//             X = L^{-1}: diagonal blocks inverted in place, one wave each;
-//             then block row i: X_ij = -X_ii sum_{k=j}^{i-1} L_ik X_kj, with the
-//             finished blocks of X kept (conjugate-transposed) in C.
-// lda >= n; T is scratch of kCholNB x n.
-constexpr int kCholNB = 16;
-// Up to this n the current panel (n x kCholNB) is staged in LDS.
-constexpr int kCholPanelRows = 512;
-__shared__ cx<double> chol_panel[kCholNB][kCholPanelRows];
-
 __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
   __builtin_amdgcn_wave_barrier();
@@ -43,7 +22,6 @@ __device__ __forceinline__ cx<double> cmul_d(cx<double> a, cx<double> b) {
 __device__ __forceinline__ cx<double> cmulcj_d(cx<double> a, cx<double> b) {
   return {a.x * b.x + a.y * b.y, a.y * b.x - a.x * b.y};
 }
-
 
 // 1/sqrt(d) from the hardware estimate, refined by three Newton-Raphson steps
 // y <- y (3/2 - d y^2 / 2).
@@ -58,229 +36,154 @@ __device__ __forceinline__ double rsq_refined(double d) {
   return y;
 }
 
-__device__ __forceinline__ void chol_inv_body(const cx<double>* __restrict__ M, int n, double s,
-                                              cx<double>* A, int lda, cx<double>* T,
-                                              cx<double>* __restrict__ Lout,
-                                              cx<double>* __restrict__ C, int* __restrict__ info,
-                                              const int* __restrict__ prior, int real_only,
-                                              int do_inverse) {
-  constexpr int NB = kCholNB;
-  __shared__ int failed;
-  __shared__ double pinv[kCholNB];  // 1 / L_kk of the current diagonal block
-  const int t = threadIdx.x, nt = blockDim.x;
-  const int lane = t & 63, wave = t >> 6, nw = nt >> 6;
-  if (prior && *prior != 0) {
-    if (t == 0) *info = *prior;
+__device__ __forceinline__ double bcast_lane(double v, int src) {
+  const long long b = __builtin_bit_cast(long long, v);
+  const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffffLL), src);
+  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), src);
+  return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned int)lo);
+}
+
+// ---------------------------------------------------------------------------
+// Factorisation of a Hermitian matrix of more than kCholRegMax rows (the
+// register form below covers the smaller ones):
+//   A = s (M + M^H)/2  (lower triangle),  A = L L^H,  optional copy of L,
+// then C = L^{-H} (k_tri_inv_wave, k_inv_global).
+//
+// Left-looking, one launch per panel of 16 columns and no other
+// synchronisation: a workgroup takes the panel's diagonal block (all of them
+// the same) and up to 48 rows below it.  The finished columns are subtracted
+// on the matrix cores (4 blocks of 16 x 16, two waves each, half of K
+// apiece); wave 0 then eliminates the 64 x 16 panel, one row per lane, the
+// pivot row's values broadcast by lane reads.  A launch takes 10 to 16 us,
+// nearly all of it latency (loads, 16 dependent pivots); one workgroup for the
+// whole matrix, its trailing triangle in global memory, took 212 us at n = 136
+// and 554 us at n = 256, the panels 116 and 262 us.
+constexpr int kPanel = 16;
+constexpr int kPanelRows = 48;
+
+typedef double v4d __attribute__((ext_vector_type(4)));
+
+__global__ __launch_bounds__(512) void k_chol_panel(const cx<double>* __restrict__ M, int n,
+                                                    double s, cx<double>* L,
+                                                    cx<double>* __restrict__ Lout, int* info,
+                                                    const int* __restrict__ prior, int real_only,
+                                                    int kb) {
+  __shared__ cx<double> sub[2][kPanel + kPanelRows][kPanel + 1];  // the halves' sums
+  __shared__ cx<double> mat[kPanel + kPanelRows][kPanel + 1];
+  const int t = threadIdx.x, lane = t & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  if (kb == 0) {
+    if (prior && *prior != 0) {
+      if (blockIdx.x == 0 && t == 0) *info = *prior;
+      return;
+    }
+  } else if (*info != 0) {
     return;
   }
-  if (t == 0) failed = 0;
-  for (int j = wave; j < n; j += nw)
-    for (int i = j + lane; i < n; i += 64) {
-      const cx<double> a = M[i + (size_t)j * n], b = M[j + (size_t)i * n];
-      A[i + (size_t)j * lda] =
-          (i == j)    ? cx<double>{s * a.x, 0.0}
-          : real_only ? cx<double>{0.5 * s * (a.x + b.x), 0.0}
-                      : cx<double>{0.5 * s * (a.x + b.x), 0.5 * s * (a.y - b.y)};
+  const int nb = n - kb < kPanel ? n - kb : kPanel;
+  const int row0 = kb + kPanel + kPanelRows * (int)blockIdx.x;
+  // row of the matrix that panel row r holds (past the end: n or more)
+  auto row_of = [&](int r) {
+    return r < kPanel ? (r < nb ? kb + r : n) : row0 + r - kPanel;
+  };
+  // the panel of A: two entries per thread
+  cx<double> m1[2], m2[2];
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const int r = (t + 512 * q) & 63, c = (t + 512 * q) >> 6;
+    const int i = row_of(r), ic = i < n ? i : n - 1, jc = kb + c < n ? kb + c : n - 1;
+    m1[q] = M[ic + (size_t)jc * n];
+    m2[q] = M[jc + (size_t)ic * n];
+  }
+  {
+    const int blk = wave & 3, half = wave >> 2, r16 = lane & 15, kq = lane >> 4;
+    const int i = row_of(16 * blk + r16), ic = i < n ? i : n - 1;
+    const int j = row_of(r16), jc = j < n ? j : n - 1;
+    v4d re = {0, 0, 0, 0}, im = {0, 0, 0, 0};
+    const int kend = (half + 1) * (kb / 2);
+    for (int k0 = half * (kb / 2); k0 < kend; k0 += 32) {
+      cx<double> a[8], b[8];  // eight steps' loads in flight
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int k = (k0 + 4 * u < kend ? k0 + 4 * u : k0) + kq;
+        a[u] = L[ic + (size_t)k * n];
+        b[u] = L[jc + (size_t)k * n];
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        if (k0 + 4 * u >= kend) break;
+        re = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u].x, b[u].x, re, 0, 0, 0);
+        im = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u].y, b[u].x, im, 0, 0, 0);
+        re = __builtin_amdgcn_mfma_f64_16x16x4f64(a[u].y, b[u].y, re, 0, 0, 0);
+        im = __builtin_amdgcn_mfma_f64_16x16x4f64(-a[u].x, b[u].y, im, 0, 0, 0);
+      }
     }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) sub[half][16 * blk + kq + 4 * v][r16] = {re[v], im[v]};
+  }
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const int r = (t + 512 * q) & 63, c = (t + 512 * q) >> 6;
+    mat[r][c] = r == c      ? cx<double>{s * m1[q].x, 0.0}
+                : real_only ? cx<double>{0.5 * s * (m1[q].x + m2[q].x), 0.0}
+                            : cx<double>{0.5 * s * (m1[q].x + m2[q].x), 0.5 * s * (m1[q].y - m2[q].y)};
+  }
   __syncthreads();
-
-  // ---- Cholesky, right-looking by panels
-  for (int kb = 0; kb < n; kb += NB) {
-    const int nb = n - kb < NB ? n - kb : NB;
-    if (n <= kCholPanelRows) {
-      // the panel (rows kb.., columns kb..kb+nb-1) in LDS: P[c][r] = A[kb + r][kb + c]
-      cx<double> (*P)[kCholPanelRows] = chol_panel;
-      const int R = n - kb;
-      for (int e = t; e < nb * R; e += nt) {
-        const int c = e / R, r = e - c * R;
-        P[c][r] = A[(kb + r) + (size_t)(kb + c) * lda];
-      }
-      __syncthreads();
-      if (wave == 0) {
-        for (int k = 0; k < nb; ++k) {
-          const double d = P[k][k].x;
-          if (!(d > 0.0) || !isfinite(d)) {
-            if (lane == 0) failed = kb + k + 1;
-            break;  // uniform across the wave
-          }
-          // 1/sqrt(d) and sqrt(d) from the refined reciprocal square root
-          // (no divide on the serial path)
-          const double inv = rsq_refined(d), r = d * inv;
-          wave_sync();
-          if (lane == 0) {
-            P[k][k] = {r, 0.0};
-            pinv[k] = inv;
-          }
-          const int i = k + 1 + lane;
-          if (i < nb) {
-            const cx<double> v = P[k][i];
-            P[k][i] = {v.x * inv, v.y * inv};
-          }
-          wave_sync();
-          // rank-1 update of the block's trailing triangle: lane -> (row
-          // offset lane % 16, column offset lane / 16 + 4 t), no divisions
+  if (wave != 0) return;
+  const int row = row_of(lane);
+  const bool live = row < n;
+  cx<double> a[kPanel];
 #pragma unroll
-          for (int tq = 0; tq < 4; ++tq) {
-            const int ii = k + 1 + (lane & 15), jj = k + 1 + (lane >> 4) + 4 * tq;
-            if (ii < nb && jj < nb && ii >= jj) {
-              const cx<double> u = cmulcj_d(P[k][ii], P[k][jj]);
-              const cx<double> v = P[jj][ii];
-              P[jj][ii] = {v.x - u.x, v.y - u.y};
-            }
-          }
-          wave_sync();
-        }
-      }
-      __syncthreads();
-      if (failed) break;
-      // rows below the diagonal block: x L_kk^H = a, one thread per row,
-      // solved in place in the LDS panel (a register array indexed by the
-      // loop counters went to scratch memory)
-      for (int r = nb + t; r < R; r += nt) {
-        for (int c = 0; c < nb; ++c) {
-          cx<double> v = P[c][r];
-          for (int d = 0; d < c; ++d) {
-            const cx<double> u = cmulcj_d(P[d][r], P[d][c]);
-            v.x -= u.x;
-            v.y -= u.y;
-          }
-          const double inv = pinv[c];
-          P[c][r] = {v.x * inv, v.y * inv};
-        }
-      }
-      __syncthreads();
-      // the finished panel back to A; the trailing lower triangle from the
-      // LDS panel (disjoint columns of A)
-      for (int e = t; e < nb * R; e += nt) {
-        const int c = e / R, r = e - c * R;
-        if (r >= c) A[(kb + r) + (size_t)(kb + c) * lda] = P[c][r];
-      }
-      // four columns jb..jb+3 per wave and lane row i: P[c][i] is read once for
-      // the four (the P[c][j] are wave-uniform broadcasts).  Loads are
-      // unconditional from clamped columns; entries above the diagonal or past
-      // n are computed on scratch values and not stored.
-      // Two row blocks (i and i + 64) per step with all eight loads issued
-      // first, so that a thread waits for memory once per step.
-      for (int jb = kb + nb + 4 * wave; jb < n; jb += 4 * nw) {
-        int jq[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) jq[q] = jb + q < n ? jb + q : n - 1;
-        for (int i0 = jb + lane; i0 < n; i0 += 128) {
-          int im[2];
-          cx<double> acc[2][4];
-#pragma unroll
-          for (int m = 0; m < 2; ++m) {
-            im[m] = i0 + 64 * m < n ? i0 + 64 * m : n - 1;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) acc[m][q] = A[im[m] + (size_t)jq[q] * lda];
-          }
-#pragma unroll
-          for (int c = 0; c < NB; ++c) {
-            if (c >= nb) break;
-            cx<double> pj[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) pj[q] = P[c][jq[q] - kb];
-#pragma unroll
-            for (int m = 0; m < 2; ++m) {
-              const cx<double> pi = P[c][im[m] - kb];
-#pragma unroll
-              for (int q = 0; q < 4; ++q) {
-                const cx<double> u = cmulcj_d(pi, pj[q]);
-                acc[m][q].x -= u.x;
-                acc[m][q].y -= u.y;
-              }
-            }
-          }
-#pragma unroll
-          for (int m = 0; m < 2; ++m) {
-            const int i = i0 + 64 * m;
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-              if (i < n && jb + q < n && i >= jb + q) A[i + (size_t)(jb + q) * lda] = acc[m][q];
-          }
-        }
-      }
-      __syncthreads();
-      continue;
-    }
-    // n > kCholPanelRows: the panel stays in global memory
-    if (wave == 0) {
-      for (int k = kb; k < kb + nb; ++k) {
-        const double d = A[k + (size_t)k * lda].x;
-        if (!(d > 0.0) || !isfinite(d)) {
-          if (lane == 0) failed = k + 1;
-          break;  // uniform across the wave
-        }
-        const double r = sqrt(d), inv = 1.0 / r;
-        wave_sync();
-        if (lane == 0) A[k + (size_t)k * lda] = {r, 0.0};
-        const int i = k + 1 + lane;
-        if (i < kb + nb) {
-          const cx<double> v = A[i + (size_t)k * lda];
-          A[i + (size_t)k * lda] = {v.x * inv, v.y * inv};
-        }
-        wave_sync();
-        const int m = kb + nb - k - 1;
-        for (int e = lane; e < m * m; e += 64) {
-          const int ii = k + 1 + e % m, jj = k + 1 + e / m;
-          if (ii < jj) continue;
-          const cx<double> u = cmulcj_d(A[ii + (size_t)k * lda], A[jj + (size_t)k * lda]);
-          cx<double> v = A[ii + (size_t)jj * lda];
-          A[ii + (size_t)jj * lda] = {v.x - u.x, v.y - u.y};
-        }
-        wave_sync();
-      }
-    }
-    __syncthreads();
-    if (failed) break;
-    // rows below the diagonal block: x L_kk^H = a, one thread per row
-    for (int i = kb + nb + t; i < n; i += nt) {
-      cx<double> x[NB];
-#pragma unroll
-      for (int c = 0; c < NB; ++c) x[c] = c < nb ? A[i + (size_t)(kb + c) * lda] : cx<double>{0, 0};
-#pragma unroll
-      for (int c = 0; c < NB; ++c) {
-        if (c >= nb) break;
-        cx<double> v = x[c];
-#pragma unroll
-        for (int d = 0; d < c; ++d) {
-          const cx<double> u = cmulcj_d(x[d], A[(kb + c) + (size_t)(kb + d) * lda]);
-          v.x -= u.x;
-          v.y -= u.y;
-        }
-        const double inv = 1.0 / A[(kb + c) + (size_t)(kb + c) * lda].x;
-        x[c] = {v.x * inv, v.y * inv};
-      }
-#pragma unroll
-      for (int c = 0; c < NB; ++c)
-        if (c < nb) A[i + (size_t)(kb + c) * lda] = x[c];
-    }
-    __syncthreads();
-    // trailing lower triangle
-    for (int j = kb + nb + wave; j < n; j += nw)
-      for (int i = j + lane; i < n; i += 64) {
-        cx<double> acc = A[i + (size_t)j * lda];
-        for (int c = 0; c < nb; ++c) {
-          const cx<double> u =
-              cmulcj_d(A[i + (size_t)(kb + c) * lda], A[j + (size_t)(kb + c) * lda]);
-          acc.x -= u.x;
-          acc.y -= u.y;
-        }
-        A[i + (size_t)j * lda] = acc;
-      }
-    __syncthreads();
+  for (int c = 0; c < kPanel; ++c) {
+    const cx<double> v = mat[lane][c], u0 = sub[0][lane][c], u1 = sub[1][lane][c];
+    a[c] = live && c < nb ? cx<double>{v.x - (u0.x + u1.x), v.y - (u0.y + u1.y)}
+                          : cx<double>{0.0, 0.0};
   }
-  const int fail_k = failed;
-  if (t == 0) *info = fail_k;
-  if (fail_k != 0) return;
-  if (Lout) {
-    for (int j = wave; j < n; j += nw)
-      for (int i = lane; i < n; i += 64)
-        Lout[i + (size_t)j * n] = (i >= j) ? A[i + (size_t)j * lda] : cx<double>{0.0, 0.0};
+  int fail_k = 0;
+#pragma unroll
+  for (int k = 0; k < kPanel; ++k) {
+    if (k < nb && fail_k == 0) {  // uniform
+      const double d = bcast_lane(a[k].x, k);
+      if (!(d > 0.0) || !isfinite(d)) {
+        fail_k = kb + k + 1;
+      } else {
+        const double inv = rsq_refined(d);
+        a[k] = lane == k ? cx<double>{d * inv, 0.0} : cx<double>{a[k].x * inv, a[k].y * inv};
+#pragma unroll
+        for (int c = k + 1; c < kPanel; ++c) {
+          const double lx = bcast_lane(a[k].x, c), ly = bcast_lane(a[k].y, c);
+          a[c].x = fma(-a[k].y, ly, fma(-a[k].x, lx, a[c].x));
+          a[c].y = fma(a[k].x, ly, fma(-a[k].y, lx, a[c].y));
+        }
+      }
+    }
   }
-  if (!do_inverse) return;  // L stays in the lower triangle of A
-  __syncthreads();  // Lout read A before the diagonal blocks are overwritten
+  if (blockIdx.x == 0 && lane == 0 && (kb == 0 || fail_k != 0)) *info = fail_k;
+  if (fail_k != 0 || !live || (lane < kPanel && blockIdx.x != 0)) return;
+#pragma unroll
+  for (int c = 0; c < kPanel; ++c) {
+    const int j = kb + c;
+    if (c >= nb || j > row) continue;
+    L[row + (size_t)j * n] = a[c];
+    if (Lout) {
+      Lout[row + (size_t)j * n] = a[c];
+      if (j < row) Lout[j + (size_t)row * n] = {0.0, 0.0};
+    }
+  }
+}
 
+// C = L^{-H} of more than 512 rows (the wave form's rows per lane grow with
+// n), one workgroup.  X = L^{-1}: diagonal blocks inverted in place, one wave
+// each; then block row i: X_ij = -X_ii sum_{k=j}^{i-1} L_ik X_kj, with the
+// finished blocks of X kept (conjugate-transposed) in C.  lda >= n; T is
+// scratch of kCholNB x n.
+constexpr int kCholNB = 16;
+
+__device__ __forceinline__ void inv_body(int n, cx<double>* A, int lda, cx<double>* T,
+                                         cx<double>* __restrict__ C) {
+  constexpr int NB = kCholNB;
+  const int t = threadIdx.x, nt = blockDim.x;
+  const int lane = t & 63, wave = t >> 6, nw = nt >> 6;
   // ---- inverse: diagonal blocks in place (one wave each)
   const int nbk = (n + NB - 1) / NB;
   for (int b = wave; b < nbk; b += nw) {
@@ -323,7 +226,6 @@ __device__ __forceinline__ void chol_inv_body(const cx<double>* __restrict__ M, 
     }
   for (int ib = 1; ib < nbk; ++ib) {
     const int ri = ib * NB, ni = n - ri < NB ? n - ri : NB;
-    // (the inverse runs here only above kCholPanelRows: from global memory)
     // T[r][col] = sum_{k = col}^{ri-1} L[ri + r][k] X[k][col]
     for (int col = wave; col < ri; col += nw)
       for (int r = lane; r < ni; r += 64) {
@@ -544,13 +446,6 @@ __global__ __launch_bounds__(1024) void k_chol_reg(const cx<double>* __restrict_
     }
 }
 
-__device__ __forceinline__ double bcast_lane(double v, int src) {
-  const long long b = __builtin_bit_cast(long long, v);
-  const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffffLL), src);
-  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), src);
-  return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned int)lo);
-}
-
 // C = L^{-H} for n <= kCholRegMax: one wave per column j of X = L^{-1}, the
 // lower triangle of L staged in LDS.  Column-oriented forward substitution:
 // lane i holds rows i and i + 64 of y = e_j - sum_{m<k} L_:m x_m; at step k
@@ -612,14 +507,11 @@ __global__ __launch_bounds__(256) void k_tri_inv(const cx<double>* __restrict__ 
   }
 }
 
-__global__ __launch_bounds__(1024) void k_chol_inv_global(const cx<double>* __restrict__ M, int n,
-                                                          double s, cx<double>* __restrict__ A,
-                                                          cx<double>* __restrict__ Lout,
-                                                          cx<double>* __restrict__ C,
-                                                          int* __restrict__ info,
-                                                          const int* __restrict__ prior,
-                                                          int real_only, int do_inverse) {
-  chol_inv_body(M, n, s, A, n, A + (size_t)n * n, Lout, C, info, prior, real_only, do_inverse);
+__global__ __launch_bounds__(1024) void k_inv_global(int n, cx<double>* __restrict__ A,
+                                                     cx<double>* __restrict__ C,
+                                                     const int* __restrict__ info) {
+  if (*info != 0) return;
+  inv_body(n, A, n, A + (size_t)n * n, C);
 }
 
 // C = L^{-H} for kCholRegMax < n <= 64 R, L (lower triangle, column-major,
@@ -627,11 +519,11 @@ __global__ __launch_bounds__(1024) void k_chol_inv_global(const cx<double>* __re
 // X = L^{-1}, many workgroups in parallel (the single-workgroup block inverse
 // took most of the factorisation's time at n = 256).  Forward substitution
 // y = e_j, x_k = y_k / L_kk, y_i -= L_ik x_k (i > k); lane l holds rows
-// l + 64 r.  Column k of L is loaded kTriPrefetch steps ahead (coalesced:
-// consecutive rows on consecutive lanes); rows at or above k read zero.  Row
+// l + 64 r.  Column k of L is loaded PD steps ahead (coalesced:
+// consecutive rows on consecutive lanes); rows at or above k read zero.  Bound by
+// that chain: n = 136 39 us with R = 4 and 4 steps ahead, 33 us with 3 and 8.  Row
 // j of C is conj(x), its entries left of the diagonal zero.
-constexpr int kTriPrefetch = 4;
-template <int R>
+template <int R, int PD>
 __global__ __launch_bounds__(64) void k_tri_inv_wave(const cx<double>* __restrict__ L, int n,
                                                      cx<double>* __restrict__ C,
                                                      const int* __restrict__ info) {
@@ -646,7 +538,6 @@ __global__ __launch_bounds__(64) void k_tri_inv_wave(const cx<double>* __restric
     inv[r] = (i >= j && i < n) ? 1.0 / L[i + (size_t)i * n].x : 0.0;
   }
   for (int k = lane; k < j; k += 64) C[j + (size_t)k * n] = {0.0, 0.0};
-  constexpr int PD = kTriPrefetch;
   cx<double> lc[PD][R];
   // column k of L below the diagonal (zero elsewhere); unconditional loads
   // from a clamped address, masked when used
@@ -719,21 +610,23 @@ ace_status chol_inv(ace_ctx c, const cx<double>* M, int n, double s, cx<double>*
     return launch(c, "tri_inv", k_tri_inv, dim3(n), dim3(256), 0, (const cx<double>*)scratch, n,
                   C, (const int*)info_dev);
   }
-  // up to 512: Cholesky in one workgroup, then C = L^{-H} one wave per column;
-  // above: the fused single-workgroup form (the wave form's rows per lane grow
-  // with n)
-  const int wave_inverse = n <= 512 ? 1 : 0;
-  ace_status st = launch(c, "chol_inv_global", k_chol_inv_global, dim3(1), dim3(1024), 0, M, n, s,
-                         scratch, Lout, C, info_dev, prior, real_only ? 1 : 0, 1 - wave_inverse);
-  if (st != ACE_OK || !wave_inverse) return st;
+  for (int kb = 0; kb < n; kb += kPanel) {
+    const int below = n - kb - kPanel;
+    const int wgs = below > 0 ? (below + kPanelRows - 1) / kPanelRows : 1;
+    const ace_status st =
+        launch(c, "chol_panel", k_chol_panel, dim3(wgs), dim3(512), 0, M, n, s, scratch, Lout,
+               info_dev, prior, real_only ? 1 : 0, kb);
+    if (st != ACE_OK) return st;
+  }
+  if (n > 512)
+    return launch(c, "inv_global", k_inv_global, dim3(1), dim3(1024), 0, n, scratch, C,
+                  (const int*)info_dev);
   const cx<double>* Lw = scratch;
-  if (n <= 128)
-    return launch(c, "tri_inv_wave", k_tri_inv_wave<2>, dim3(n), dim3(64), 0, Lw, n, C,
-                  (const int*)info_dev);
-  if (n <= 256)
-    return launch(c, "tri_inv_wave", k_tri_inv_wave<4>, dim3(n), dim3(64), 0, Lw, n, C,
-                  (const int*)info_dev);
-  return launch(c, "tri_inv_wave", k_tri_inv_wave<8>, dim3(n), dim3(64), 0, Lw, n, C,
+  const auto wave_form = n <= 128   ? k_tri_inv_wave<2, 12>
+                         : n <= 192 ? k_tri_inv_wave<3, 8>
+                         : n <= 256 ? k_tri_inv_wave<4, 8>
+                                    : k_tri_inv_wave<8, 4>;
+  return launch(c, "tri_inv_wave", wave_form, dim3(n), dim3(64), 0, Lw, n, C,
                 (const int*)info_dev);
 }
 

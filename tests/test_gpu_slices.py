@@ -77,3 +77,29 @@ def test_gram_products(prec, n, nb, pad):
     if prec.startswith("real"):
         S = S.real
     assert np.max(np.abs(S - np.eye(nb))) <= tol
+
+
+@pytest.mark.parametrize("nb", [89, 112, 136, 161])
+@pytest.mark.parametrize("bad", [None, 0, 15, 16, 65, 88])
+def test_panel_factorisation(nb, bad):
+    """Cholesky by panels: whole and cut last panels, one to several workgroups;
+    the first pivot that is not positive is reported (a zero vector's)."""
+    import torch
+    from paper_1601_07159_amd import ace
+    n = 12
+    print(f"panel factorisation nb={nb} bad={bad}", flush=True)
+    L = 0.43 * n
+    g = ogrid(n, L)
+    rng = np.random.default_rng(nb)
+    X = rng.standard_normal((nb, n ** 3)) + 1j * rng.standard_normal((nb, n ** 3))
+    if bad is not None:
+        X[bad] = 0.0
+    info = torch.full((1,), -7, dtype=torch.int32, device="cuda")
+    Q = ace.orthonormalize(to_gpu(X.reshape(nb, n, n, n), "fp64"), ggrid(n, L), "fp64", info=info)
+    torch.cuda.synchronize()
+    assert int(info.item()) == (0 if bad is None else bad + 1)
+    if bad is None:
+        Q = to_np(Q).reshape(nb, -1)
+        # 1728 products per entry of unit vectors: sqrt(1728) eps = 5e-15, with
+        # a margin of a hundred for the factor's condition
+        assert np.max(np.abs(g.dV * (Q.conj() @ Q.T) - np.eye(nb))) <= 5e-13
