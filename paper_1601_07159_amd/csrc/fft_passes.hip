@@ -852,11 +852,23 @@ int line_shape(ace_ctx c, int n, int eb) {
 // pass at N = 72 (quads: 1,512 -> 1,267 us at 24 orbitals).  Below, one thread
 // per line runs at the copy rate already.  (kSplitSlabN, kSplitPlaneN)
 
+// FP64 passes over at most so many planes (slabs) run on quads, whose waves are
+// four times as many: below some ten planes per CU a pass lasts as long as one
+// plane takes.  Builds of 8 to 24 orbitals against the forms for more planes:
+// 24^3 31.1 -> 28.6 us (36 pairs), 43.3 -> 42.0 (105), but 46.8 -> 53.7 (136);
+// 32^3 98.4 -> 83.1 (136), 159 -> 145 (300), 265 -> 257 (528); 40^3 65.6 -> 60.4
+// (36), 127 -> 118 (105), 333 -> 335 (300).  No gain at 16^3, none from 48^3.
+constexpr long quad_planes(int n, size_t eb) {
+  if (eb != sizeof(cx<double>)) return 0;
+  return n == 24 ? 24 * 105L : n == 32 ? 32 * 400L : n == 40 ? 40 * 128L : 0L;
+}
+
 // Bytes of the transposed orbitals that a slab pass over `pairs` pairs takes on
 // split lines; 0: another form is used, because of the size or because the
 // copies (8 to 16 us at the smallest sizes) outweigh the pairs.
 size_t slab_split_bytes(const GridInfo& g, size_t eb, long pairs, long orbitals) {
   if (g.n < (eb == sizeof(cx<double>) ? kSplitSlabN<double> : kSplitSlabN<float>)) return 0;
+  if (pairs * g.n <= quad_planes(g.n, eb)) return 0;
   return pairs >= 4 * orbitals ? align_up((size_t)orbitals * g.ng * eb, 256) : 0;
 }
 
@@ -1039,10 +1051,11 @@ constexpr bool kOctOk = N % 8 == 0 && N >= 16;
 // pairs, 64^3 FP32 1.31 against 1.37 ms per 1,800; 40^3 FP64 0.55 against
 // 0.80 ms (one thread per line) per 1,353 pairs.
 template <int N, typename T>
-int pass_form(ace_ctx c, bool plane_pass) {
+int pass_form(ace_ctx c, bool plane_pass, long np) {
   const int sh = line_shape(c, N, (int)sizeof(cx<T>));
   if (sh == 8) return kOctOk<N, T> ? 8 : 4;
   if (sh == 1 || sh == 4 || sh == 16) return sh;
+  if (np * N <= quad_planes(N, sizeof(cx<T>))) return 4;
   if (plane_pass) return N >= kSplitPlaneN<T> ? 2 : 1;
   return N >= (sizeof(T) == 8 ? 64 : 72) ? 4 : 1;
 }
@@ -1075,7 +1088,7 @@ ace_status fwd_slab(ace_ctx c, const cx<T>* phi, long ldphi, const cx<T>* psi, l
     return ACE_OK;
   }
   const dim3 grid(xcd_pad((long)N * np));
-  const int form = pass_form<N, T>(c, false);
+  const int form = pass_form<N, T>(c, false, np);
   if constexpr (kOctOk<N, T>)
     if (form == 8)
       return launch(c, "pair_fwd_slab", k_pair_fwd_slab_oct<N, T>, grid, dim3(8 * N), 0, phi,
@@ -1105,7 +1118,7 @@ ace_status plane(ace_ctx c, cx<T>* buf, const ace_kspec& ks, int np) {
     return ACE_OK;
   }
   const dim3 grid(xcd_pad((long)N * np));
-  const int form = pass_form<N, T>(c, true);
+  const int form = pass_form<N, T>(c, true, np);
   if constexpr (N >= kSplitPlaneN<T>)
     if (form == 2) return split_plane<T>(c, N, buf, ks, np);
   if constexpr (kOctOk<N, T>)

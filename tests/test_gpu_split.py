@@ -13,8 +13,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("n,prec,nocc,nband", [
     (40, "fp64", 29, 33),   # runs of 8 (slab) and 4 (plane) and their remainders
-    (40, "fp64", 8, 8),     # the fewest pairs that take it, one per workgroup
-    (40, "fp64", 7, 7),     # one below
+    (40, "fp64", 16, 16),   # the fewest pairs that take it
+    (40, "fp64", 15, 15),   # quads
     (48, "fp64", 17, 18),   # runs of 3
     (64, "fp64", 12, 13),   # runs of 2
     (72, "fp64", 11, 14),
@@ -58,7 +58,7 @@ def test_split_lines_equal_quads(n, prec, nocc, nband):
 def test_captured_without_room_for_copies():
     import torch
     from paper_1601_07159_amd import ace
-    n, nocc, nband = 40, 12, 14
+    n, nocc, nband = 48, 12, 14
     print("split lines: captured without room for the copies", flush=True)
     gg = ggrid(n, 0.43 * n)
     x = to_gpu(synth.smooth_orbitals(n, 0.43 * n, nband, seed=5), "fp64")
