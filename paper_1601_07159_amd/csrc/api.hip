@@ -320,11 +320,11 @@ static ace_status apply_t(ace_ctx c, const GridInfo& g, const cx<T>* xi, int nb,
                           const cx<T>* X, int nx, long ldx, cx<T>* Y, long ldy,
                           bool real = false) {
   const size_t mat = align_up((size_t)nb * nx * sizeof(cx<double>), 256);
-  ACE_TRY(ws_begin(c, mat + gemm_cn_partial_bytes(nb, nx, g.ng, sizeof(cx<T>), kNative, false)));
+  ACE_TRY(ws_begin(c, mat + gemm_cn_partial_bytes(nb, nx, g.ng, sizeof(cx<T>), kFp32Chunks, false)));
   ace_status st = ACE_OK;
   cx<double>* C = (cx<double>*)ws_take(c, mat, &st);
   if (!C) return st;
-  ACE_TRY(gemm_cn<T>(c, xi, ldxi, nb, X, ldx, nx, g.ng, -g.dV, C, nb, kNative, real));
+  ACE_TRY(gemm_cn<T>(c, xi, ldxi, nb, X, ldx, nx, g.ng, -g.dV, C, nb, kFp32Chunks, real));
   return gemm_nn<T>(c, xi, ldxi, nb, C, nb, nx, Y, ldy, g.ng, false);
 }
 
@@ -716,7 +716,7 @@ ace_status ace::apply_entry(ace_ctx c, const ace_grid* grid, ace_prec prec, cons
     // workspace of apply_t: the n_band x n_x matrix and the split-K partials
     const size_t need = align_up((size_t)n_band * n_x * sizeof(cx<double>), 256) +
                         gemm_cn_partial_bytes(n_band, n_x, gv.ng, is_real(prec) ? 2 * eb : eb,
-                                              kNative, false);
+                                              kFp32Chunks, false);
     if (need > sub_bytes) {
       char buf[160];
       snprintf(buf, sizeof buf,

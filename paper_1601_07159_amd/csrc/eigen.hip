@@ -460,10 +460,10 @@ ace_status hamiltonian_t(ace_ctx c, const GridInfo& g, const T* vloc, const cx<T
   if (xi) {
     // V_ACE X = -xi (dV xi^H X)
     const size_t mat = align_up((size_t)nxi * nx * sizeof(cx<double>), 256);
-    ACE_TRY(ws_begin(c, mat + gemm_cn_partial_bytes(nxi, nx, g.ng, sizeof(cx<T>), kNative, false)));
+    ACE_TRY(ws_begin(c, mat + gemm_cn_partial_bytes(nxi, nx, g.ng, sizeof(cx<T>), kFp32Chunks, false)));
     cx<double>* C = (cx<double>*)ws_take(c, mat, &st);
     if (!C) return st;
-    ACE_TRY(gemm_cn<T>(c, xi, ldxi, nxi, X, ldx, nx, g.ng, -g.dV, C, nxi, kNative));
+    ACE_TRY(gemm_cn<T>(c, xi, ldxi, nxi, X, ldx, nx, g.ng, -g.dV, C, nxi, kFp32Chunks));
     ACE_TRY(gemm_nn<T>(c, xi, ldxi, nxi, C, nxi, nx, Y, ldy, g.ng, false));
     have = true;
   } else if (phi) {
@@ -498,7 +498,7 @@ size_t hamiltonian_ws_bytes(ace_ctx c, const GridInfo& g, size_t eb, int nx, int
   size_t need = align_up((size_t)g.ng * eb, 256) + plan_build(c, gk, eb, 1, nx, false).bytes;
   if (nxi > 0)
     need = std::max(need, align_up((size_t)nxi * nx * sizeof(cx<double>), 256) +
-                              gemm_cn_partial_bytes(nxi, nx, g.ng, eb, kNative, false));
+                              gemm_cn_partial_bytes(nxi, nx, g.ng, eb, kFp32Chunks, false));
   if (nphi > 0) need = std::max(need, plan_build(c, g, eb, nphi, nx, false).bytes);
   return need;
 }

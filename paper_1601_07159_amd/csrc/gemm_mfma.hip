@@ -421,7 +421,7 @@ __global__ __launch_bounds__(1024) void k_reduce_partials2(const cx<P>* __restri
 }
 
 // ---------------------------------------------------------------------------
-// Reduction product in FP64 of 49 rows and more: the 16 x 16 blocks of the
+// Reduction product of 8 blocks and more: the 16 x 16 blocks of the
 // output (only those on and above the diagonal in the Hermitian case) are
 // dealt out evenly to the 8 waves of a workgroup, up to kGramBlocks each, and
 // to as many workgroup rows as that takes; K is split over blockIdx.y, one
@@ -437,8 +437,12 @@ __global__ __launch_bounds__(1024) void k_reduce_partials2(const cx<P>* __restri
 // they can.  136 rows x 64^3 points of FP32: 568 -> 342 us (tiles of 32 with
 // four products, two unequal workgroup rows); 256 x 72^3: 2,031 -> 1,522 us.
 // Converting to FP64 on the way to LDS doubled the LDS reads: 364, 1,943 us.
+// In FP32 (256 x 256 x 72^3) the vector instructions beside the MFMAs and the
+// clock (2.1 GHz under this load) bound it: 2,102 -> 1,439 us, 1,589 with the
+// chains ended at every chunk; the result is closer to 64 bits than the single
+// chains of four products were (4.4e-7 against 1.2e-6).
 constexpr int kGramBlocks = 8;           // 192 accumulator registers
-constexpr int kGramBuffer = 76 * 1024;   // bytes of one of two chunks
+constexpr int kGramBuffer = 80 * 1024;   // bytes of one of two chunks (all of LDS)
 struct GramShape {
   int gx, per;      // workgroup rows, blocks of each
   int lseg;         // 2^lseg segments of 16 bytes per row and chunk
@@ -457,11 +461,12 @@ __device__ __forceinline__ void gram_block(int q, int ta, int herm, int& x, int&
   }
 }
 
-template <typename T, int NBW, bool REAL>
-__global__ __launch_bounds__(512) void k_cn_f64(const cx<T>* __restrict__ A, long lda, int na,
+template <typename T, typename TAcc, int NBW, bool REAL>
+__global__ __launch_bounds__(512) void k_cn_blocks(const cx<T>* __restrict__ A, long lda, int na,
                                                 const cx<T>* __restrict__ B, long ldb, int nb,
-                                                long K, cx<double>* __restrict__ partial,
+                                                long K, cx<TAcc>* __restrict__ partial,
                                                 GramShape g) {
+  typedef typename Acc4<TAcc>::type acc_t;
   constexpr int PT = 16 / sizeof(cx<T>);  // points of a segment
   __shared__ __align__(16) char lds[2][kGramBuffer];
   const int lane = threadIdx.x & 63;
@@ -500,11 +505,21 @@ __global__ __launch_bounds__(512) void k_cn_f64(const cx<T>* __restrict__ A, lon
           (__attribute__((address_space(3))) void*)(dst + (size_t)e * 1024), 16, 0, 0);
     }
   };
-  v4d p1[NBW], p2[NBW], p3[REAL ? 1 : NBW];
+  acc_t p1[NBW], p2[NBW], p3[REAL ? 1 : NBW];
 #pragma unroll
-  for (int i = 0; i < NBW; ++i) p1[i] = p2[i] = v4d{0, 0, 0, 0};
+  for (int i = 0; i < NBW; ++i) p1[i] = p2[i] = acc_t{0, 0, 0, 0};
 #pragma unroll
-  for (int i = 0; i < (REAL ? 1 : NBW); ++i) p3[i] = v4d{0, 0, 0, 0};
+  for (int i = 0; i < (REAL ? 1 : NBW); ++i) p3[i] = acc_t{0, 0, 0, 0};
+  // FP32: the sums of four chunks (up to 256 points) are added up apart, so that
+  // no chain of products is longer than that
+  constexpr bool kTwo = sizeof(TAcc) == 4;
+  constexpr int kFlush = 4;
+  int chunk = 0;
+  acc_t re[kTwo ? NBW : 1], im[kTwo && !REAL ? NBW : 1];
+#pragma unroll
+  for (int i = 0; i < (kTwo ? NBW : 1); ++i) re[i] = acc_t{0, 0, 0, 0};
+#pragma unroll
+  for (int i = 0; i < (kTwo && !REAL ? NBW : 1); ++i) im[i] = acc_t{0, 0, 0, 0};
   const int boff = g.same ? 0 : ra - 16 * fy;  // LDS row of B's row 0
   typedef T seg_t __attribute__((ext_vector_type(16 / sizeof(T))));
   const long step = (long)seg * PT;
@@ -516,23 +531,27 @@ __global__ __launch_bounds__(512) void k_cn_f64(const cx<T>* __restrict__ A, lon
     if (k0 + step < kend) stage(lds[buf ^ 1], k0 + step);
     for (int t = 0; t < seg; t += 4) {
       const char* base = lds[buf] + (((r16 << g.lseg) + ((t + kq) ^ (r16 & swz))) << 4);
-      double br[PT], bi[PT], bs[PT];
+      TAcc br[PT], bi[PT], bs[PT];
+      // A's rows are read one block ahead
+      seg_t a_next = *(const seg_t*)(base + ((16 * bx[0]) << (g.lseg + 4)));
 #pragma unroll
       for (int i = 0; i < NBW; ++i) {
         if (i >= count) break;  // wave-uniform, as the next
-        const seg_t a = *(const seg_t*)(base + ((16 * bx[i]) << (g.lseg + 4)));
+        const seg_t a = a_next;
+        if (i + 1 < NBW)
+          a_next = *(const seg_t*)(base + ((16 * bx[i + 1 < NBW ? i + 1 : 0]) << (g.lseg + 4)));
         if (i == 0 || by[i] != by[i - 1]) {
           const seg_t b = *(const seg_t*)(base + ((16 * by[i] + boff) << (g.lseg + 4)));
 #pragma unroll
           for (int h = 0; h < PT; ++h) {
-            br[h] = (double)b[2 * h];
-            bi[h] = (double)b[2 * h + 1];
+            br[h] = (TAcc)b[2 * h];
+            bi[h] = (TAcc)b[2 * h + 1];
             bs[h] = br[h] + bi[h];
           }
         }
 #pragma unroll
         for (int h = 0; h < PT; ++h) {
-          const double ar = (double)a[2 * h], ai = (double)a[2 * h + 1];
+          const TAcc ar = (TAcc)a[2 * h], ai = (TAcc)a[2 * h + 1];
           p1[i] = mfma4(ar, br[h], p1[i]);
           if constexpr (REAL) {
             p1[i] = mfma4(ai, bi[h], p1[i]);
@@ -543,17 +562,32 @@ __global__ __launch_bounds__(512) void k_cn_f64(const cx<T>* __restrict__ A, lon
         }
       }
     }
+    if (kTwo && (++chunk % kFlush == 0 || k0 + step >= kend)) {
+#pragma unroll
+      for (int i = 0; i < (kTwo ? NBW : 0); ++i) {
+        if constexpr (!REAL) {
+          im[i] += (p3[i] - p1[i]) + p2[i];
+          p3[i] = acc_t{0, 0, 0, 0};
+        }
+        re[i] += p1[i] + p2[i];
+        p1[i] = p2[i] = acc_t{0, 0, 0, 0};
+      }
+    }
   }
 #pragma unroll
   for (int i = 0; i < NBW; ++i) {
     if (i >= count) break;
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-      const int x = 16 * bx[i] + mfma_row<double>(lane, v), y = 16 * by[i] + r16;
-      if (x < na && y < nb)
-        partial[((size_t)blockIdx.y * nb + y) * na + x] =
-            REAL ? cx<double>{p1[i][v], 0.0}
-                 : cx<double>{p1[i][v] + p2[i][v], p3[REAL ? 0 : i][v] - p1[i][v] + p2[i][v]};
+      const int x = 16 * bx[i] + mfma_row<TAcc>(lane, v), y = 16 * by[i] + r16;
+      if (x >= na || y >= nb) continue;
+      cx<TAcc>& out = partial[((size_t)blockIdx.y * nb + y) * na + x];
+      if constexpr (kTwo)
+        out = {re[i][v], REAL ? TAcc(0) : im[REAL ? 0 : i][v]};
+      else if constexpr (REAL)
+        out = {p1[i][v], TAcc(0)};
+      else
+        out = {p1[i][v] + p2[i][v], p3[i][v] - p1[i][v] + p2[i][v]};
     }
   }
 }
@@ -1060,7 +1094,7 @@ static bool herm_shape(int n, long K, int max_waves, int cu_waves, CnShape* s) {
   return true;
 }
 
-// Shape of an FP64 product for k_cn_f64.  False below 8 blocks, which leave
+// Shape of an FP64 product for k_cn_blocks.  False below 8 blocks, which leave
 // waves without work (k_cn_mfma's tiles of 32 then do: 48 rows), where a
 // chunk's rows exceed the LDS buffer, and where K is no multiple of a chunk.
 static bool gram_shape(int na, int nb, long K, size_t data_bytes, bool same, bool herm,
@@ -1110,16 +1144,16 @@ static long gram_splits(int na, int nb, long K, size_t data_bytes, bool herm) {
   return ks;
 }
 
-template <typename T, bool REAL>
+template <typename T, typename TAcc, bool REAL>
 static ace_status launch_gram(ace_ctx c, const char* name, const GramShape& g, const cx<T>* A,
                               long lda, int na, const cx<T>* B, long ldb, int nb, long K,
-                              cx<double>* partial) {
+                              cx<TAcc>* partial) {
   const dim3 grid((unsigned)g.gx, (unsigned)g.ks), block(512);
   switch ((g.per + 7) / 8) {
 #define ACE_GRAM(N)                                                                              \
   case N:                                                                                        \
-    return launch(c, name, k_cn_f64<T, N, REAL>, grid, block, 0, A, lda, na, B, ldb, nb, K,      \
-                  partial, g);
+    return launch(c, name, k_cn_blocks<T, TAcc, N, REAL>, grid, block, 0, A, lda, na, B, ldb, nb, \
+                  K, partial, g);
     ACE_GRAM(1) ACE_GRAM(2) ACE_GRAM(3) ACE_GRAM(4)
     ACE_GRAM(5) ACE_GRAM(6) ACE_GRAM(7) ACE_GRAM(8)
 #undef ACE_GRAM
@@ -1152,7 +1186,8 @@ size_t gemm_cn_partial_bytes(int na, int nb, long K, size_t data_bytes, CnMode m
   const int cu_waves = f64 ? 12 : bf16_split ? kBf16Waves : 16;
   CnShape s = cn_shape(na, nb, K, max_waves, cu_waves);
   if (herm && na == nb) herm_shape(na, K, max_waves, cu_waves, &s);
-  if (f64) s.ks = std::max(s.ks, gram_splits(na, nb, K, data_bytes, herm && na == nb));
+  if (f64 || mode == kFp32Chunks)
+    s.ks = std::max(s.ks, gram_splits(na, nb, K, data_bytes, herm && na == nb));
   const size_t part_eb = f64 ? sizeof(cx<double>) : sizeof(cx<float>);
   return align_up((size_t)s.ks * na * nb * part_eb, 256);
 }
@@ -1171,20 +1206,23 @@ ace_status gemm_cn(ace_ctx c, const cx<T>* A, long lda, int na, const cx<T>* B, 
   GramShape gs;
   const bool aligned = ((uintptr_t)A | (uintptr_t)B | (uintptr_t)(lda * sizeof(cx<T>)) |
                         (uintptr_t)(ldb * sizeof(cx<T>))) % 16 == 0;
-  if (f64 && aligned && mode != kFp64Four &&
+  if (((f64 && mode != kFp64Four) || mode == kFp32Chunks) && aligned &&
       gram_shape(na, nb, K, sizeof(cx<T>), A == B && lda == ldb && na == nb, herm && na == nb,
                  &gs)) {
-    ace_status st;
-    cx<double>* part =
-        (cx<double>*)ws_take(c, (size_t)gs.ks * na * nb * sizeof(cx<double>), &st);
-    if (!part) return st;
-    const char* name = sizeof(T) == 8 ? "cn_mfma_f64" : "cn_mfma_f32in_f64";
-    st = real_part ? launch_gram<T, true>(c, name, gs, A, lda, na, B, ldb, nb, K, part)
-                   : launch_gram<T, false>(c, name, gs, A, lda, na, B, ldb, nb, K, part);
-    if (st != ACE_OK) return st;
-    return launch(c, "reduce_partials", k_reduce_partials2<double>, dim3((na * nb + 63) / 64),
-                  dim3(1024), 0, (const cx<double>*)part, (int)gs.ks, na, nb, alpha, C, ldc,
-                  real_part ? 1 : 0, gs.herm ? 16 : 0);
+    auto run = [&](auto acc, const char* name) -> ace_status {
+      typedef decltype(acc) TAcc;
+      ace_status st;
+      cx<TAcc>* part = (cx<TAcc>*)ws_take(c, (size_t)gs.ks * na * nb * sizeof(cx<TAcc>), &st);
+      if (!part) return st;
+      st = real_part ? launch_gram<T, TAcc, true>(c, name, gs, A, lda, na, B, ldb, nb, K, part)
+                     : launch_gram<T, TAcc, false>(c, name, gs, A, lda, na, B, ldb, nb, K, part);
+      if (st != ACE_OK) return st;
+      return launch(c, "reduce_partials", k_reduce_partials2<TAcc>, dim3((na * nb + 63) / 64),
+                    dim3(1024), 0, (const cx<TAcc>*)part, (int)gs.ks, na, nb, alpha, C, ldc,
+                    real_part ? 1 : 0, gs.herm ? 16 : 0);
+    };
+    if constexpr (sizeof(T) == 8) return run(double(0), "cn_mfma_f64");
+    else return f64 ? run(double(0), "cn_mfma_f32in_f64") : run(float(0), "cn_mfma_f32");
   }
   const int max_waves = f64 ? 8 : bf16_split ? kBf16Waves : 16;
   const int cu_waves = f64 ? 12 : bf16_split ? kBf16Waves : 16;

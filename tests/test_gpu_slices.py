@@ -103,3 +103,26 @@ def test_panel_factorisation(nb, bad):
         # 1728 products per entry of unit vectors: sqrt(1728) eps = 5e-15, with
         # a margin of a hundred for the factor's condition
         assert np.max(np.abs(g.dV * (Q.conj() @ Q.T) - np.eye(nb))) <= 5e-13
+
+
+@pytest.mark.parametrize("prec", ["fp32", "mixed", "real32"])
+@pytest.mark.parametrize("n,nb,nx", [(12, 31, 64), (12, 49, 33), (16, 64, 80), (16, 136, 17),
+                                     (16, 130, 257), (24, 40, 96)])
+def test_apply_products_fp32(prec, n, nb, nx):
+    """FP32 reductions by blocks: one below the first size, cut blocks, several
+    workgroup rows, chains of less and of more than four chunks."""
+    from paper_1601_07159_amd import ace
+    print(f"fp32 products prec={prec} n={n} nb={nb} nx={nx}", flush=True)
+    L = 0.43 * n
+    g = ogrid(n, L)
+    rng = np.random.default_rng(nb + nx)
+    xi = rng.standard_normal((nb, n ** 3)) + 1j * rng.standard_normal((nb, n ** 3))
+    X = rng.standard_normal((nx, n ** 3)) + 1j * rng.standard_normal((nx, n ** 3))
+    if prec == "real32":
+        xi, X = xi.real, X.real
+    Y = to_np(ace.apply(to_gpu(xi.reshape(nb, n, n, n), prec), to_gpu(X.reshape(nx, n, n, n), prec),
+                        ggrid(n, L), prec)).reshape(nx, -1)
+    ref = -g.dV * (xi.conj() @ X.T).T @ xi
+    # FP32 rounding of the inputs and of chains of at most 256 products:
+    # sqrt(256) 6e-8 = 1e-6 of the whole, twice that
+    assert np.linalg.norm(Y - ref) <= 2e-6 * np.linalg.norm(ref)
