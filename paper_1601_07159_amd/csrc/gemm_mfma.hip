@@ -719,14 +719,19 @@ constexpr int kNnResA = 80;
 // workgroup: 256 orbitals x 64 columns x 8 bytes = 128 KiB of LDS.
 constexpr int kNnResA2 = 256;
 
+// upper: C is upper triangular (C[a][b] = 0 for a > b), so a step of four
+// orbitals past the last column of a 16-column block adds nothing to it and
+// its MFMAs are skipped (FP64 with up to two column blocks; others are not
+// asked to).
 template <typename TIn, typename TAcc, int NBB, int ACAP>
 __global__ __launch_bounds__(512) void k_nn_mfma_res(const cx<TIn>* __restrict__ A, long lda,
                                                      int na, const cx<double>* __restrict__ C,
                                                      int ldc, int nb, cx<TIn>* __restrict__ Y,
-                                                     long ldy, long K) {
+                                                     long ldy, long K, int upper) {
   typedef typename Acc4<TAcc>::type acc_t;
   constexpr int XB = NnShape<TAcc>::XB;
   constexpr int NBC = 16 * NBB;
+  constexpr bool kSkip = sizeof(TAcc) == 8;
   constexpr int R = sizeof(TIn) == 8 ? 4 : 8;  // grid-row loads in flight
   __shared__ TAcc cs_re[ACAP][NBC];
   __shared__ TAcc cs_im[ACAP][NBC];
@@ -797,6 +802,7 @@ __global__ __launch_bounds__(512) void k_nn_mfma_res(const cx<TIn>* __restrict__
         if (st < nsteps) {
 #pragma unroll
           for (int y = 0; y < NBB; ++y) {
+            if (kSkip && upper && 4 * st > b0 + 16 * y + 15) continue;  // wave-uniform
             const TAcc cr = cb[j & 1][y][0], ci = cb[j & 1][y][1];
 #pragma unroll
             for (int x = 0; x < XB; ++x) {
@@ -1267,11 +1273,14 @@ static ace_status nn_dispatch(ace_ctx c, const char* name, const cx<TIn>* A, lon
                               const cx<double>* C, int ldc, int nb, cx<TIn>* Y, long ldy,
                               long K, bool c_upper) {
   // In FP64 slices of C in LDS, up to 608 orbitals and 32 slices; past that C is
-  // staged chunk by chunk.
+  // staged chunk by chunk.  Up to 32 columns of a short product keep the other
+  // forms, whose workgroups are smaller and whose loads run further ahead: 64
+  // orbitals and 8 columns at 24^3 23 against 32 us, 128 and 8 at 32^3 45
+  // against 55 us (whole calls), while at 48^3 slices are the faster ones.
   if constexpr (sizeof(TAcc) == 8) {
     NnSlices sl;
     unsigned grid;
-    if (nn_slices(na, nb, K, c_upper, &sl, &grid))
+    if ((nb > 32 || K > 65536) && nn_slices(na, nb, K, c_upper, &sl, &grid))
       return launch(c, name, k_nn_f64<TIn>, dim3(grid), dim3(512), 0, A, lda, na, C, ldc, Y, ldy,
                     K, c_upper ? 1 : 0, sl);
   }
@@ -1287,13 +1296,13 @@ static ace_status nn_dispatch(ace_ctx c, const char* name, const cx<TIn>* A, lon
     const long cap = (256 + gy - 1) / gy;                                                      \
     if (gx > cap) gx = cap;                                                                    \
     return launch(c, name, k_nn_mfma_res<TIn, TAcc, NBBV, CAP>, dim3((unsigned)gx, gy),        \
-                  dim3(512), 0, A, lda, na, C, ldc, nb, Y, ldy, K);                            \
+                  dim3(512), 0, A, lda, na, C, ldc, nb, Y, ldy, K, c_upper ? 1 : 0);           \
   }
 #define ACE_NN(NBBV)                                                                           \
   case NBBV: {                                                                                 \
-    if constexpr (sizeof(TAcc) == 4) {                                                         \
+    if constexpr (sizeof(TAcc) == 4 || NBBV <= 2) {                                            \
       if (resident) ACE_NN_RES(NBBV, kNnResA)                                                  \
-      if constexpr (NBBV <= 4)                                                                 \
+      if constexpr (sizeof(TAcc) == 4 && NBBV <= 4)                                            \
         if (resident2) ACE_NN_RES(NBBV, kNnResA2)                                              \
     }                                                                                          \
     const long rows = NnShape<TAcc>::ROWS;                                                    \
