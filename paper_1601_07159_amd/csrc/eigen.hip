@@ -104,6 +104,7 @@ inline unsigned stream_blocks(long total) {
 // A is kept in LDS up to kJacobiLds rows, in global scratch beyond.
 constexpr int kJacobiMax = 512;
 constexpr int kJacobiLds = 88;  // 88^2 complex128 = 121 KiB of LDS
+constexpr int kJacobiSmall = 32;  // up to here the vectors turn along with A
 constexpr int kJacobiSweeps = 30;
 
 struct alignas(16) JacobiRot {
@@ -171,9 +172,10 @@ __device__ __forceinline__ void jacobi_block(cx<double> (&b)[2][2], const Jacobi
 }
 
 // A = (S + S^H)/2 (ne x ne, the padding of odd n zero).
+template <int NT>
 __device__ __forceinline__ void jacobi_load(const cx<double>* __restrict__ S, int lds_, int n,
                                             int ne, cx<double>* A, int lda) {
-  for (int e = threadIdx.x; e < ne * ne; e += 1024) {
+  for (int e = threadIdx.x; e < ne * ne; e += NT) {
     const int i = e % ne, j = e / ne;
     cx<double> v = {0.0, 0.0};
     if (i < n && j < n) {
@@ -187,11 +189,12 @@ __device__ __forceinline__ void jacobi_load(const cx<double>* __restrict__ S, in
 
 // Whether the off-diagonal Frobenius norm of A is at most tol times the whole
 // one (the same answer in every thread).
+template <int NT>
 __device__ __forceinline__ bool jacobi_converged(const cx<double>* A, int lda, int n, double tol) {
-  __shared__ double red[2][1024];
+  __shared__ double red[2][NT];
   const int t = threadIdx.x;
   double off = 0.0, all = 0.0;
-  for (int e = t; e < n * n; e += 1024) {
+  for (int e = t; e < n * n; e += NT) {
     const int i = e % n, j = e / n;
     const cx<double> u = A[i + j * lda];
     const double v = fma(u.x, u.x, u.y * u.y);
@@ -201,7 +204,7 @@ __device__ __forceinline__ bool jacobi_converged(const cx<double>* A, int lda, i
   red[0][t] = off;
   red[1][t] = all;
   __syncthreads();
-  for (int w = 512; w > 0; w >>= 1) {
+  for (int w = NT / 2; w > 0; w >>= 1) {
     if (t < w) {
       red[0][t] += red[0][t + w];
       red[1][t] += red[1][t + w];
@@ -215,10 +218,11 @@ __device__ __forceinline__ bool jacobi_converged(const cx<double>* A, int lda, i
 
 // ctl[0] = the number of sweeps; the eigenvalues in ascending order (ties by
 // index) and the rank of diagonal entry i in ctl[1 + i].
+template <int NT>
 __device__ __forceinline__ void jacobi_finish(const cx<double>* A, int lda, int n, int sweeps,
                                               int* __restrict__ ctl, double* __restrict__ evals) {
   if (threadIdx.x == 0) ctl[0] = sweeps;
-  for (int i = threadIdx.x; i < n; i += 1024) {
+  for (int i = threadIdx.x; i < n; i += NT) {
     const double ei = A[i + i * lda].x;
     int rank = 0;
     for (int j = 0; j < n; ++j) {
@@ -255,28 +259,44 @@ struct JacobiPos {  // the two indices of a pair, as offsets of one stride
   }
 };
 
-__global__ __launch_bounds__(1024) void k_jacobi_sweeps_lds(const cx<double>* __restrict__ S,
+//
+// VEC (n <= kJacobiSmall): threads without blocks turn the vectors V along, each
+// one pair of columns of one row, instead of a second launch that replays the
+// rotations: the Rayleigh-Ritz step on 16 vectors at 16^3 181 -> 158 us, on 8
+// 95 -> 82 us, with 256 threads up to n = 16 (170 and 86 us with 1,024).
+template <int LD, bool VEC, int NT>
+__global__ __launch_bounds__(NT) void k_jacobi_sweeps_lds(const cx<double>* __restrict__ S,
                                                             int lds_, int n,
                                                             JacobiRot* __restrict__ rots,
                                                             int* __restrict__ ctl,
                                                             double* __restrict__ evals,
-                                                            int max_sweeps, double tol) {
-  constexpr int LD = kJacobiLds;
+                                                            int max_sweeps, double tol,
+                                                            cx<double>* __restrict__ Vout) {
   constexpr int RB = (int)sizeof(cx<double>), CB = LD * RB;  // row and column strides in bytes
   typedef double v2d __attribute__((ext_vector_type(2)));
   __shared__ alignas(16) cx<double> A[LD * LD];
   __shared__ v2d rot[2][LD / 2];  // (cs, sn) and (er, ei): 16-byte strides, no bank conflicts
-  static_assert((LD / 2) * ((LD / 2 + 1) / 2) <= 1024 && LD / 2 <= 64, "two blocks per thread");
+  constexpr int LV = LD + 1;
+  __shared__ cx<double> V[VEC ? LD * LV : 1];
+  constexpr int kFirstV = (LD / 2) * ((LD / 2 + 1) / 2);  // threads before have blocks
+  static_assert(!VEC || kFirstV + LD * (LD / 2) <= NT - 64, "a thread per row and pair of V");
+  static_assert((LD / 2) * ((LD / 2 + 1) / 2) <= NT && LD / 2 <= 64, "two blocks per thread");
   const int t = threadIdx.x;
   const int ne = n + (n & 1), m = ne - 1, np = ne / 2, dl = (np + 1) / 2;
-  jacobi_load(S, lds_, n, ne, A, LD);
+  jacobi_load<NT>(S, lds_, n, ne, A, LD);
   const int k = t % np;
   const bool has0 = t / np < dl, has1 = has0 && t / np + dl < np;
   const int l0 = has0 ? t / np : 0, l1 = has1 ? l0 + dl : 0;
-  const int kr = t - 960;  // pair whose rotation this thread forms (last wave)
+  const int kr = t - (NT - 64);  // pair whose rotation this thread forms (last wave)
   const bool rotator = kr >= 0 && kr < np;
   const int kc = rotator ? kr : 0;
   JacobiPos rk(k, m, RB), c0(l0, m, CB), c1(l1, m, CB), rr(kc, m, RB), rc(kc, m, CB);
+  const int tv = t - kFirstV;
+  const bool turner = VEC && tv >= 0 && tv < n * np;
+  const int rowv = turner ? tv / np : 0, kv = turner ? tv - rowv * np : 0;
+  JacobiPos pv(kv, m, 1);
+  if constexpr (VEC)
+    for (int e = t; e < LD * LV; e += NT) V[e] = {e / LV == e % LV ? 1.0 : 0.0, 0.0};
   auto at = [&](int off) {
     const v2d v = *reinterpret_cast<const v2d*>(reinterpret_cast<const char*>(A) + off);
     return cx<double>{v.x, v.y};
@@ -290,7 +310,7 @@ __global__ __launch_bounds__(1024) void k_jacobi_sweeps_lds(const cx<double>* __
   };
   int sweep = 0;
   for (; sweep < max_sweeps; ++sweep) {
-    if (jacobi_converged(A, LD, n, tol)) break;
+    if (jacobi_converged<NT>(A, LD, n, tol)) break;
     JacobiRot* out = rots + (size_t)sweep * m * np + kc;
     for (int st = 0; st < m; ++st, out += np) {
       if (rotator) {
@@ -299,7 +319,7 @@ __global__ __launch_bounds__(1024) void k_jacobi_sweeps_lds(const cx<double>* __
         if (q < n * RB) r = jacobi_rotation(at(p + pc).x, at(q + qc).x, at(p + qc));
         rot[0][kr] = v2d{r.cs, r.sn};
         rot[1][kr] = v2d{r.er, r.ei};
-        *out = r;
+        if constexpr (!VEC) *out = r;
       }
       rr.advance();
       rc.advance();
@@ -333,10 +353,30 @@ __global__ __launch_bounds__(1024) void k_jacobi_sweeps_lds(const cx<double>* __
         put(pk + q1, b1[0][1]);
         put(qk + q1, b1[1][1]);
       }
+      if constexpr (VEC) {
+        const int p = pv.p(), q = pv.q();
+        pv.advance();
+        if (turner) {
+          const JacobiRot x = rotation(kv);
+          if (x.sn != 0.0) {
+            cx<double> vp = V[rowv * LV + p], vq = V[rowv * LV + q];
+            jacobi_cols(vp, vq, x);
+            V[rowv * LV + p] = vp;
+            V[rowv * LV + q] = vq;
+          }
+        }
+      }
       __syncthreads();
     }
   }
-  jacobi_finish(A, LD, n, sweep, ctl, evals);
+  jacobi_finish<NT>(A, LD, n, sweep, ctl, evals);
+  if constexpr (VEC) {
+    __syncthreads();
+    for (int e = t; e < n * n; e += NT) {
+      const int row = e % n, c = e / n;
+      Vout[row + (size_t)ctl[1 + c] * n] = V[row * LV + c];
+    }
+  }
 }
 
 // Sweeps for larger n: A (ne x ne) in global memory (L2), block by block.
@@ -349,12 +389,12 @@ __global__ __launch_bounds__(1024) void k_jacobi_sweeps(const cx<double>* __rest
   __shared__ JacobiRot rot[kJacobiMax / 2];
   const int t = threadIdx.x;
   const int ne = n + (n & 1), m = ne - 1, np = ne / 2;
-  jacobi_load(S, lds_, n, ne, A, ne);
+  jacobi_load<1024>(S, lds_, n, ne, A, ne);
   // the thread's first block (k, l) and the step to its next one
   const int k0 = t % np, l0 = t / np, dk = 1024 % np, dl = 1024 / np;
   int sweep = 0;
   for (; sweep < max_sweeps; ++sweep) {
-    if (jacobi_converged(A, ne, n, tol)) break;
+    if (jacobi_converged<1024>(A, ne, n, tol)) break;
     JacobiRot* out = rots + (size_t)sweep * m * np;
     for (int st = 0; st < m; ++st, out += np) {
       for (int k = t; k < np; k += 1024) {
@@ -388,7 +428,7 @@ __global__ __launch_bounds__(1024) void k_jacobi_sweeps(const cx<double>* __rest
       __syncthreads();
     }
   }
-  jacobi_finish(A, ne, n, sweep, ctl, evals);
+  jacobi_finish<1024>(A, ne, n, sweep, ctl, evals);
 }
 
 // V = the product of the recorded rotations, columns in the order of the
@@ -543,17 +583,26 @@ ace_status rayleigh_ritz_t(ace_ctx c, const GridInfo& g, const cx<T>* X, long ld
   c->ws_used = used;
   JacobiRot* rots = (JacobiRot*)ws_take(c, jacobi_rot_bytes(n), &st);
   if (!rots) return st;
-  if (n <= kJacobiLds)
-    ACE_TRY(launch(c, "jacobi_sweeps", k_jacobi_sweeps_lds, dim3(1), dim3(1024), 0,
-                   (const cx<double>*)S, n, n, rots, ctl, evals, kJacobiSweeps, 1e-15));
+  if (n <= 16)
+    ACE_TRY(launch(c, "jacobi_sweeps", k_jacobi_sweeps_lds<17, true, 256>, dim3(1), dim3(256), 0,
+                   (const cx<double>*)S, n, n, rots, ctl, evals, kJacobiSweeps, 1e-15, Q));
+  else if (n <= kJacobiSmall)
+    ACE_TRY(launch(c, "jacobi_sweeps", k_jacobi_sweeps_lds<kJacobiSmall + 1, true, 1024>, dim3(1),
+                   dim3(1024), 0, (const cx<double>*)S, n, n, rots, ctl, evals, kJacobiSweeps,
+                   1e-15, Q));
+  else if (n <= kJacobiLds)
+    ACE_TRY(launch(c, "jacobi_sweeps", k_jacobi_sweeps_lds<kJacobiLds, false, 1024>, dim3(1),
+                   dim3(1024), 0, (const cx<double>*)S, n, n, rots, ctl, evals, kJacobiSweeps,
+                   1e-15, Q));
   else
     ACE_TRY(launch(c, "jacobi_sweeps", k_jacobi_sweeps, dim3(1), dim3(1024), 0,
                    (const cx<double>*)S, n, n, A, rots, ctl, evals, kJacobiSweeps, 1e-15));
   const auto vectors = n <= 128   ? k_jacobi_vectors<1>
                        : n <= 256 ? k_jacobi_vectors<2>
                                   : k_jacobi_vectors<4>;
-  ACE_TRY(launch(c, "jacobi_vectors", vectors, dim3(n), dim3(64), 0, (const JacobiRot*)rots,
-                 (const int*)ctl, n, Q, n));
+  if (n > kJacobiSmall)
+    ACE_TRY(launch(c, "jacobi_vectors", vectors, dim3(n), dim3(64), 0, (const JacobiRot*)rots,
+                   (const int*)ctl, n, Q, n));
   ACE_TRY(gemm_nn<T>(c, X, ldx, n, Q, n, n, Xout, ldo, g.ng, true));
   if (HXout) ACE_TRY(gemm_nn<T>(c, HX, ldhx, n, Q, n, n, HXout, ldo, g.ng, true));
   return ACE_OK;

@@ -1,5 +1,6 @@
 """Rayleigh-Ritz at the edges of the Jacobi eigensolver's forms: one, two and
-three vectors, an odd count (padded), the last size with A in LDS and the first
+three vectors, the last size of the small and of the middle form with the
+vectors turned along and the first ones past them, an odd count (padded), the last size with A in LDS and the first
 ones in global memory, and the counts where a lane of the vector kernel takes a
 second and a third pair."""
 import numpy as np
@@ -12,7 +13,7 @@ from tests._helpers import ggrid, ogrid, to_gpu, to_np
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("nb", [1, 2, 3, 63, 87, 88, 89, 128, 129, 257])
+@pytest.mark.parametrize("nb", [1, 2, 3, 15, 16, 17, 31, 32, 33, 63, 87, 88, 89, 128, 129, 257])
 def test_ritz_pairs(nb):
     from paper_1601_07159_amd import ace
     n, L = 16, 12.0
