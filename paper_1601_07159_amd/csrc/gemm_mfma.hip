@@ -376,10 +376,10 @@ __global__ __launch_bounds__(1024) void k_reduce_partials2(const cx<P>* __restri
   const int el = threadIdx.x & 63, g = threadIdx.x >> 6;
   const int idx = blockIdx.x * 64 + el;
   const int a = idx % na, b = idx / na;
-  // Hermitian mode (herm: the side of a tile): tiles below the diagonal were not
+  // Hermitian mode (tiles of 2^herm): tiles below the diagonal were not
   // computed; the entries of the tiles above it are written twice, the second
   // time conjugated
-  const bool live = idx < na * nb && !(herm && a / herm > b / herm);
+  const bool live = idx < na * nb && !(herm && a >> herm > b >> herm);
   double sr = 0.0, si = 0.0;
   if (live) {
     const cx<P>* p = partial + idx;
@@ -416,7 +416,7 @@ __global__ __launch_bounds__(1024) void k_reduce_partials2(const cx<P>* __restri
   if (g == 0 && live) {
     const double re = alpha * red[0][0][el], im = real_part ? 0.0 : alpha * red[1][0][el];
     C[a + (size_t)b * ldc] = {re, im};
-    if (herm && a / herm < b / herm) C[b + (size_t)a * ldc] = {re, -im};
+    if (herm && a >> herm < b >> herm) C[b + (size_t)a * ldc] = {re, -im};
   }
 }
 
@@ -1225,7 +1225,7 @@ ace_status gemm_cn(ace_ctx c, const cx<T>* A, long lda, int na, const cx<T>* B, 
       if (st != ACE_OK) return st;
       return launch(c, "reduce_partials", k_reduce_partials2<TAcc>, dim3((na * nb + 63) / 64),
                     dim3(1024), 0, (const cx<TAcc>*)part, (int)gs.ks, na, nb, alpha, C, ldc,
-                    real_part ? 1 : 0, gs.herm ? 16 : 0);
+                    real_part ? 1 : 0, gs.herm ? 4 : 0);
     };
     if constexpr (sizeof(T) == 8) return run(double(0), "cn_mfma_f64");
     else return f64 ? run(double(0), "cn_mfma_f32in_f64") : run(float(0), "cn_mfma_f32");
@@ -1234,7 +1234,7 @@ ace_status gemm_cn(ace_ctx c, const cx<T>* A, long lda, int na, const cx<T>* B, 
   const int cu_waves = f64 ? 12 : bf16_split ? kBf16Waves : 16;
   CnShape s = cn_shape(na, nb, K, max_waves, cu_waves);
   herm = herm && na == nb && herm_shape(na, K, max_waves, cu_waves, &s);
-  const int hm = herm ? 32 : 0;
+  const int hm = herm ? 5 : 0;  // log2 of a tile's side
   ace_status st;
   const size_t part_eb = f64 ? sizeof(cx<double>) : sizeof(cx<float>);
   void* partial = ws_take(c, (size_t)s.ks * na * nb * part_eb, &st);
@@ -1273,14 +1273,14 @@ static ace_status nn_dispatch(ace_ctx c, const char* name, const cx<TIn>* A, lon
                               const cx<double>* C, int ldc, int nb, cx<TIn>* Y, long ldy,
                               long K, bool c_upper) {
   // In FP64 slices of C in LDS, up to 608 orbitals and 32 slices; past that C is
-  // staged chunk by chunk.  Up to 32 columns of a short product keep the other
-  // forms, whose workgroups are smaller and whose loads run further ahead: 64
-  // orbitals and 8 columns at 24^3 23 against 32 us, 128 and 8 at 32^3 45
-  // against 55 us (whole calls), while at 48^3 slices are the faster ones.
+  // staged chunk by chunk.  Up to 16 columns, and up to 32 of a short product,
+  // keep the other forms, whose workgroups are smaller and whose loads run
+  // further ahead: 64 orbitals and 8 columns at 24^3 23 against 32 us, 128 and 8
+  // at 32^3 45 against 55 us, 4 and 4 at 48^3 32.4 against 33.3 us (whole calls).
   if constexpr (sizeof(TAcc) == 8) {
     NnSlices sl;
     unsigned grid;
-    if ((nb > 32 || K > 65536) && nn_slices(na, nb, K, c_upper, &sl, &grid))
+    if ((nb > 32 || (nb > 16 && K > 65536)) && nn_slices(na, nb, K, c_upper, &sl, &grid))
       return launch(c, name, k_nn_f64<TIn>, dim3(grid), dim3(512), 0, A, lda, na, C, ldc, Y, ldy,
                     K, c_upper ? 1 : 0, sl);
   }
