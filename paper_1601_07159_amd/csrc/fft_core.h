@@ -578,35 +578,33 @@ __device__ __forceinline__ int quad_block_index(int k, int M, int h) {
 }
 
 // ---------------------------------------------------------------------------
-// Lines split over T lanes 64 / T apart (T = 1, 2, 4; N = T M), so that 64 / T
-// consecutive lanes hold the same part of as many consecutive lines and a
-// global access of theirs is one contiguous run.  Part h of a line holds
-//   decimated  x[h + T m],           m = 0..M-1
+// Lines split over four lanes 16 apart (N = 4 M), so that 16 consecutive lanes
+// hold the same part of as many consecutive lines and a global access of theirs
+// is one contiguous run.  Part h of a line holds
+//   decimated  x[h + 4 m],           m = 0..M-1
 //   split      X[split_pos(r, h)],   r = 0..M-1
-// and N = T x M: an M-point DFT per lane, twiddles exp(S 2 pi i h k / N), then
-// the T-point DFTs over the parts.  For those the values are transposed
-// between T registers and T lanes (the gfx950 permlane swaps exchange two
+// and N = 4 x M: an M-point DFT per lane, twiddles exp(S 2 pi i h k / N), then
+// the 4-point DFTs over the parts.  For those the values are transposed
+// between four registers and four lanes (the gfx950 permlane swaps exchange two
 // registers between lane halves in one instruction, one per value and level),
-// after which each lane owns whole T-point DFTs: k = T j + h of its register
-// group j, outputs X[T j + h + M q] in register T j + q.  Against butterflies
+// after which each lane owns whole 4-point DFTs: k = 4 j + h of its register
+// group j, outputs X[4 j + h + M q] in register 4 j + q.  Against butterflies
 // across lanes (fft_quad_*: a swap and a multiply-add per component and level)
 // this saves half of the exchange instructions.  Registers past the last whole
-// group (M mod T of them) keep the butterfly form and the block positions.
-template <int N, int T>
+// group (M mod 4 of them) keep the butterfly form and the block positions.
+template <int N>
 struct Split {
-  static_assert(N % T == 0 && (T == 1 || T == 2 || T == 4), "split lines");
-  static constexpr int M = N / T;
-  static constexpr int D = 64 / T;         // lane distance of the parts
-  static constexpr int kGrouped = M - M % T;
+  static_assert(N % 4 == 0, "split lines");
+  static constexpr int M = N / 4;
+  static constexpr int kGrouped = M - M % 4;
 };
 
 // Position of register r of part h; kp(h) as for quads.
-template <int N, int T>
+template <int N>
 __device__ __forceinline__ int split_pos(int r, int h) {
-  using P = Split<N, T>;
-  if constexpr (T == 1) return r;
-  if (r < P::kGrouped) return r - r % T + P::M * (r % T) + h;
-  return r + P::M * (T == 2 ? h : ((h >> 1) | ((h & 1) << 1)));
+  using P = Split<N>;
+  if (r < P::kGrouped) return r - r % 4 + P::M * (r % 4) + h;
+  return r + P::M * ((h >> 1) | ((h & 1) << 1));
 }
 
 __device__ __forceinline__ void lane_swap16(float& a, float& b) {
@@ -647,35 +645,31 @@ __device__ __forceinline__ void lane_swap(cx<R>& a, cx<R>& b) {
   lane_swap<D>(a.y, b.y);
 }
 
-// v[q] of part h <-> v[h] of part q, q, h < T.
-template <int T, typename R>
+// v[q] of part h <-> v[h] of part q.
+template <typename R>
 __device__ __forceinline__ void split_transpose(cx<R>* v) {
-  if constexpr (T == 2) {
-    lane_swap<32>(v[0], v[1]);
-  } else if constexpr (T == 4) {
-    lane_swap<16>(v[0], v[1]);
-    lane_swap<16>(v[2], v[3]);
-    lane_swap<32>(v[0], v[2]);
-    lane_swap<32>(v[1], v[3]);
-  }
+  lane_swap<16>(v[0], v[1]);
+  lane_swap<16>(v[2], v[3]);
+  lane_swap<32>(v[0], v[2]);
+  lane_swap<32>(v[1], v[3]);
 }
 
 // Twiddles exp(S 2 pi i h k / N), stored [k][h] ([0]: S = -1, [1]: S = +1).
-template <int N, int T, typename R>
+template <int N, typename R>
 struct SplitRoots {
   cx<R> w[2][N];
   constexpr SplitRoots() : w() {
-    for (int k = 0; k < N / T; ++k)
-      for (int h = 0; h < T; ++h) {
+    for (int k = 0; k < N / 4; ++k)
+      for (int h = 0; h < 4; ++h) {
         const cs_pair p = ce_unit_root((long)h * k, N);
         const bool one = h * k == 0;
-        w[0][T * k + h] = one ? cx<R>{R(1), R(0)} : cx<R>{R(p.c), R(-1 * p.s)};
-        w[1][T * k + h] = one ? cx<R>{R(1), R(0)} : cx<R>{R(p.c), R(p.s)};
+        w[0][4 * k + h] = one ? cx<R>{R(1), R(0)} : cx<R>{R(p.c), R(-1 * p.s)};
+        w[1][4 * k + h] = one ? cx<R>{R(1), R(0)} : cx<R>{R(p.c), R(p.s)};
       }
   }
 };
-template <int N, int T, typename R>
-__constant__ constexpr SplitRoots<N, T, R> kSplitRoots{};
+template <int N, typename R>
+__constant__ constexpr SplitRoots<N, R> kSplitRoots{};
 
 // Rounding of the twiddle products between the line and the exchange, chosen so
 // that FP32 values are those of the quad forms as they were compiled: the
@@ -686,79 +680,71 @@ enum class TwRound { kIm, kImSums, kRe };
 
 // The lane's twiddles, from the tables in LDS (in registers they cost 2 M of
 // them, from memory a load each).
-template <int N, int T, typename R>
+template <int N, typename R>
 struct SplitTw {
   const cx<R>* s;
   __device__ __forceinline__ SplitTw(int h, const cx<R>* lds) : s(lds + h) {}
   template <int S, TwRound F>
   __device__ __forceinline__ void apply(cx<R>* v) const {
-    if constexpr (T > 1) {
 #pragma unroll
-      for (int k = 1; k < N / T; ++k) {
-        const cx<R> w = s[(S > 0 ? N : 0) + T * k];
-        const bool sum = N / T % 3 == 0 ? k % 3 == 0 : 2 * k == N / T;
-        v[k] = F == TwRound::kRe || (F == TwRound::kImSums && sum)
-                   ? cmul_fma<false, false>(v[k], w)
-                   : cmul_fma<false, true>(v[k], w);
-      }
+    for (int k = 1; k < N / 4; ++k) {
+      const cx<R> w = s[(S > 0 ? N : 0) + 4 * k];
+      const bool sum = N / 4 % 3 == 0 ? k % 3 == 0 : 2 * k == N / 4;
+      v[k] = F == TwRound::kRe || (F == TwRound::kImSums && sum) ? cmul_fma<false, false>(v[k], w)
+                                                                 : cmul_fma<false, true>(v[k], w);
     }
   }
 };
 
 // The part's own line: with pinned rounding where FP32 results are to be those
 // of the quad forms.
-template <int N, int T, int S, typename R>
+template <int N, int S, typename R>
 __device__ __forceinline__ void split_line(cx<R>* v) {
-  fft_line<N / T, S, R, sizeof(R) == 4 && (N / T == 16 || N / T == 18)>(v);
+  fft_line<N / 4, S, R, sizeof(R) == 4 && (N / 4 == 16 || N / 4 == 18)>(v);
 }
 
 // decimated -> split positions
-template <int N, int T, int S, TwRound F, typename R>
-__device__ __forceinline__ void fft_split(cx<R>* v, int h, const SplitTw<N, T, R>& tw) {
-  using P = Split<N, T>;
-  split_line<N, T, S, R>(v);
-  if constexpr (T > 1) {
-    tw.template apply<S, F>(v);
+template <int N, int S, TwRound F, typename R>
+__device__ __forceinline__ void fft_split(cx<R>* v, int h, const SplitTw<N, R>& tw) {
+  using P = Split<N>;
+  split_line<N, S, R>(v);
+  tw.template apply<S, F>(v);
 #pragma unroll
-    for (int g = 0; g < P::kGrouped; g += T) {
-      split_transpose<T>(v + g);
-      SmallDft<T, S, R>::run(v + g);
-    }
-    if constexpr (P::kGrouped < P::M) {
-      static_assert(T == 4, "leftover registers only with four parts");
-      const bool hi = (h >> 1) != 0, odd = (h & 1) != 0;
-      const R sg_hi = hi ? R(-1) : R(1), sg_odd = odd ? R(-1) : R(1);
+  for (int g = 0; g < P::kGrouped; g += 4) {
+    split_transpose(v + g);
+    SmallDft<4, S, R>::run(v + g);
+  }
+  if constexpr (P::kGrouped < P::M) {
+    const bool hi = (h >> 1) != 0, odd = (h & 1) != 0;
+    const R sg_hi = hi ? R(-1) : R(1), sg_odd = odd ? R(-1) : R(1);
 #pragma unroll
-      for (int k = P::kGrouped; k < P::M; ++k) {
-        v[k] = xor_bfly<32>(v[k], sg_hi);
-        v[k] = xor_bfly<16>(hi && odd ? mul_si<S>(v[k]) : v[k], sg_odd);
-      }
+    for (int k = P::kGrouped; k < P::M; ++k) {
+      v[k] = xor_bfly<32>(v[k], sg_hi);
+      v[k] = xor_bfly<16>(hi && odd ? mul_si<S>(v[k]) : v[k], sg_odd);
     }
   }
 }
 
 // split positions -> decimated
-template <int N, int T, int S, TwRound F, typename R>
-__device__ __forceinline__ void fft_unsplit(cx<R>* v, int h, const SplitTw<N, T, R>& tw) {
-  using P = Split<N, T>;
-  if constexpr (T > 1) {
+template <int N, int S, TwRound F, typename R>
+__device__ __forceinline__ void fft_unsplit(cx<R>* v, int h, const SplitTw<N, R>& tw) {
+  using P = Split<N>;
 #pragma unroll
-    for (int g = 0; g < P::kGrouped; g += T) {
-      SmallDft<T, S, R>::run(v + g);
-      split_transpose<T>(v + g);
-    }
-    if constexpr (P::kGrouped < P::M) {
-      const bool hi = (h >> 1) != 0, odd = (h & 1) != 0;
-      const R sg_hi = hi ? R(-1) : R(1), sg_odd = odd ? R(-1) : R(1);
-#pragma unroll
-      for (int k = P::kGrouped; k < P::M; ++k) {
-        v[k] = xor_bfly<16>(v[k], sg_odd);
-        v[k] = xor_bfly<32>(hi && odd ? mul_si<S>(v[k]) : v[k], sg_hi);
-      }
-    }
-    tw.template apply<S, F>(v);
+  for (int g = 0; g < P::kGrouped; g += 4) {
+    SmallDft<4, S, R>::run(v + g);
+    split_transpose(v + g);
   }
-  split_line<N, T, S, R>(v);
+  if constexpr (P::kGrouped < P::M) {
+    const bool hi = (h >> 1) != 0, odd = (h & 1) != 0;
+    const R sg_hi = hi ? R(-1) : R(1), sg_odd = odd ? R(-1) : R(1);
+#pragma unroll
+    for (int k = P::kGrouped; k < P::M; ++k) {
+      v[k] = xor_bfly<16>(v[k], sg_odd);
+      v[k] = xor_bfly<32>(hi && odd ? mul_si<S>(v[k]) : v[k], sg_hi);
+    }
+  }
+  tw.template apply<S, F>(v);
+  split_line<N, S, R>(v);
 }
 
 // ---------------------------------------------------------------------------

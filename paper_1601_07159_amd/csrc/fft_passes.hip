@@ -16,6 +16,7 @@
 //                         orbitals i of the block, inverse FFT, multiply by
 //                         phi_i, accumulate in thread-private LDS; w_j is
 //                         written once per block (no atomics, no barriers).
+// (Larger sizes run the first two on split lines, split_passes.h.)
 // The 1/N_g of the inverse transform, the minus sign and the caller's scale are
 // folded into the scaled kernel K'(G) = -scale K(G) / N_g, evaluated on the fly
 // in the plane pass from the per-axis factors (2 pi / L_a)^2 (no N_g table).

@@ -5,12 +5,8 @@
 namespace ace {
 namespace {
 
-// Lanes per line: four, which leaves 60 to 126 registers per lane and so two
-// (FP64) to six (FP32) waves on a SIMD.
-template <int N, typename R>
-constexpr int kSplitT = 4;
 // Waves per SIMD that the registers are budgeted for (the most that needs no
-// spills).
+// spills; four lanes per line leave 60 to 126 registers to a lane).
 template <int N, typename R>
 constexpr int kSplitWaves = sizeof(R) == 4 ? 4 : N >= 64 ? 2 : 3;
 
@@ -24,21 +20,19 @@ int run_length(int n, int np, int most) {
 template <int N, typename R>
 ace_status slab_n(ace_ctx c, const cx<R>* phi, const cx<R>* psi, cx<R>* buf, int mode, int i0,
                   int A, int j0, long p0, int np) {
-  constexpr int T = kSplitT<N, R>;
   const int run = run_length(N, np, kSlabRun);
   const long runs = (np + run - 1) / run;
-  return launch(c, "pair_fwd_slab", k_slab_split<N, R, T, kSplitWaves<N, R>>,
-                dim3(xcd_pad(N * runs)), dim3(kSplitThreads<N, T>), 0, phi, psi, buf, mode, i0, A,
+  return launch(c, "pair_fwd_slab", k_slab_split<N, R, kSplitWaves<N, R>>,
+                dim3(xcd_pad(N * runs)), dim3(kSplitThreads<N>), 0, phi, psi, buf, mode, i0, A,
                 j0, p0, np, run);
 }
 
 template <int N, typename R>
 ace_status plane_n(ace_ctx c, cx<R>* buf, const ace_kspec& ks, int np) {
-  constexpr int T = kSplitT<N, R>;
   const int run = run_length(N, np, kPlaneRun);
   const long runs = (np + run - 1) / run;
-  return launch(c, "plane_kernel", k_plane_split<N, R, T, kSplitWaves<N, R>>,
-                dim3(xcd_pad(N * runs)), dim3(kSplitThreads<N, T>), 0, buf, ks, np, run);
+  return launch(c, "plane_kernel", k_plane_split<N, R, kSplitWaves<N, R>>,
+                dim3(xcd_pad(N * runs)), dim3(kSplitThreads<N>), 0, buf, ks, np, run);
 }
 
 }  // namespace

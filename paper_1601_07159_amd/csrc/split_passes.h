@@ -18,21 +18,21 @@
 namespace ace {
 namespace {
 
-// One N x N plane per workgroup, T lanes per line; LDS rows an odd number of
+// One N x N plane per workgroup, four lanes per line; LDS rows an odd number of
 // elements apart (rows at one offset fall into different banks).
-template <int N, int T>
-constexpr int kSplitThreads = (N * T + 63) / 64 * 64;
+template <int N>
+constexpr int kSplitThreads = (N * 4 + 63) / 64 * 64;
 template <int N>
 constexpr int kSplitLd = N + 1 - (N & 1);
 
 // Line l and part h of a thread.  Threads past the last line repeat it and
 // store nothing (live).
-template <int N, int T>
+template <int N>
 struct SplitLane {
   int l, h;
   bool live;
   __device__ __forceinline__ explicit SplitLane(int t) {
-    constexpr int LPW = 64 / T;  // lines per wave
+    constexpr int LPW = 16;  // lines per wave
     const int line = (t >> 6) * LPW + (t & (LPW - 1));
     h = (t & 63) / LPW;
     live = N % LPW == 0 || line < N;
@@ -65,17 +65,17 @@ struct LaneBlock {
 
 // Position of register r of part h = fixed part of r + lane part of h (the
 // registers past the last whole group have a lane part of their own).
-template <int N, int T>
+template <int N>
 struct SplitLanePos {
   int grouped, rest;
   __device__ __forceinline__ SplitLanePos(int h, int stride, int base)
       : grouped(base + h * stride),
-        rest(base + N / T * (T == 4 ? ((h >> 1) | ((h & 1) << 1)) : 0) * stride) {}
+        rest(base + N / 4 * ((h >> 1) | ((h & 1) << 1)) * stride) {}
   __device__ __forceinline__ int lane(int r) const {
-    return r < Split<N, T>::kGrouped ? grouped : rest;
+    return r < Split<N>::kGrouped ? grouped : rest;
   }
   __device__ static constexpr int fixed(int r) {
-    return T == 1 || r >= Split<N, T>::kGrouped ? r : r - r % T + N / T * (r % T);
+    return r >= Split<N>::kGrouped ? r : r - r % 4 + N / 4 * (r % 4);
   }
 };
 
@@ -97,9 +97,9 @@ __global__ __launch_bounds__(256) void k_orbital_transpose(const V* __restrict__
 
 // The twiddle tables (both signs) into LDS, visible after the workgroup's next
 // barrier.
-template <int N, int T, typename R>
+template <int N, typename R>
 __device__ __forceinline__ void split_tw_stage(cx<R>* s) {
-  for (int e = threadIdx.x; e < 2 * N; e += blockDim.x) s[e] = kSplitRoots<N, T, R>.w[0][e];
+  for (int e = threadIdx.x; e < 2 * N; e += blockDim.x) s[e] = kSplitRoots<N, R>.w[0][e];
 }
 
 // Pairs of one slab that a workgroup takes in a row: the twiddles, and the
@@ -112,17 +112,17 @@ __device__ __forceinline__ void split_tw_stage(cx<R>* s) {
 // 1,353 pairs: one thread per line 0.47 -> 0.34 ms (4.1 TB/s).
 constexpr int kSlabRun = 8;  // at most (`run`)
 
-template <int N, typename R, int T, int WPE>
-__global__ __launch_bounds__((kSplitThreads<N, T>)) __attribute__((amdgpu_waves_per_eu(WPE))) void
+template <int N, typename R, int WPE>
+__global__ __launch_bounds__(kSplitThreads<N>) __attribute__((amdgpu_waves_per_eu(WPE))) void
 k_slab_split(const cx<R>* __restrict__ phi, const cx<R>* __restrict__ psi, cx<R>* __restrict__ buf,
              int mode, int i0, int A, int j0, long p0, int npairs, int run) {
-  constexpr int NN = N * N, LD = kSplitLd<N>, M = N / T;
+  constexpr int NN = N * N, LD = kSplitLd<N>, M = N / 4;
   __shared__ cx<R> s[N * LD];
   __shared__ cx<R> s_tw[2 * N];
   const int nruns = (npairs + run - 1) / run;
   const long lid = xcd_logical(blockIdx.x, gridDim.x);
   if (lid >= (long)N * nruns) return;
-  const SplitLane<N, T> ln((int)threadIdx.x);
+  const SplitLane<N> ln((int)threadIdx.x);
   const int l = ln.l, h = ln.h;
   const int x0 = (int)(lid / nruns);
   int p = (int)(lid - (long)x0 * nruns) * run;
@@ -130,14 +130,14 @@ k_slab_split(const cx<R>* __restrict__ phi, const cx<R>* __restrict__ psi, cx<R>
   int i, j;
   pair_of(mode, i0, A, j0, p0, p, &i, &j);
   const int ibeg = mode == 3 ? 0 : i0;
-  split_tw_stage<N, T, R>(s_tw);
-  const SplitTw<N, T, R> tw(h, s_tw);
-  const SplitLanePos<N, T> row(h, LD, l), col(h, N, l);
+  split_tw_stage<N, R>(s_tw);
+  const SplitTw<N, R> tw(h, s_tw);
+  const SplitLanePos<N> row(h, LD, l), col(h, N, l);
   cx<R> va[M], vb[M];
   auto load = [&](cx<R> (&x)[M], const cx<R>* f, int orb) {
     const LaneBlock<R> b(f + ((size_t)orb * N + x0) * NN);
 #pragma unroll
-    for (int m = 0; m < M; ++m) x[m] = b.load(h * N + l, T * m * N);
+    for (int m = 0; m < M; ++m) x[m] = b.load(h * N + l, 4 * m * N);
   };
   load(vb, psi, j);
   __syncthreads();
@@ -159,14 +159,14 @@ k_slab_split(const cx<R>* __restrict__ phi, const cx<R>* __restrict__ psi, cx<R>
         ++i;
       }
         }
-    fft_split<N, T, -1, TwRound::kIm>(v, h, tw);  // axis 2 of column l = x1
+    fft_split<N, -1, TwRound::kIm>(v, h, tw);  // axis 2 of column l = x1
     if (!first) __syncthreads();       // the rows of the pair before are read
 #pragma unroll
     for (int r = 0; r < M; ++r) s[row.lane(r) + LD * row.fixed(r)] = v[r];
     __syncthreads();
 #pragma unroll
-    for (int m = 0; m < M; ++m) v[m] = s[l * LD + h + T * m];
-    fft_split<N, T, -1, TwRound::kImSums>(v, h, tw);  // axis 1 of row l = k2
+    for (int m = 0; m < M; ++m) v[m] = s[l * LD + h + 4 * m];
+    fft_split<N, -1, TwRound::kImSums>(v, h, tw);  // axis 1 of row l = k2
     if (ln.live) {
 #pragma unroll
       for (int r = 0; r < M; ++r)
@@ -190,54 +190,54 @@ constexpr int kPlaneRun = 4;  // at most (`run`)
 template <int N, typename R>
 constexpr bool kPlaneDif = N <= 64;
 
-template <int N, typename R, int T, int WPE>
-__global__ __launch_bounds__((kSplitThreads<N, T>)) __attribute__((amdgpu_waves_per_eu(WPE))) void
+template <int N, typename R, int WPE>
+__global__ __launch_bounds__(kSplitThreads<N>) __attribute__((amdgpu_waves_per_eu(WPE))) void
 k_plane_split(cx<R>* __restrict__ buf, ace_kspec ks, int npairs, int run) {
-  constexpr int NN = N * N, LD = kSplitLd<N>, M = N / T;
+  constexpr int NN = N * N, LD = kSplitLd<N>, M = N / 4;
   __shared__ cx<R> s[N * LD];
   __shared__ cx<R> s_tw[2 * N];
   const int nruns = (npairs + run - 1) / run;
   const long lid = xcd_logical(blockIdx.x, gridDim.x);
   if (lid >= (long)N * nruns) return;
-  const SplitLane<N, T> ln((int)threadIdx.x);
+  const SplitLane<N> ln((int)threadIdx.x);
   const int l = ln.l, h = ln.h;
   int p = (int)(lid / N) * run;
   const int k1 = (int)(lid % N);
   const int pend = p + run < npairs ? p + run : npairs;
-  split_tw_stage<N, T, R>(s_tw);
-  const SplitTw<N, T, R> tw(h, s_tw);
-  const SplitLanePos<N, T> row(h, 1, l * LD);
+  split_tw_stage<N, R>(s_tw);
+  const SplitTw<N, R> tw(h, s_tw);
+  const SplitLanePos<N> row(h, 1, l * LD);
   R kk[M];
   {
     const KEval<R> ke(ks);
     const R s12 = ke.part12(k1, l);
 #pragma unroll
-    for (int r = 0; r < M; ++r) kk[r] = ke.at(split_pos<N, T>(r, h), s12);
+    for (int r = 0; r < M; ++r) kk[r] = ke.at(split_pos<N>(r, h), s12);
   }
   __syncthreads();
   for (bool first = true;; first = false) {
     const LaneBlock<R> plane(buf + (size_t)p * N * NN + (size_t)k1 * N);
     cx<R> v[M];
 #pragma unroll
-    for (int m = 0; m < M; ++m) v[m] = plane.load(h * NN + l, T * m * NN);
+    for (int m = 0; m < M; ++m) v[m] = plane.load(h * NN + l, 4 * m * NN);
     const bool more = ++p < pend;
-    fft_split<N, T, -1, TwRound::kIm>(v, h, tw);  // axis 0 of column l = k2
+    fft_split<N, -1, TwRound::kIm>(v, h, tw);  // axis 0 of column l = k2
 #pragma unroll
     for (int r = 0; r < M; ++r) {
       v[r].x *= kk[r];
       v[r].y *= kk[r];
       keep_rounded(v[r]);
     }
-    fft_unsplit<N, T, +1, TwRound::kIm>(v, h, tw);
+    fft_unsplit<N, +1, TwRound::kIm>(v, h, tw);
     if (!first) __syncthreads();  // the planes of the pair before are stored
 #pragma unroll
-    for (int m = 0; m < M; ++m) s[(h + T * m) * LD + l] = v[m];
+    for (int m = 0; m < M; ++m) s[(h + 4 * m) * LD + l] = v[m];
     __syncthreads();
     // axis 2 of row l = x0, read and rewritten by its own lanes only
     if constexpr (kPlaneDif<N, R>) {
 #pragma unroll
-      for (int m = 0; m < M; ++m) v[m] = s[l * LD + h + T * m];
-      fft_split<N, T, +1, TwRound::kImSums>(v, h, tw);
+      for (int m = 0; m < M; ++m) v[m] = s[l * LD + h + 4 * m];
+      fft_split<N, +1, TwRound::kImSums>(v, h, tw);
       if (ln.live) {
 #pragma unroll
         for (int r = 0; r < M; ++r) s[row.lane(r) + row.fixed(r)] = v[r];
@@ -245,17 +245,17 @@ k_plane_split(cx<R>* __restrict__ buf, ace_kspec ks, int npairs, int run) {
     } else {
 #pragma unroll
       for (int r = 0; r < M; ++r) v[r] = s[row.lane(r) + row.fixed(r)];
-      fft_unsplit<N, T, +1, TwRound::kRe>(v, h, tw);
+      fft_unsplit<N, +1, TwRound::kRe>(v, h, tw);
       if (ln.live) {
 #pragma unroll
-        for (int m = 0; m < M; ++m) s[l * LD + h + T * m] = v[m];
+        for (int m = 0; m < M; ++m) s[l * LD + h + 4 * m] = v[m];
       }
     }
     __syncthreads();
     if (ln.live) {
 #pragma unroll
       for (int m = 0; m < M; ++m)
-        plane.template store<false>(h * NN + l, T * m * NN, s[(h + T * m) * LD + l]);
+        plane.template store<false>(h * NN + l, 4 * m * NN, s[(h + 4 * m) * LD + l]);
     }
     if (!more) break;  // uniform
   }
