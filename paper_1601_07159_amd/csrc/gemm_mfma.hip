@@ -856,8 +856,10 @@ __global__ __launch_bounds__(512) void k_nn_mfma_res(const cx<TIn>* __restrict__
 // the time; the former kernel staged C again for every 64 rows and multiplied
 // four real products.  136 columns x 64^3 rows of FP32, triangular: 728 -> 334
 // us; 256 x 72^3: 2,008 -> 1,357 us (53 TFLOP/s of real products); 80 x 48^3:
-// 97 -> 68 us.
-constexpr int kSliceElems = 9728;  // 152 KiB of LDS
+// 97 -> 68 us.  In FP32 (MFMAs busy 74 %) against all of C resident in every
+// workgroup: 80 x 80 x 48^3 77 -> 68 us, 96 x 96 x 32^3 40 -> 31 us, 256 x 256 x
+// 72^3 1.28 ms both.
+constexpr int kSliceBytes = 152 * 1024;  // of LDS
 constexpr int kSliceBlocks = 5;    // 16-column blocks: 120 accumulator registers
 constexpr int kMaxSlices = 32;
 struct NnSlices {
@@ -868,12 +870,15 @@ struct NnSlices {
 
 // XB tiles of 16 grid rows at a time: narrow slices take several, so that the
 // loads of three steps ahead cover the memory latency.
-template <typename TIn, int NBB>
-__device__ __forceinline__ void nn_slice_body(double2* cs, const cx<TIn>* __restrict__ A, long lda,
+template <typename TIn, typename TAcc, int NBB>
+__device__ __forceinline__ void nn_slice_body(cx<TAcc>* cs, const cx<TIn>* __restrict__ A, long lda,
                                               int na, const cx<double>* __restrict__ C, int ldc,
                                               int b0, int nb, cx<TIn>* __restrict__ Y, long ldy,
                                               long K, int upper, int wg, int nwg) {
-  constexpr int W = 16 * NBB, XB = NBB == 1 ? 4 : NBB == 2 ? 2 : 1;
+  typedef typename Acc4<TAcc>::type acc_t;
+  constexpr int W = 16 * NBB;
+  constexpr int XB = (NBB == 1 ? 4 : NBB == 2 ? 2 : 1) *
+                     (sizeof(TAcc) == 4 && NBB > 1 && NBB < 5 ? 2 : 1);
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r16 = lane & 15, kq = lane >> 4;
@@ -881,10 +886,10 @@ __device__ __forceinline__ void nn_slice_body(double2* cs, const cx<TIn>* __rest
   const int groups = (rows + 15) / 16;  // of 16 orbitals: four MFMA steps
   for (int e = threadIdx.x; e < 16 * groups * W; e += 512) {
     const int bb = e / (16 * groups), aa = e - bb * (16 * groups);  // down the columns of C
-    double2 v = {0.0, 0.0};
+    cx<TAcc> v = {0, 0};
     if (aa < na && b0 + bb < nb) {
       const cx<double> cv = C[aa + (size_t)(b0 + bb) * ldc];
-      v = {cv.x, cv.y};
+      v = {(TAcc)cv.x, (TAcc)cv.y};
     }
     cs[aa * W + bb] = v;
   }
@@ -919,15 +924,15 @@ __device__ __forceinline__ void nn_slice_body(double2* cs, const cx<TIn>* __rest
 #pragma unroll
   for (int u = 0; u < 3; ++u) load(x[u], u);
   for (; tile < ntiles; tile += stride) {
-    v4d p1[XB][NBB], p2[XB][NBB], p3[XB][NBB];
+    acc_t p1[XB][NBB], p2[XB][NBB], p3[XB][NBB];
 #pragma unroll
     for (int q = 0; q < XB; ++q)
 #pragma unroll
-      for (int y = 0; y < NBB; ++y) p1[q][y] = p2[q][y] = p3[q][y] = v4d{0, 0, 0, 0};
-    double2 c[2][NBB];
-    auto loadc = [&](auto first, double2 (&cv)[NBB], int st) {
+      for (int y = 0; y < NBB; ++y) p1[q][y] = p2[q][y] = p3[q][y] = acc_t{0, 0, 0, 0};
+    cx<TAcc> c[2][NBB];
+    auto loadc = [&](auto first, cx<TAcc> (&cv)[NBB], int st) {
       constexpr int F = decltype(first)::value;
-      const double2* p = cs + (4 * st + kq) * W + r16;
+      const cx<TAcc>* p = cs + (4 * st + kq) * W + r16;
 #pragma unroll
       for (int y = F; y < NBB; ++y) cv[y] = p[16 * y];
     };
@@ -941,10 +946,10 @@ __device__ __forceinline__ void nn_slice_body(double2* cs, const cx<TIn>* __rest
         if (u < 3) loadc(first, c[(u + 1) & 1], 4 * g + u + 1);
 #pragma unroll
         for (int q = 0; q < XB; ++q) {
-          const double xr = (double)x[u][q].x, xi = (double)x[u][q].y, xs = xr + xi;
+          const TAcc xr = (TAcc)x[u][q].x, xi = (TAcc)x[u][q].y, xs = xr + xi;
 #pragma unroll
           for (int y = F; y < NBB; ++y) {
-            const double2 cv = c[u & 1][y];
+            const cx<TAcc> cv = c[u & 1][y];
             p1[q][y] = mfma4(cv.x, xr, p1[q][y]);
             p2[q][y] = mfma4(cv.y, xi, p2[q][y]);
             p3[q][y] = mfma4(cv.x + cv.y, xs, p3[q][y]);
@@ -971,7 +976,7 @@ __device__ __forceinline__ void nn_slice_body(double2* cs, const cx<TIn>* __rest
       for (int y = 0; y < NBB; ++y)
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-          const int b = b0 + 16 * y + mfma_row<double>(lane, v);
+          const int b = b0 + 16 * y + mfma_row<TAcc>(lane, v);
           if (b < nb && in)
             Y[(size_t)b * ldy + row[q]] = {(TIn)(p1[q][y][v] - p2[q][y][v]),
                                            (TIn)(p3[q][y][v] - p1[q][y][v] - p2[q][y][v])};
@@ -982,18 +987,18 @@ __device__ __forceinline__ void nn_slice_body(double2* cs, const cx<TIn>* __rest
   }
 }
 
-template <typename TIn>
-__global__ __launch_bounds__(512) void k_nn_f64(const cx<TIn>* __restrict__ A, long lda, int na,
+template <typename TIn, typename TAcc>
+__global__ __launch_bounds__(512) void k_nn_slices(const cx<TIn>* __restrict__ A, long lda, int na,
                                                 const cx<double>* __restrict__ C, int ldc,
                                                 cx<TIn>* __restrict__ Y, long ldy, long K,
                                                 int upper, NnSlices sl) {
-  __shared__ double2 cs[kSliceElems];
+  __shared__ __align__(16) cx<TAcc> cs[kSliceBytes / sizeof(cx<TAcc>)];
   int q = 0;
   while (q + 1 < sl.n && (int)blockIdx.x >= sl.wg0[q + 1]) ++q;
   const int wg = (int)blockIdx.x - sl.wg0[q], nwg = sl.wg0[q + 1] - sl.wg0[q];
   const int b0 = sl.b0[q], nb = sl.b0[q + 1];
 #define ACE_BODY(NBBV)                                                                     \
-  nn_slice_body<TIn, NBBV>(cs, A, lda, na, C, ldc, b0, nb, Y, ldy, K, upper, wg, nwg)
+  nn_slice_body<TIn, TAcc, NBBV>(cs, A, lda, na, C, ldc, b0, nb, Y, ldy, K, upper, wg, nwg)
   switch ((nb - b0 + 15) / 16) {
     case 1: ACE_BODY(1); break;
     case 2: ACE_BODY(2); break;
@@ -1009,7 +1014,9 @@ __global__ __launch_bounds__(512) void k_nn_f64(const cx<TIn>* __restrict__ A, l
 // Column slices of an expansion product in FP64 and the workgroups of each;
 // false when n_a is too large for a slice of 16 columns in LDS or the slices
 // are too many.
-static bool nn_slices(int na, int nb, long K, bool upper, NnSlices* s, unsigned* grid) {
+static bool nn_slices(int na, int nb, long K, size_t acc_bytes, bool upper, NnSlices* s,
+                      unsigned* grid) {
+  const int elems = kSliceBytes / (int)acc_bytes;
   double work[kMaxSlices], total = 0;
   s->n = 0;
   for (int b0 = 0; b0 < nb;) {
@@ -1020,7 +1027,7 @@ static bool nn_slices(int na, int nb, long K, bool upper, NnSlices* s, unsigned*
       const int rows = upper && b0 + 16 * blocks < na ? b0 + 16 * blocks : na;
       return (rows + 15) / 16;
     };
-    while (w > 0 && 256 * groups(w) * w > kSliceElems) --w;
+    while (w > 0 && 256 * groups(w) * w > elems) --w;
     if (w == 0) return false;
     const int even = (left + w - 1) / w;  // slices still to come, of like widths
     w = (left + even - 1) / even;
@@ -1272,16 +1279,17 @@ template <typename TIn, typename TAcc>
 static ace_status nn_dispatch(ace_ctx c, const char* name, const cx<TIn>* A, long lda, int na,
                               const cx<double>* C, int ldc, int nb, cx<TIn>* Y, long ldy,
                               long K, bool c_upper) {
-  // In FP64 slices of C in LDS, up to 608 orbitals and 32 slices; past that C is
-  // staged chunk by chunk.  Up to 16 columns, and up to 32 of a short product,
-  // keep the other forms, whose workgroups are smaller and whose loads run
-  // further ahead: 64 orbitals and 8 columns at 24^3 23 against 32 us, 128 and 8
-  // at 32^3 45 against 55 us, 4 and 4 at 48^3 32.4 against 33.3 us (whole calls).
-  if constexpr (sizeof(TAcc) == 8) {
+  // Slices of C in LDS, up to 608 orbitals (1,216 in FP32) and 32 slices; past
+  // that C is staged chunk by chunk.  Up to 16 columns, and up to 32 of a short
+  // product, keep the other forms, whose workgroups are smaller and whose loads
+  // run further ahead: in FP64 64 orbitals and 8 columns at 24^3 23 against 32
+  // us, 128 and 8 at 32^3 45 against 55 us, 4 and 4 at 48^3 32.4 against 33.3 us
+  // (whole calls).
+  {
     NnSlices sl;
     unsigned grid;
-    if ((nb > 32 || (nb > 16 && K > 65536)) && nn_slices(na, nb, K, c_upper, &sl, &grid))
-      return launch(c, name, k_nn_f64<TIn>, dim3(grid), dim3(512), 0, A, lda, na, C, ldc, Y, ldy,
+    if ((nb > 32 || (nb > 16 && K > 65536)) && nn_slices(na, nb, K, sizeof(cx<TAcc>), c_upper, &sl, &grid))
+      return launch(c, name, k_nn_slices<TIn, TAcc>, dim3(grid), dim3(512), 0, A, lda, na, C, ldc, Y, ldy,
                     K, c_upper ? 1 : 0, sl);
   }
   const int nbb = nb <= 16 ? 1 : nb <= 32 ? 2 : nb <= 48 ? 3 : nb <= 80 && nb > 64 ? 5 : 4;
@@ -1300,9 +1308,9 @@ static ace_status nn_dispatch(ace_ctx c, const char* name, const cx<TIn>* A, lon
   }
 #define ACE_NN(NBBV)                                                                           \
   case NBBV: {                                                                                 \
-    if constexpr (sizeof(TAcc) == 4 || NBBV <= 2) {                                            \
+    if constexpr (NBBV <= 2) {                                                                 \
       if (resident) ACE_NN_RES(NBBV, kNnResA)                                                  \
-      if constexpr (sizeof(TAcc) == 4 && NBBV <= 4)                                            \
+      if constexpr (sizeof(TAcc) == 4)                                                         \
         if (resident2) ACE_NN_RES(NBBV, kNnResA2)                                              \
     }                                                                                          \
     const long rows = NnShape<TAcc>::ROWS;                                                    \
@@ -1325,9 +1333,12 @@ static ace_status nn_dispatch(ace_ctx c, const char* name, const cx<TIn>* A, lon
 template <typename T>
 ace_status gemm_nn(ace_ctx c, const cx<T>* A, long lda, int na, const cx<double>* C, int ldc,
                    int nb, cx<T>* Y, long ldy, long K, bool fp64_accumulate, bool c_upper) {
-  if (fp64_accumulate || std::is_same<T, double>::value)
+  if constexpr (std::is_same<T, double>::value)
     return nn_dispatch<T, double>(c, "nn_mfma_f64", A, lda, na, C, ldc, nb, Y, ldy, K, c_upper);
-  return nn_dispatch<T, float>(c, "nn_mfma_f32", A, lda, na, C, ldc, nb, Y, ldy, K, c_upper);
+  else if (fp64_accumulate)
+    return nn_dispatch<T, double>(c, "nn_mfma_f64", A, lda, na, C, ldc, nb, Y, ldy, K, c_upper);
+  else
+    return nn_dispatch<T, float>(c, "nn_mfma_f32", A, lda, na, C, ldc, nb, Y, ldy, K, c_upper);
 }
 
 template ace_status gemm_cn<float>(ace_ctx, const cx<float>*, long, int, const cx<float>*, long,
