@@ -1118,6 +1118,19 @@ static bool gram_shape(int na, int nb, long K, size_t data_bytes, bool same, boo
   s->herm = herm;
   s->same = same;
   s->gx = (total + 8 * kGramBlocks - 1) / (8 * kGramBlocks);
+  if (!herm) {
+    // The allocation-free apply holds 48 MiB for the matrix and the partials:
+    // more workgroup rows, and so fewer partials, where they would not fit (256 x
+    // 256 in FP64: 42 partials of six rows instead of 64 of four).
+    const size_t entry = (size_t)na * nb;
+    const int max_waves = data_bytes == sizeof(cx<double>) ? 8 : 16;
+    const CnShape tiles = cn_shape(na, nb, K, max_waves, max_waves == 8 ? 12 : 16);
+    const size_t mat = entry * sizeof(cx<double>), room = (size_t)47 << 20;
+    const size_t cap =
+        std::max((size_t)tiles.ks * entry * data_bytes, room > mat ? room - mat : (size_t)0);
+    while (s->gx < 256 && 256 / s->gx * entry * data_bytes > cap) ++s->gx;
+    s->gx = std::min(s->gx, total);
+  }
   s->per = (total + s->gx - 1) / s->gx;
   // rows of the workgroup with the most of them
   int rows = 0;

@@ -28,8 +28,8 @@ ace_status apply_entry(ace_ctx c, const ace_grid* grid, ace_prec prec, const voi
 namespace {
 
 // 48 MiB: n_band x n_x up to 256 x 256 at any grid of the library in every
-// precision (partials of at most 64 K chunks in FP32 or 32 in FP64, plus the
-// 1 MiB matrix).
+// precision (partials of at most 64 K chunks at that size in FP32 or 42 in FP64,
+// plus the 1 MiB matrix; smaller sizes split K further, within 47 MiB).
 constexpr size_t kScratchBytes = (size_t)48 << 20;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 

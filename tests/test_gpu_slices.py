@@ -126,3 +126,30 @@ def test_apply_products_fp32(prec, n, nb, nx):
     # FP32 rounding of the inputs and of chains of at most 256 products:
     # sqrt(256) 6e-8 = 1e-6 of the whole, twice that
     assert np.linalg.norm(Y - ref) <= 2e-6 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("prec,nb,nx", [("fp64", 256, 256), ("fp64", 128, 128), ("fp64", 200, 120),
+                                        ("fp32", 256, 256), ("real64", 256, 256)])
+def test_noalloc_sizes(prec, nb, nx):
+    """The allocation-free apply takes every size up to 256 x 256 and gives what
+    apply gives, bit for bit (the grid is large enough for the full K split)."""
+    import ctypes
+    import torch
+    from paper_1601_07159_amd import _lib, ace
+    n = 24
+    print(f"allocation-free apply prec={prec} nb={nb} nx={nx}", flush=True)
+    gg = ggrid(n, 0.43 * n)
+    dt = {"fp64": torch.complex128, "fp32": torch.complex64, "real64": torch.float64}[prec]
+    gen = torch.Generator(device="cuda").manual_seed(nb)
+    xi = torch.randn(nb, n ** 3, dtype=dt, device="cuda", generator=gen)
+    X = torch.randn(nx, n ** 3, dtype=dt, device="cuda", generator=gen)
+    Y = torch.full_like(X, float("nan"))
+    ctx = ace.Context()
+    g = gg.as_c()
+    ctx._bind_stream()
+    st = _lib.load().ace_apply_noalloc(
+        ctx._h, ctypes.byref(g), ace._prec(prec), ctypes.c_void_p(xi.data_ptr()), nb, xi.stride(0),
+        ctypes.c_void_p(X.data_ptr()), nx, X.stride(0), ctypes.c_void_p(Y.data_ptr()), Y.stride(0))
+    assert st == 0
+    assert torch.equal(Y, ctx.apply(xi, X, gg, prec))
+    ctx.close()
