@@ -87,3 +87,42 @@ def test_captured_without_room_for_copies():
     del graph
     ctx.close()
     ref.close()
+
+
+@pytest.mark.parametrize("n,prec,nocc,nband", [(48, "fp64", 12, 14), (72, "fp32", 9, 11)])
+def test_captured_after_reserve(n, prec, nocc, nband):
+    import torch
+    from paper_1601_07159_amd import ace
+    print(f"split lines: captured after reserve n={n} prec={prec}", flush=True)
+    gg = ggrid(n, 0.43 * n)
+    x = to_gpu(synth.smooth_orbitals(n, 0.43 * n, nband, seed=6), prec)
+    own = x[:nocc].flip(0).contiguous()
+    ref, ctx = ace.Context(), ace.Context()
+    ctx.reserve(gg, prec, nocc, nband, nband)
+    Ws, Wo, e = torch.zeros_like(x), torch.zeros_like(x), torch.zeros((), dtype=torch.float64,
+                                                                      device="cuda")
+
+    def path(c, W1, W2, en):
+        c.build_W(x[:nocc], x, gg, prec, out=W1)
+        c.build_W(own, x, gg, prec, out=W2)
+        return c.exchange_energy(own, gg, prec, out=en)
+
+    path(ref, torch.zeros_like(x), torch.zeros_like(x), torch.zeros_like(e))
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        path(ctx, Ws, Wo, e)
+    for rep in range(3):
+        x.mul_(1.0 + 0.5 * rep)
+        own.mul_(1.0 - 0.25 * rep)
+        Ws.zero_(), Wo.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        W1, W2, en = torch.zeros_like(x), torch.zeros_like(x), torch.zeros_like(e)
+        path(ref, W1, W2, en)
+        torch.cuda.synchronize()
+        # the same kernels on the same data
+        assert torch.equal(Ws, W1) and torch.equal(Wo, W2) and torch.equal(e, en)
+    del graph
+    ctx.close()
+    ref.close()
