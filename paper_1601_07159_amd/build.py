@@ -5,7 +5,8 @@ python -m paper_1601_07159_amd.build   (or call build())
 build_host_checks() (also run by build()) compiles the same sources with the
 host code under AddressSanitizer and UndefinedBehaviorSanitizer (device code
 as usual) and links them with the C-ABI checks of tests/native/host_checks.cpp
-into tests/native/ace_host_checks.
+into tests/native/ace_host_checks, and with a stand-in for the HIP runtime
+(tests/native/plan_checks.hip) into tests/native/ace_plan_checks.
 """
 from __future__ import annotations
 
@@ -41,10 +42,12 @@ SAN_DIR = os.path.join(BUILD_DIR, "san")
 CLANG = os.environ.get("ACE_CLANG", "/opt/rocm/llvm/bin/clang++")
 CHECKS_SRC = os.path.join(ROOT, "tests", "native", "host_checks.cpp")
 CHECKS_OUT = os.path.join(ROOT, "tests", "native", "ace_host_checks")
+PLAN_SRC = os.path.join(ROOT, "tests", "native", "plan_checks.hip")
+PLAN_OUT = os.path.join(ROOT, "tests", "native", "ace_plan_checks")
 
 
 def _compile(src: str, out_dir: str = BUILD_DIR, extra=()) -> str:
-    obj = os.path.join(out_dir, os.path.splitext(src)[0] + ".o")
+    obj = os.path.join(out_dir, os.path.splitext(os.path.basename(src))[0] + ".o")
     cmd = [HIPCC, *FLAGS, *extra, "-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
@@ -59,12 +62,15 @@ def _run(cmd, what):
 
 
 def build_host_checks(verbose: bool = True, jobs: int = 0) -> str:
-    """The sanitized host-check program (host code of libace and the checks
-    under ASan + UBSan, device code unchanged)."""
+    """The sanitized check programs (host code of libace and the checks under
+    ASan + UBSan, device code unchanged): the C-ABI checks, and the plan checks,
+    which run without a GPU or the HIP runtime."""
     os.makedirs(SAN_DIR, exist_ok=True)
     jobs = jobs or min(len(SOURCES), max(1, int(os.environ.get("MAX_JOBS", os.cpu_count() or 4))))
     with cf.ThreadPoolExecutor(jobs) as ex:
+        plan = ex.submit(_compile, PLAN_SRC, SAN_DIR, SAN_HOST_FLAGS)
         objs = list(ex.map(lambda s: _compile(s, SAN_DIR, SAN_HOST_FLAGS), SOURCES))
+        plan_obj = plan.result()
     san = "-fsanitize=address,undefined"   # host-only compile and link lines (clang++, no HIP)
     drv = os.path.join(SAN_DIR, "host_checks.o")
     _run([CLANG, "-std=c++17", "-O1", "-g", "-fno-omit-frame-pointer", san,
@@ -74,6 +80,9 @@ def build_host_checks(verbose: bool = True, jobs: int = 0) -> str:
     _run([CLANG, san, "-o", tmp, drv, *objs, "-L/opt/rocm/lib", "-lamdhip64",
           "-Wl,-rpath,/opt/rocm/lib"], "host checks link")
     shutil.move(tmp, CHECKS_OUT)
+    tmp = PLAN_OUT + ".tmp"
+    _run([CLANG, san, "-o", tmp, plan_obj, *objs], "plan checks link")
+    shutil.move(tmp, PLAN_OUT)
     if verbose:
         print(f"built {CHECKS_OUT}", file=sys.stderr)
     return CHECKS_OUT

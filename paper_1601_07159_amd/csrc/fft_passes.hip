@@ -970,10 +970,10 @@ BuildPlan plan_build(ace_ctx c, const GridInfo& g, size_t eb, int nocc, int nban
   pl.B = B;
   pl.A = (int)std::max<long>(1, std::min<long>(nocc, maxpairs / B));
   pl.pairs_alloc = std::max<size_t>((size_t)pl.A * pl.B, (size_t)sym_alloc);
-  // transposed copies of psi, which holds phi too, or of both
+  // transposed copies: of the one array's orbitals, or of both arrays'
   pl.orb_bytes = slab_split_bytes(
       g, eb, pl.sym ? tri + (long)nocc * (nband - nocc) : (long)nocc * nband,
-      psi_starts_with_phi ? nband : (long)nocc + nband);
+      psi_starts_with_phi ? std::max(nocc, nband) : (long)nocc + nband);
   pl.bytes = align_up(pl.pairs_alloc * pair_bytes, 256) + pl.orb_bytes;
   return pl;
 }
@@ -1208,9 +1208,13 @@ ace_status build_W_n(ace_ctx c, const GridInfo& g, const cx<T>* phi, int nocc, l
   if (split) {
     cx<T>* orb = (cx<T>*)ws_take(c, pl.orb_bytes, &st);
     if (!orb) return st;
-    if ((st = orbital_transpose<cx<T>>(c, N, psi, ldpsi, nband, orb)) != ACE_OK) return st;
+    // one array for both: its orbitals up to the last that either takes
+    const bool one = psi == phi && ldpsi == ldphi;
+    if ((st = orbital_transpose<cx<T>>(c, N, psi, ldpsi, one ? std::max(nocc, nband) : nband,
+                                       orb)) != ACE_OK)
+      return st;
     psi_t = phi_t = orb;
-    if (!(psi == phi && ldpsi == ldphi)) {
+    if (!one) {
       phi_t = orb + (size_t)nband * g.ng;
       if ((st = orbital_transpose<cx<T>>(c, N, phi, ldphi, nocc, orb + (size_t)nband * g.ng)) !=
           ACE_OK)

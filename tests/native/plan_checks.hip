@@ -1,0 +1,289 @@
+// Checks of libace's host logic without a GPU: the library's objects (host code
+// under AddressSanitizer and UndefinedBehaviorSanitizer) are linked with the
+// stand-in for the HIP runtime below, which hands out addresses of a "device"
+// of a chosen size and shows every kernel launch to the check instead of
+// running it.  So the reads and writes that a launch's arguments imply can be
+// compared with the buffers, and allocations can be made to fail.
+//
+// Exit status: 0 when every check held, 1 otherwise.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <cstdio>
+#include <cstring>
+#include <functional>
+#include <map>
+#include <memory>
+#include <string>
+#include <vector>
+
+#include "../../paper_1601_07159_amd/csrc/ace_internal.h"
+
+// ---------------------------------------------------------------- HIP runtime
+namespace {
+
+struct Device {
+  size_t free_bytes = (size_t)1 << 40;
+  std::map<char*, size_t> live;
+  char* next = (char*)0x100000000000;
+  int mallocs = 0, refused = 0;
+  bool capturing = false;
+} dev;
+
+struct Launch {
+  std::string name;
+  dim3 grid, block;
+  void** args;
+  template <typename T>
+  T arg(int k) const {
+    return *(T*)args[k];
+  }
+  bool is(const char* kernel) const { return name.find(kernel) != std::string::npos; }
+};
+std::function<void(const Launch&)> on_launch;
+
+std::map<const void*, std::string>& kernel_names() {
+  static std::map<const void*, std::string> m;
+  return m;
+}
+struct {
+  dim3 grid, block;
+  size_t shmem;
+  hipStream_t stream;
+} call;
+
+}  // namespace
+
+extern "C" {
+void** __hipRegisterFatBinary(const void*) {
+  static void* h;
+  return &h;
+}
+void __hipUnregisterFatBinary(void**) {}
+void __hipRegisterVar(void**, void*, char*, const char*, int, size_t, int, int) {}
+void __hipRegisterFunction(void**, const void* host, char*, const char* name, unsigned, void*,
+                           void*, void*, void*, int*) {
+  kernel_names()[host] = name;
+}
+hipError_t __hipPushCallConfiguration(dim3 grid, dim3 block, size_t shmem, hipStream_t stream) {
+  call = {grid, block, shmem, stream};
+  return hipSuccess;
+}
+hipError_t __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* shmem, hipStream_t* stream) {
+  *grid = call.grid;
+  *block = call.block;
+  *shmem = call.shmem;
+  *stream = call.stream;
+  return hipSuccess;
+}
+hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, size_t, hipStream_t) {
+  if (on_launch) on_launch({kernel_names()[f], grid, block, args});
+  return hipSuccess;
+}
+hipError_t hipMalloc(void** p, size_t n) {
+  ++dev.mallocs;
+  if (n > dev.free_bytes) {
+    ++dev.refused;
+    *p = nullptr;
+    return hipErrorOutOfMemory;
+  }
+  dev.free_bytes -= n;
+  *p = dev.next;
+  dev.live[dev.next] = n;
+  dev.next += (n + 0x1ffff) / 0x10000 * 0x10000;
+  return hipSuccess;
+}
+hipError_t hipFree(void* p) {
+  if (!p) return hipSuccess;
+  const auto it = dev.live.find((char*)p);
+  if (it == dev.live.end()) return hipErrorInvalidValue;
+  dev.free_bytes += it->second;
+  dev.live.erase(it);
+  return hipSuccess;
+}
+hipError_t hipMemGetInfo(size_t* f, size_t* t) {
+  *f = dev.free_bytes;
+  *t = (size_t)1 << 40;
+  return hipSuccess;
+}
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* s) {
+  *s = dev.capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+  return hipSuccess;
+}
+hipError_t hipGetDevice(int* d) {
+  *d = 0;
+  return hipSuccess;
+}
+hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) {
+  *v = 256;
+  return hipSuccess;
+}
+hipError_t hipGetSymbolAddress(void** p, const void*) {
+  *p = (void*)0x200000000000;
+  return hipSuccess;
+}
+hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) {
+  *s = (hipStream_t)1;
+  return hipSuccess;
+}
+hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode) {
+  dev.capturing = true;
+  return hipSuccess;
+}
+hipError_t hipStreamEndCapture(hipStream_t, hipGraph_t* g) {
+  dev.capturing = false;
+  *g = (hipGraph_t)1;
+  return hipSuccess;
+}
+hipError_t hipGraphInstantiate(hipGraphExec_t* e, hipGraph_t, hipGraphNode_t*, char*, size_t) {
+  *e = (hipGraphExec_t)1;
+  return hipSuccess;
+}
+hipError_t hipEventCreate(hipEvent_t* e) {
+  *e = (hipEvent_t)1;
+  return hipSuccess;
+}
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { return hipEventCreate(e); }
+const char* hipGetErrorString(hipError_t) { return "error"; }
+hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
+hipError_t hipGraphDestroy(hipGraph_t) { return hipSuccess; }
+hipError_t hipGraphExecDestroy(hipGraphExec_t) { return hipSuccess; }
+hipError_t hipGraphLaunch(hipGraphExec_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) {
+  *ms = 1.f;
+  return hipSuccess;
+}
+hipError_t hipMemcpy(void*, const void*, size_t, hipMemcpyKind) { return hipSuccess; }
+hipError_t hipMemcpyAsync(void* d, const void*, size_t n, hipMemcpyKind k, hipStream_t) {
+  if (k == hipMemcpyDeviceToHost) std::memset(d, 0, n);
+  return hipSuccess;
+}
+hipError_t hipMemcpy2DAsync(void*, size_t, const void*, size_t, size_t, size_t, hipMemcpyKind,
+                            hipStream_t) {
+  return hipSuccess;
+}
+hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int* n, const void*, int, size_t) {
+  *n = 1;
+  return hipSuccess;
+}
+}  // extern "C"
+
+// --------------------------------------------------------------------- checks
+namespace {
+
+int g_checks = 0, g_failures = 0;
+std::string g_case;
+
+void expect(bool ok, const char* what, int line) {
+  ++g_checks;
+  if (!ok) {
+    ++g_failures;
+    std::printf("FAIL line %d: %s [%s]\n", line, what, g_case.c_str());
+  }
+}
+#define EXPECT(cond) expect((cond), #cond, __LINE__)
+
+ace_grid cubic(int n) {
+  ace_grid g{};
+  for (int a = 0; a < 3; ++a) {
+    g.n[a] = n;
+    g.L[a] = 0.43 * n;
+  }
+  g.kind = ACE_COULOMB;
+  return g;
+}
+
+// Caller's arrays, far apart.
+char* array_at(int k) { return (char*)0x400000000000 + (size_t)k * 0x10000000000; }
+
+size_t cx_bytes(ace_prec p) { return p == ACE_FP64 || p == ACE_REAL64 ? 16 : 8; }
+
+// Every value that the slab pass on split lines reads lies in the transposed
+// copies, which lie in the workspace.
+void slab_reads(ace_ctx c, size_t eb, int n, int* slabs) {
+  const long ng = (long)n * n * n;
+  auto copied = std::make_shared<std::vector<std::pair<char*, char*>>>();
+  on_launch = [=](const Launch& l) {
+    const char* end = (const char*)c->ws + c->ws_bytes;
+    if (l.is("k_orbital_transpose")) {
+      char* y = l.arg<char*>(2);
+      const size_t bytes = (size_t)l.grid.x / n * ng * eb;
+      EXPECT(y >= (char*)c->ws && y + bytes <= end);
+      copied->push_back({y, y + bytes});
+    }
+    if (!l.is("k_slab_split")) return;
+    ++*slabs;
+    const char* phi = l.arg<const char*>(0);
+    const char* psi = l.arg<const char*>(1);
+    const char* buf = l.arg<const char*>(2);
+    const int mode = l.arg<int>(3), i0 = l.arg<int>(4), A = l.arg<int>(5), j0 = l.arg<int>(6);
+    const long p0 = l.arg<long>(7);
+    const int np = l.arg<int>(8);
+    EXPECT(buf + (size_t)np * ng * eb <= end);
+    long imax = 0, jmax = 0, j = 0;
+    for (long p = 0; p < np; ++p) {
+      long i = i0 + p % A, jj = j0 + p / A;
+      const long tri = (long)A * (A + 1) / 2;
+      if (mode == 1 || (mode == 3 && p < tri)) {
+        const long q = p + p0;
+        while ((j + 1) * (j + 2) / 2 <= q) ++j;
+        i = i0 + q - j * (j + 1) / 2;
+        jj = (mode == 1 ? j0 : i0) + j;
+      } else if (mode == 3) {
+        i = (p - tri) % A;
+        jj = j0 + (p - tri) / A;
+      }
+      imax = std::max(imax, i);
+      jmax = std::max(jmax, jj);
+    }
+    bool phi_in = false, psi_in = false;
+    for (const auto& r : *copied) {
+      phi_in |= phi >= r.first && phi + (size_t)(imax + 1) * ng * eb <= r.second;
+      psi_in |= psi >= r.first && psi + (size_t)(jmax + 1) * ng * eb <= r.second;
+    }
+    EXPECT(phi_in);
+    EXPECT(psi_in);
+  };
+}
+
+// W = V_X[phi] psi with phi and psi one array (any n_band against n_occ).
+void shared_orbitals_on_split_lines() {
+  for (int n : {40, 72})
+    for (ace_prec prec : {ACE_FP64, ACE_FP32})
+      for (auto [nocc, nband] : {std::pair{20, 10}, {20, 19}, {20, 20}, {20, 24}, {33, 12}})
+        for (long symmetry : {0L, 1L})
+          for (long budget : {0L, 3L, 37L}) {
+            if (symmetry && nband < nocc) continue;
+            const ace_grid g = cubic(n);
+            const long ng = (long)n * n * n;
+            g_case = "n " + std::to_string(n) + " prec " + std::to_string(prec) + " nocc " +
+                     std::to_string(nocc) + " nband " + std::to_string(nband) + " symmetry " +
+                     std::to_string(symmetry) + " budget " + std::to_string(budget);
+            ace_ctx c = nullptr;
+            EXPECT(ace_create(&c, nullptr, nullptr) == ACE_OK);
+            ace_set_tuning(c, ACE_TUNE_SYMMETRY, symmetry);
+            ace_set_pair_budget(c, budget * ng * (long)cx_bytes(prec));
+            int slabs = 0;
+            slab_reads(c, cx_bytes(prec), n, &slabs);
+            EXPECT(ace_build_W(c, &g, prec, array_at(0), nocc, ng, array_at(0), nband, ng,
+                               array_at(1), ng, 1.0) == ACE_OK);
+            EXPECT(slabs > 0 || (prec == ACE_FP32 && n < 72));
+            on_launch = nullptr;
+            ace_destroy(c);
+          }
+}
+
+}  // namespace
+
+int main() {
+  setvbuf(stdout, nullptr, _IOLBF, 0);
+  shared_orbitals_on_split_lines();
+  std::printf("plan checks: %d checks, %d failures\n", g_checks, g_failures);
+  return g_failures ? 1 : 0;
+}
