@@ -368,7 +368,7 @@ ace_status ace_set_pair_budget(ace_ctx ctx, long bytes);
  *  ACE_TUNE_PAIR_BUDGET  same as ace_set_pair_budget (bytes; 0 = default)
  *  ACE_TUNE_JBLOCK       bands j per pair block of the build (0 = all)
  *  ACE_TUNE_SYMMETRY     1 (default): when psi's first n_occ orbitals are phi
- *                        (same pointer and ld), FFT only the pairs i <= j of the
+ *                        (same pointer and ld, n_band >= n_occ), FFT only the pairs i <= j of the
  *                        occupied block and use u_ji = conj(u_ij); 0: all pairs
  *  ACE_TUNE_FFT_SHAPE    line FFTs of the slab and plane passes: 1 one thread
  *                        per line, 4 a lane quad per line, 8 an octet of lanes

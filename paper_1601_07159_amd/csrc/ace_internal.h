@@ -174,6 +174,7 @@ size_t gemm_cn_scratch_bytes(int na, int nb, long K);
 
 // Blocking of the build: A occupied orbitals x B bands per pair block, or the
 // symmetric occupied triangle; `bytes` is the workspace the build takes.
+// one_array: phi and psi start at one address with one leading dimension.
 struct BuildPlan {
   int A, B;       // rectangle chunks: A orbitals x B bands
   bool sym;       // i <-> j symmetry on the occupied block
@@ -184,7 +185,7 @@ struct BuildPlan {
   size_t bytes;      // of everything
 };
 BuildPlan plan_build(ace_ctx c, const GridInfo& g, size_t elem_bytes, int nocc, int nband,
-                     bool psi_starts_with_phi);
+                     bool one_array);
 // Workspace of ace_apply_h for n_x vectors (exchange from n_xi projection
 // vectors or n_phi orbitals; 0 for none).
 size_t hamiltonian_ws_bytes(ace_ctx c, const GridInfo& g, size_t eb, int nx, int nxi, int nphi);
@@ -272,7 +273,7 @@ ace_status build_W_real_impl(ace_ctx c, const GridInfo& g, const T* phi, int noc
                              const T* psi, int nband, long ldpsi, T* W, long ldW, double scale,
                              const double* dscale = nullptr);
 BuildPlan plan_build_real(ace_ctx c, const GridInfo& g, size_t cx_bytes, int nocc, int nband,
-                          bool psi_starts_with_phi);
+                          bool one_array);
 
 // Argument checks shared by the entry points (api.hip).
 ace_status check_grid(ace_ctx c, const ace_grid* g, ace_prec prec, GridInfo* out);

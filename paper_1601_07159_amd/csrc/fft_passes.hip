@@ -912,7 +912,7 @@ size_t energy_direct_ws_bytes(ace_ctx c, const GridInfo& g, size_t eb, int nocc)
 }
 
 BuildPlan plan_build(ace_ctx c, const GridInfo& g, size_t eb, int nocc, int nband,
-                     bool psi_starts_with_phi) {
+                     bool one_array) {
   BuildPlan pl;
   const size_t pair_bytes = (size_t)g.ng * eb;
   // explicit knobs first, then an autotuned entry for this grid size, then defaults
@@ -929,14 +929,16 @@ BuildPlan plan_build(ace_ctx c, const GridInfo& g, size_t eb, int nocc, int nban
   // Band block B (all bands unless tuned otherwise): the accumulating pass runs
   // (N^2 / 64) * B one-wave workgroups, each looping over the i block, and W is
   // read-modified-written once per i block.
-  // Pair symmetry: when psi's first n_occ orbitals are phi, u_ji = conj(u_ij)
-  // on the occupied block and only its triangle i <= j needs FFTs.  When the
+  // Pair symmetry: when psi's first n_occ orbitals are phi (one array, at least
+  // n_occ bands), u_ji = conj(u_ij) on the occupied block and only its triangle
+  // i <= j needs FFTs.  (With fewer bands the bands would need pairs below the
+  // diagonal whose mirror images are not among theirs.)  When the
   // whole triangle fits the budget it is one chunk; otherwise the occupied
   // orbitals are split into blocks of b, and each block pair I <= J is one
   // chunk (the triangle of I for I = J, the rectangle I x J otherwise) whose
   // spectra serve the bands of J and, conjugated, those of I.
   const long tri = (long)nocc * (nocc + 1) / 2;
-  pl.sym = c->use_symmetry && psi_starts_with_phi && nocc >= 2;
+  pl.sym = c->use_symmetry && one_array && nband >= nocc && nocc >= 2;
   pl.symblk = 0;
   long sym_alloc = 0;
   pl.merged = false;
@@ -973,14 +975,15 @@ BuildPlan plan_build(ace_ctx c, const GridInfo& g, size_t eb, int nocc, int nban
   // transposed copies: of the one array's orbitals, or of both arrays'
   pl.orb_bytes = slab_split_bytes(
       g, eb, pl.sym ? tri + (long)nocc * (nband - nocc) : (long)nocc * nband,
-      psi_starts_with_phi ? std::max(nocc, nband) : (long)nocc + nband);
+      one_array ? std::max(nocc, nband) : (long)nocc + nband);
   pl.bytes = align_up(pl.pairs_alloc * pair_bytes, 256) + pl.orb_bytes;
   return pl;
 }
 
 // Real orbitals: units of two pairs; A orbitals (even unless all of them) x B
 // bands per chunk, Am = ceil(A / 2) units per band.
-// Real orbitals with psi's first n_occ orbitals equal to phi: u_ij = u_ji on
+// Real orbitals with psi's first n_occ orbitals equal to phi (one array, at
+// least n_occ bands): u_ij = u_ji on
 // the occupied block, so only pairs i <= j are transformed.  Column c of the
 // triangle packs rows (2m, 2m + 1), 2m <= c, into unit real_tri_units(c) + m
 // (row 2m + 1 absent when it exceeds c); the extra bands follow as rectangle
@@ -988,7 +991,7 @@ BuildPlan plan_build(ace_ctx c, const GridInfo& g, size_t eb, int nocc, int nban
 // Used when all units fit the pair budget (one chunk); otherwise the rectangle
 // chunks below.
 BuildPlan plan_build_real(ace_ctx c, const GridInfo& g, size_t cx_bytes, int nocc, int nband,
-                          bool psi_starts_with_phi) {
+                          bool one_array) {
   BuildPlan pl;
   const size_t unit_bytes = (size_t)g.ng * cx_bytes;
   size_t budget = c->pair_budget;
@@ -1000,7 +1003,7 @@ BuildPlan plan_build_real(ace_ctx c, const GridInfo& g, size_t cx_bytes, int noc
   pl.merged = false;
   pl.orb_bytes = 0;
   const long sym_units = real_tri_units(nocc) + (long)((nocc + 1) / 2) * (nband - nocc);
-  if (c->use_symmetry && psi_starts_with_phi && nocc >= 2 && jblock == 0 &&
+  if (c->use_symmetry && one_array && nband >= nocc && nocc >= 2 && jblock == 0 &&
       sym_units <= maxunits) {
     pl.sym = true;
     pl.merged = true;

@@ -17,7 +17,9 @@
 #include <string>
 #include <vector>
 
-#include "../../paper_1601_07159_amd/csrc/ace_internal.h"
+#include "../../paper_1601_07159_amd/csrc/pass_bodies.h"
+
+using ace::real_tri_units;
 
 // ---------------------------------------------------------------- HIP runtime
 namespace {
@@ -259,7 +261,6 @@ void shared_orbitals_on_split_lines() {
       for (auto [nocc, nband] : {std::pair{20, 10}, {20, 19}, {20, 20}, {20, 24}, {33, 12}})
         for (long symmetry : {0L, 1L})
           for (long budget : {0L, 3L, 37L}) {
-            if (symmetry && nband < nocc) continue;
             const ace_grid g = cubic(n);
             const long ng = (long)n * n * n;
             g_case = "n " + std::to_string(n) + " prec " + std::to_string(prec) + " nocc " +
@@ -279,11 +280,68 @@ void shared_orbitals_on_split_lines() {
           }
 }
 
+// Every spectrum that the accumulate pass reads was written by the slab pass
+// before it, and it writes the bands of W only.
+void spectra_reads(int nband, int* accums) {
+  auto pairs = std::make_shared<long>(0);
+  on_launch = [=](const Launch& l) {
+    if (l.is("k_slab_split")) *pairs = l.arg<int>(8);
+    if (l.is("k_pair_fwd_slab")) *pairs = l.arg<int>(10);
+    if (l.is("k_pair_fwd_real")) *pairs = l.arg<int>(9);
+    if (!l.is("k_pencil_accum")) return;
+    ++*accums;
+    long read = 0;  // one past the last pair
+    if (l.is("k_pencil_accum_real_sym")) {
+      const long A = l.arg<int>(5), extra = l.arg<int>(6) - (A + 1) / 2;
+      read = real_tri_units((int)A) + (A + 1) / 2 * extra;
+      EXPECT(extra >= 0 && A + extra <= nband);
+    } else if (l.is("k_pencil_accum_real")) {
+      read = (long)l.arg<int>(7) * l.arg<int>(9);
+      EXPECT(l.arg<int>(8) + l.arg<int>(9) <= nband);
+    } else {
+      const long A = l.arg<int>(6), nbc = l.arg<int>(8);
+      const int mode = l.arg<int>(10);
+      const long tri = A * (A + 1) / 2;
+      read = mode == 1 ? tri : mode == 3 ? tri + A * std::max(0L, nbc - A) : A * nbc;
+      EXPECT(l.arg<int>(7) + nbc <= nband);
+    }
+    EXPECT(read <= *pairs);
+  };
+}
+
+// One array for phi and psi, fewer bands than orbitals, with pair symmetry.
+void fewer_bands_than_orbitals() {
+  for (int n : {16, 48})
+    for (ace_prec prec : {ACE_FP64, ACE_FP32, ACE_REAL64, ACE_REAL32})
+      for (auto [nocc, nband] : {std::pair{2, 1}, {17, 16}, {17, 2}, {20, 10}, {9, 9}, {9, 12}})
+        for (long budget : {0L, 2L, 5L, 60L}) {
+          const ace_grid g = cubic(n);
+          const long ng = (long)n * n * n;
+          g_case = "n " + std::to_string(n) + " prec " + std::to_string(prec) + " nocc " +
+                   std::to_string(nocc) + " nband " + std::to_string(nband) + " budget " +
+                   std::to_string(budget);
+          ace_ctx c = nullptr;
+          EXPECT(ace_create(&c, nullptr, nullptr) == ACE_OK);
+          ace_set_pair_budget(c, budget * ng * (long)cx_bytes(prec));
+          int accums = 0;
+          spectra_reads(nband, &accums);
+          EXPECT(ace_build_W(c, &g, prec, array_at(0), nocc, ng, array_at(0), nband, ng,
+                             array_at(1), ng, 1.0) == ACE_OK);
+          if (prec == ACE_FP64 || prec == ACE_FP32)
+            EXPECT(ace_apply_h(c, &g, prec, nullptr, nullptr, 0, 0, array_at(0), nocc, ng, 1.0,
+                               array_at(0), nband, ng, array_at(1), ng) == ACE_OK);
+          EXPECT(accums > 0);
+          on_launch = nullptr;
+          ace_destroy(c);
+        }
+}
+
 }  // namespace
 
 int main() {
   setvbuf(stdout, nullptr, _IOLBF, 0);
   shared_orbitals_on_split_lines();
+  fewer_bands_than_orbitals();
   std::printf("plan checks: %d checks, %d failures\n", g_checks, g_failures);
   return g_failures ? 1 : 0;
 }
