@@ -294,10 +294,10 @@ bool overlap(Span a, Span b);
 // data type (FP32 MFMA for complex64, FP64 for complex128), kBf16Split the
 // BF16 hi/lo products with FP32 accumulation (complex64 only), kFp64 FP64 MFMA
 // products of complex64 data with FP64 accumulation.
-// kNative: the data's precision, four real products in the order of k_cn_mfma
-// for FP32; kFp64Four: FP64 in that order; kFp32Chunks: the data's precision,
-// FP32 in three products and short chains (k_cn_blocks).
-enum CnMode { kNative = 0, kBf16Split = 1, kFp64 = 2, kFp64Four = 3, kFp32Chunks = 4 };
+// kNative: the data's precision, FP32 by tiles (k_cn_mfma); kFp64Tiles: FP64 by
+// tiles; kFp32Chunks: the data's precision, FP32 by blocks with short chains too
+// (k_cn_blocks).
+enum CnMode { kNative = 0, kBf16Split = 1, kFp64 = 2, kFp64Tiles = 3, kFp32Chunks = 4 };
 // Exact scratch bytes of one gemm_cn call (complex data of data_bytes per
 // element, arithmetic mode, Hermitian shape or not).
 size_t gemm_cn_partial_bytes(int na, int nb, long K, size_t data_bytes, CnMode mode, bool herm);

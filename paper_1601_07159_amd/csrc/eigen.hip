@@ -574,10 +574,10 @@ ace_status rayleigh_ritz_t(ace_ctx c, const GridInfo& g, const cx<T>* X, long ld
   if (!S || !A || !ctl || !Q) return st;
   const size_t used = c->ws_used;
   // S = dV X^H (H X), Hermitian for Hermitian H: upper tiles, lower mirrored.
-  // Four real products: the sweeps end at a threshold, and with three the
-  // vectors of close eigenvalues turned by 1e-4 (96 vectors at 48^3, 0.05 ms
-  // of 2.2).
-  ACE_TRY(gemm_cn<T>(c, X, ldx, n, HX, ldhx, n, g.ng, g.dV, S, n, kFp64Four, false, true));
+  // By tiles, in one order of summation: the sweeps end at a threshold, and
+  // rounding differences of S turn the vectors of close eigenvalues (by 1e-4,
+  // 96 vectors at 48^3; 0.05 ms of 2.2).
+  ACE_TRY(gemm_cn<T>(c, X, ldx, n, HX, ldhx, n, g.ng, g.dV, S, n, kFp64Tiles, false, true));
   // the rotations take the place of the reduction's partial sums, which the
   // stream has consumed by then
   c->ws_used = used;

@@ -428,20 +428,28 @@ __global__ __launch_bounds__(1024) void k_reduce_partials2(const cx<P>* __restri
 // workgroup per CU.  The rows of both operands come to LDS in chunks by loads
 // that write LDS directly, one chunk ahead.  A row's 16-byte segments are
 // permuted by its number (exclusive or), so that 16 rows read at one segment
-// touch all banks once.  Three real products (Gauss): with P1 = ar br, P2 =
-// ai bi, P3 = (ar - ai)(br + bi), Re = P1 + P2 and Im = P3 - P1 + P2; P3 is
-// left out where the real part is all that is asked for.
+// touch all banks once.
 //
-// Bound by the FP64 matrix cores (65 % busy) and the conversions and sums that
-// share the FP64 units with them, so a wave's blocks share a column of B where
-// they can.  136 rows x 64^3 points of FP32: 568 -> 342 us (tiles of 32 with
-// four products, two unequal workgroup rows); 256 x 72^3: 2,031 -> 1,522 us.
-// Converting to FP64 on the way to LDS doubled the LDS reads: 364, 1,943 us.
-// In FP32 (256 x 256 x 72^3) the vector instructions beside the MFMAs and the
-// clock (2.1 GHz under this load) bound it: 2,102 -> 1,439 us, 1,589 with the
-// chains ended at every chunk; the result is closer to 64 bits than the single
-// chains of four products were (4.4e-7 against 1.2e-6).
-constexpr int kGramBlocks = 8;           // 192 accumulator registers
+// Precision: four real products per complex one (two where only the real part
+// is asked for), and chains of at most kChainPoints points whose sums are added
+// up apart in FP64.  Three products (Gauss) would take a quarter of the MFMAs
+// away, but they form Im as a difference of sums of the size of Re: measured
+// 10 to 3,000 times further off for smooth or nearly parallel orbitals.  With
+// fewer K splits than k_cn_mfma (256 against up to 1,024 for few rows) longer
+// chains were up to 6 times further off than its own.  Against it, in error and
+// time (smooth orbitals; whole product): 64 rows x 48^3 of FP32 with FP64 sums
+// 0.30 of the error, 72 -> 74 us; 136 x 64^3 0.05, 594 -> 435 us; 256 x 72^3
+// 0.01, 2,081 -> 1,803 us; FP64 data 136 x 64^3 0.39, 828 -> 464 us; FP32 sums
+// 64 x 64 x 48^3 0.49, 63 -> 52 us, 256 x 256 x 72^3 0.004, 2,308 -> 1,728 us.
+//
+// Bound by the FP64 matrix cores and, for FP32 data, the conversions that share
+// the FP64 units with them, so a wave's blocks share a column of B where they
+// can.  Converting to FP64 on the way to LDS doubled the LDS reads (1.07 and
+// 1.28 times the time at 136 x 64^3 and 256 x 72^3).
+// Blocks of a wave: 192 accumulator registers.
+template <typename TAcc>
+constexpr int kGramBlocks = sizeof(TAcc) == 8 ? 6 : 8;
+constexpr int kChainPoints = 64;  // the shortest chains that k_cn_mfma takes
 constexpr int kGramBuffer = 80 * 1024;   // bytes of one of two chunks (all of LDS)
 struct GramShape {
   int gx, per;      // workgroup rows, blocks of each
@@ -505,24 +513,22 @@ __global__ __launch_bounds__(512) void k_cn_blocks(const cx<T>* __restrict__ A, 
           (__attribute__((address_space(3))) void*)(dst + (size_t)e * 1024), 16, 0, 0);
     }
   };
-  acc_t p1[NBW], p2[NBW], p3[REAL ? 1 : NBW];
+  // the running chains and their sums
+  acc_t c1[NBW], c2[REAL ? 1 : NBW];
+  v4d re[NBW], im[REAL ? 1 : NBW];
 #pragma unroll
-  for (int i = 0; i < NBW; ++i) p1[i] = p2[i] = acc_t{0, 0, 0, 0};
-#pragma unroll
-  for (int i = 0; i < (REAL ? 1 : NBW); ++i) p3[i] = acc_t{0, 0, 0, 0};
-  // FP32: the sums of four chunks (up to 256 points) are added up apart, so that
-  // no chain of products is longer than that
-  constexpr bool kTwo = sizeof(TAcc) == 4;
-  constexpr int kFlush = 4;
-  int chunk = 0;
-  acc_t re[kTwo ? NBW : 1], im[kTwo && !REAL ? NBW : 1];
-#pragma unroll
-  for (int i = 0; i < (kTwo ? NBW : 1); ++i) re[i] = acc_t{0, 0, 0, 0};
-#pragma unroll
-  for (int i = 0; i < (kTwo && !REAL ? NBW : 1); ++i) im[i] = acc_t{0, 0, 0, 0};
+  for (int i = 0; i < NBW; ++i) {
+    c1[i] = acc_t{0, 0, 0, 0};
+    re[i] = v4d{0, 0, 0, 0};
+    if constexpr (!REAL) {
+      c2[i] = acc_t{0, 0, 0, 0};
+      im[i] = v4d{0, 0, 0, 0};
+    }
+  }
   const int boff = g.same ? 0 : ra - 16 * fy;  // LDS row of B's row 0
   typedef T seg_t __attribute__((ext_vector_type(16 / sizeof(T))));
-  const long step = (long)seg * PT;
+  const int step = seg * PT;
+  int chained = 0;  // points in the running chains
   stage(lds[0], kbeg);
   int buf = 0;
   for (long k0 = kbeg; k0 < kend; k0 += step, buf ^= 1) {
@@ -531,7 +537,7 @@ __global__ __launch_bounds__(512) void k_cn_blocks(const cx<T>* __restrict__ A, 
     if (k0 + step < kend) stage(lds[buf ^ 1], k0 + step);
     for (int t = 0; t < seg; t += 4) {
       const char* base = lds[buf] + (((r16 << g.lseg) + ((t + kq) ^ (r16 & swz))) << 4);
-      TAcc br[PT], bi[PT], bs[PT];
+      TAcc br[PT], bi[PT], bneg[PT];
       // A's rows are read one block ahead
       seg_t a_next = *(const seg_t*)(base + ((16 * bx[0]) << (g.lseg + 4)));
 #pragma unroll
@@ -546,31 +552,30 @@ __global__ __launch_bounds__(512) void k_cn_blocks(const cx<T>* __restrict__ A, 
           for (int h = 0; h < PT; ++h) {
             br[h] = (TAcc)b[2 * h];
             bi[h] = (TAcc)b[2 * h + 1];
-            bs[h] = br[h] + bi[h];
+            bneg[h] = -br[h];
           }
         }
 #pragma unroll
         for (int h = 0; h < PT; ++h) {
           const TAcc ar = (TAcc)a[2 * h], ai = (TAcc)a[2 * h + 1];
-          p1[i] = mfma4(ar, br[h], p1[i]);
-          if constexpr (REAL) {
-            p1[i] = mfma4(ai, bi[h], p1[i]);
-          } else {
-            p2[i] = mfma4(ai, bi[h], p2[i]);
-            p3[i] = mfma4(ar - ai, bs[h], p3[i]);
-          }
+          c1[i] = mfma4(ar, br[h], c1[i]);
+          if constexpr (!REAL) c2[i] = mfma4(ar, bi[h], c2[i]);
+          c1[i] = mfma4(ai, bi[h], c1[i]);
+          if constexpr (!REAL) c2[i] = mfma4(ai, bneg[h], c2[i]);
         }
       }
     }
-    if (kTwo && (++chunk % kFlush == 0 || k0 + step >= kend)) {
+    chained += step;
+    if (chained >= kChainPoints || k0 + step >= kend) {
+      chained = 0;
 #pragma unroll
-      for (int i = 0; i < (kTwo ? NBW : 0); ++i) {
+      for (int i = 0; i < NBW; ++i) {
+        re[i] += __builtin_convertvector(c1[i], v4d);
+        c1[i] = acc_t{0, 0, 0, 0};
         if constexpr (!REAL) {
-          im[i] += (p3[i] - p1[i]) + p2[i];
-          p3[i] = acc_t{0, 0, 0, 0};
+          im[i] += __builtin_convertvector(c2[i], v4d);
+          c2[i] = acc_t{0, 0, 0, 0};
         }
-        re[i] += p1[i] + p2[i];
-        p1[i] = p2[i] = acc_t{0, 0, 0, 0};
       }
     }
   }
@@ -581,13 +586,8 @@ __global__ __launch_bounds__(512) void k_cn_blocks(const cx<T>* __restrict__ A, 
     for (int v = 0; v < 4; ++v) {
       const int x = 16 * bx[i] + mfma_row<TAcc>(lane, v), y = 16 * by[i] + r16;
       if (x >= na || y >= nb) continue;
-      cx<TAcc>& out = partial[((size_t)blockIdx.y * nb + y) * na + x];
-      if constexpr (kTwo)
-        out = {re[i][v], REAL ? TAcc(0) : im[REAL ? 0 : i][v]};
-      else if constexpr (REAL)
-        out = {p1[i][v], TAcc(0)};
-      else
-        out = {p1[i][v] + p2[i][v], p3[i][v] - p1[i][v] + p2[i][v]};
+      partial[((size_t)blockIdx.y * nb + y) * na + x] = {
+          (TAcc)re[i][v], REAL ? TAcc(0) : (TAcc)im[REAL ? 0 : i][v]};
     }
   }
 }
@@ -1107,28 +1107,30 @@ static bool herm_shape(int n, long K, int max_waves, int cu_waves, CnShape* s) {
   return true;
 }
 
-// Shape of an FP64 product for k_cn_blocks.  False below 8 blocks, which leave
-// waves without work (k_cn_mfma's tiles of 32 then do: 48 rows), where a
-// chunk's rows exceed the LDS buffer, and where K is no multiple of a chunk.
-static bool gram_shape(int na, int nb, long K, size_t data_bytes, bool same, bool herm,
-                       GramShape* s) {
+// Shape of a product for k_cn_blocks (bytes of a data and of an accumulated
+// value).  False below 8 blocks, which leave waves without work (k_cn_mfma's
+// tiles of 32 then do: 48 rows), where a chunk's rows exceed the LDS buffer, and
+// where K is no multiple of a chunk.
+static bool gram_shape(int na, int nb, long K, size_t data_bytes, size_t acc_bytes, bool same,
+                       bool herm, GramShape* s) {
   const int ta = (na + 15) / 16, tb = (nb + 15) / 16;
   const int total = herm ? tb * (tb + 1) / 2 : ta * tb;
   if (total < 8) return false;
   s->herm = herm;
   s->same = same;
-  s->gx = (total + 8 * kGramBlocks - 1) / (8 * kGramBlocks);
+  const int most = 8 * (acc_bytes == sizeof(cx<double>) ? kGramBlocks<double> : kGramBlocks<float>);
+  s->gx = (total + most - 1) / most;
   if (!herm) {
     // The allocation-free apply holds 48 MiB for the matrix and the partials:
     // more workgroup rows, and so fewer partials, where they would not fit (256 x
     // 256 in FP64: 42 partials of six rows instead of 64 of four).
     const size_t entry = (size_t)na * nb;
-    const int max_waves = data_bytes == sizeof(cx<double>) ? 8 : 16;
+    const int max_waves = acc_bytes == sizeof(cx<double>) ? 8 : 16;
     const CnShape tiles = cn_shape(na, nb, K, max_waves, max_waves == 8 ? 12 : 16);
     const size_t mat = entry * sizeof(cx<double>), room = (size_t)47 << 20;
     const size_t cap =
-        std::max((size_t)tiles.ks * entry * data_bytes, room > mat ? room - mat : (size_t)0);
-    while (s->gx < 256 && 256 / s->gx * entry * data_bytes > cap) ++s->gx;
+        std::max((size_t)tiles.ks * entry * acc_bytes, room > mat ? room - mat : (size_t)0);
+    while (s->gx < 256 && 256 / s->gx * entry * acc_bytes > cap) ++s->gx;
     s->gx = std::min(s->gx, total);
   }
   s->per = (total + s->gx - 1) / s->gx;
@@ -1160,12 +1162,12 @@ static bool gram_shape(int na, int nb, long K, size_t data_bytes, bool same, boo
   return true;
 }
 
-// K splits of an FP64 product, whichever kernel takes it.
-static long gram_splits(int na, int nb, long K, size_t data_bytes, bool herm) {
+// K splits of a product by blocks (0: its size or shape takes tiles).
+static long gram_splits(int na, int nb, long K, size_t data_bytes, size_t acc_bytes, bool herm) {
   long ks = 0;
   for (int same = 0; same < 2; ++same) {
     GramShape g;
-    if (gram_shape(na, nb, K, data_bytes, same != 0, herm, &g) && g.ks > ks) ks = g.ks;
+    if (gram_shape(na, nb, K, data_bytes, acc_bytes, same != 0, herm, &g) && g.ks > ks) ks = g.ks;
   }
   return ks;
 }
@@ -1176,10 +1178,12 @@ static ace_status launch_gram(ace_ctx c, const char* name, const GramShape& g, c
                               cx<TAcc>* partial) {
   const dim3 grid((unsigned)g.gx, (unsigned)g.ks), block(512);
   switch ((g.per + 7) / 8) {
-#define ACE_GRAM(N)                                                                              \
-  case N:                                                                                        \
-    return launch(c, name, k_cn_blocks<T, TAcc, N, REAL>, grid, block, 0, A, lda, na, B, ldb, nb, \
-                  K, partial, g);
+#define ACE_GRAM(N)                                                                          \
+  case N:                                                                                    \
+    if constexpr (N <= kGramBlocks<TAcc>)                                                    \
+      return launch(c, name, k_cn_blocks<T, TAcc, N, REAL>, grid, block, 0, A, lda, na, B,   \
+                    ldb, nb, K, partial, g);                                                 \
+    break;
     ACE_GRAM(1) ACE_GRAM(2) ACE_GRAM(3) ACE_GRAM(4)
     ACE_GRAM(5) ACE_GRAM(6) ACE_GRAM(7) ACE_GRAM(8)
 #undef ACE_GRAM
@@ -1197,9 +1201,10 @@ size_t gemm_cn_scratch_bytes(int na, int nb, long K) {
     if (herm_shape(na, K, kBf16Waves, kBf16Waves, &h) && h.ks > k32) k32 = h.ks;
     if (herm_shape(na, K, 8, 12, &h) && h.ks > k64) k64 = h.ks;
   }
-  for (size_t eb : {sizeof(cx<float>), sizeof(cx<double>)})
-    for (int herm = 0; herm < (na == nb ? 2 : 1); ++herm)
-      k64 = std::max(k64, gram_splits(na, nb, K, eb, herm != 0));
+  for (int herm = 0; herm < (na == nb ? 2 : 1); ++herm) {
+    k32 = std::max(k32, gram_splits(na, nb, K, 8, 8, herm != 0));
+    for (size_t eb : {8, 16}) k64 = std::max(k64, gram_splits(na, nb, K, eb, 16, herm != 0));
+  }
   const size_t b32 = (size_t)k32 * na * nb * sizeof(cx<float>);
   const size_t b64 = (size_t)k64 * na * nb * sizeof(cx<double>);
   return align_up(b32 > b64 ? b32 : b64, 256);
@@ -1213,7 +1218,7 @@ size_t gemm_cn_partial_bytes(int na, int nb, long K, size_t data_bytes, CnMode m
   CnShape s = cn_shape(na, nb, K, max_waves, cu_waves);
   if (herm && na == nb) herm_shape(na, K, max_waves, cu_waves, &s);
   if (f64 || mode == kFp32Chunks)
-    s.ks = std::max(s.ks, gram_splits(na, nb, K, data_bytes, herm && na == nb));
+    s.ks = std::max(s.ks, gram_splits(na, nb, K, data_bytes, f64 ? 16 : 8, herm && na == nb));
   const size_t part_eb = f64 ? sizeof(cx<double>) : sizeof(cx<float>);
   return align_up((size_t)s.ks * na * nb * part_eb, 256);
 }
@@ -1223,7 +1228,7 @@ ace_status gemm_cn(ace_ctx c, const cx<T>* A, long lda, int na, const cx<T>* B, 
                    long K, double alpha, cx<double>* C, int ldc, CnMode mode,
                    bool real_part, bool herm) {
   const bool bf16_split = std::is_same<T, float>::value && mode == kBf16Split;
-  const bool f64 = sizeof(T) == 8 || mode == kFp64 || mode == kFp64Four;
+  const bool f64 = sizeof(T) == 8 || mode == kFp64 || mode == kFp64Tiles;
   // the BF16-split kernel addresses a tile's 32 rows through a buffer
   // resource with 32-bit byte offsets
   if (bf16_split && (lda > (1L << 31) / 256 || ldb > (1L << 31) / 256))
@@ -1232,9 +1237,9 @@ ace_status gemm_cn(ace_ctx c, const cx<T>* A, long lda, int na, const cx<T>* B, 
   GramShape gs;
   const bool aligned = ((uintptr_t)A | (uintptr_t)B | (uintptr_t)(lda * sizeof(cx<T>)) |
                         (uintptr_t)(ldb * sizeof(cx<T>))) % 16 == 0;
-  if (((f64 && mode != kFp64Four) || mode == kFp32Chunks) && aligned &&
-      gram_shape(na, nb, K, sizeof(cx<T>), A == B && lda == ldb && na == nb, herm && na == nb,
-                 &gs)) {
+  if (((f64 && mode != kFp64Tiles) || mode == kFp32Chunks) && aligned &&
+      gram_shape(na, nb, K, sizeof(cx<T>), f64 ? 16 : 8, A == B && lda == ldb && na == nb,
+                 herm && na == nb, &gs)) {
     auto run = [&](auto acc, const char* name) -> ace_status {
       typedef decltype(acc) TAcc;
       ace_status st;

@@ -153,3 +153,33 @@ def test_noalloc_sizes(prec, nb, nx):
     assert st == 0
     assert torch.equal(Y, ctx.apply(xi, X, gg, prec))
     ctx.close()
+
+
+@pytest.mark.parametrize("prec,nb,nx", [("fp64", 96, 17), ("fp64", 161, 32), ("fp32", 272, 17)])
+def test_small_imaginary_parts(prec, nb, nx):
+    """Orbitals that are all but real: the imaginary parts of <xi_a, X_b> are as
+    exact as their own terms, not as the real parts.  xi is the identity on its
+    first nb grid points, where Y = V_ACE X then holds -<xi_a, X_b> itself."""
+    from paper_1601_07159_amd import ace
+    n = 24
+    print(f"small imaginary parts prec={prec} nb={nb} nx={nx}", flush=True)
+    L, K = 0.43 * n, n ** 3
+    g = ogrid(n, L)
+    small, eps = (1e-8, 1.1e-16) if prec == "fp64" else (1e-4, 6e-8)
+    t = 2 * np.pi * np.arange(K) / K
+    kx, ky = np.arange(nb)[:, None], np.arange(nx)[:, None]
+    xi = 1 + 0.4 * np.cos((kx % 17 + 1) * t) + 1j * small * np.sin((kx % 13 + 1) * t)
+    X = 1 + 0.4 * np.cos((ky + 2) * t) + 1j * small * np.cos((ky + 5) * t)
+    xi[:, :nb] = np.eye(nb)
+    dt = np.complex128 if prec == "fp64" else np.complex64
+    xi, X = xi.astype(dt), X.astype(dt)
+    Y = to_np(ace.apply(to_gpu(xi.reshape(nb, n, n, n), prec), to_gpu(X.reshape(nx, n, n, n), prec),
+                        ggrid(n, L), prec)).reshape(nx, -1)[:, :nb]
+    ld = np.longdouble
+    xr, xm, Xr, Xm = (v.astype(ld) for v in (xi.real, xi.imag, X.real, X.imag))
+    ref = -ld(g.dV) * (Xm @ xr.T - Xr @ xm.T)
+    # chains of 128 terms, each at most 3 small, added up over K points: a random
+    # walk of sqrt(128) roundings in each chain, times ten (the real parts' own
+    # rounding, K g.dV eps, is 1e8 and 1e4 times the terms')
+    bound = 10 * np.sqrt(128) * eps * 3 * small * K * g.dV
+    assert np.max(np.abs(Y.imag - ref)) <= bound
