@@ -8,10 +8,9 @@
 // consecutive complex grid values (re0, im0, re1, im1) of its row; every real
 // becomes one K slot, so Re(conj(a) b) accumulates a_s b_s and Im(conj(a) b)
 // accumulates a_s b''_s with b'' = (im0, -re0, im1, -re1).  For the expansion
-// the K slots are orbitals: the streaming kernel (more orbitals than fit) forms Re y = ar cr - ai ci,
-// Im y = ar ci + ai cr (four real products), the resident ones three real
-// products P1 = ar cr, P2 = ai ci, P3 = (ar + ai)(cr + ci) with Re y = P1 - P2,
-// Im y = P3 - P1 - P2 (Gauss).
+// the K slots are orbitals: four real products, Re y = ar cr - ai ci, Im y =
+// ar ci + ai cr, or three (Gauss), P1 = ar cr, P2 = ai ci, P3 = (ar + ai)(cr + ci)
+// with Re y = P1 - P2, Im y = P3 - P1 - P2 (k_nn_mfma_res, some of k_nn_slices).
 //
 // MFMA operand layout (16x16xK blocks): lane l supplies A[row l%16][k group
 // l/16] and B[k group l/16][col l%16]; the 16x16 result sits in 4 registers of
@@ -842,23 +841,30 @@ __global__ __launch_bounds__(512) void k_nn_mfma_res(const cx<TIn>* __restrict__
 }
 
 // ---------------------------------------------------------------------------
-// Expansion product with FP64 accumulation.  One workgroup of 8 waves per CU
-// keeps a slice of C's columns in LDS for the whole launch (up to kSliceElems
-// values; an upper triangular C needs only the rows above the slice's last
+// Expansion product by slices of C.  One workgroup of 8 waves per CU
+// keeps a slice of C's columns in LDS for the whole launch (up to kSliceBytes;
+// an upper triangular C needs only the rows above the slice's last
 // column) and its waves walk the 16-row tiles of Y.  The workgroups are dealt
 // out to the slices in proportion to their matrix work, and those of every
 // slice sweep the grid rows in the same order, so that A is read from HBM
-// about once.  Three real products (Gauss, as above).  C is the first operand
-// of the MFMAs: a lane's results belong to one grid row, and 16 lanes store 16
-// consecutive rows of a column.
+// about once.  C is the first operand of the MFMAs: a lane's results belong to
+// one grid row, and 16 lanes store 16 consecutive rows of a column.
 //
-// Bound by the FP64 matrix cores (64 cycles an MFMA), which are busy 70 % of
-// the time; the former kernel staged C again for every 64 rows and multiplied
-// four real products.  136 columns x 64^3 rows of FP32, triangular: 728 -> 334
-// us; 256 x 72^3: 2,008 -> 1,357 us (53 TFLOP/s of real products); 80 x 48^3:
-// 97 -> 68 us.  In FP32 (MFMAs busy 74 %) against all of C resident in every
-// workgroup: 80 x 80 x 48^3 77 -> 68 us, 96 x 96 x 32^3 40 -> 31 us, 256 x 256 x
-// 72^3 1.28 ms both.
+// Three real products (Gauss) or four.  With three, Im y is a difference of
+// sums of the size of Re y: 1.0 to 1.23 times the whole error, 1.25 times that of
+// Im (smooth orbitals: 14 to 17 times), at all sizes.  FP64 sums of FP32 data
+// take three: the stored FP32 value is the same to all digits measured.  So do
+// up to 80 orbitals, and up to 256 in FP32 (but for 65 to 80 columns of more than
+// 80), as k_nn_mfma_res does; the others take four, as k_nn_mfma does.
+//
+// Bound by the matrix cores (FP64: 64 cycles an MFMA), busy 70 % of the time;
+// k_nn_mfma stages C again for every 64 rows.  Against k_nn_mfma (four
+// products): FP32 with FP64 sums, three products, 136 columns x 48^3 rows 448 ->
+// 275 us, triangular 324 -> 167, 256 x 48^3 1,085 -> 763; FP64, four, 136 x 48^3
+// 500 -> 342 us (three: 285), triangular 351 -> 206 (180), 256 x 48^3 1,256 ->
+// 956 (800); FP32, three, 136 x 48^3 361 -> 169, four, 400 x 96 x 48^3 668 -> 380
+// (319) us.  In FP32 against all of C resident in every workgroup: 80 x 80 x 48^3
+// 77 -> 68 us, 96 x 96 x 32^3 40 -> 31 us, 256 x 256 x 72^3 1.28 ms both.
 constexpr int kSliceBytes = 152 * 1024;  // of LDS
 constexpr int kSliceBlocks = 5;    // 16-column blocks: 120 accumulator registers
 constexpr int kMaxSlices = 32;
@@ -870,7 +876,8 @@ struct NnSlices {
 
 // XB tiles of 16 grid rows at a time: narrow slices take several, so that the
 // loads of three steps ahead cover the memory latency.
-template <typename TIn, typename TAcc, int NBB>
+// MUL real products per complex one: 3 (Gauss) or 4.
+template <typename TIn, typename TAcc, int NBB, int MUL>
 __device__ __forceinline__ void nn_slice_body(cx<TAcc>* cs, const cx<TIn>* __restrict__ A, long lda,
                                               int na, const cx<double>* __restrict__ C, int ldc,
                                               int b0, int nb, cx<TIn>* __restrict__ Y, long ldy,
@@ -924,11 +931,15 @@ __device__ __forceinline__ void nn_slice_body(cx<TAcc>* cs, const cx<TIn>* __res
 #pragma unroll
   for (int u = 0; u < 3; ++u) load(x[u], u);
   for (; tile < ntiles; tile += stride) {
-    acc_t p1[XB][NBB], p2[XB][NBB], p3[XB][NBB];
+    // P1, P2 and P3, or Re and Im
+    acc_t p1[XB][NBB], p2[XB][NBB], p3[MUL == 3 ? XB : 1][MUL == 3 ? NBB : 1];
 #pragma unroll
     for (int q = 0; q < XB; ++q)
 #pragma unroll
-      for (int y = 0; y < NBB; ++y) p1[q][y] = p2[q][y] = p3[q][y] = acc_t{0, 0, 0, 0};
+      for (int y = 0; y < NBB; ++y) {
+        p1[q][y] = p2[q][y] = acc_t{0, 0, 0, 0};
+        if constexpr (MUL == 3) p3[q][y] = acc_t{0, 0, 0, 0};
+      }
     cx<TAcc> c[2][NBB];
     auto loadc = [&](auto first, cx<TAcc> (&cv)[NBB], int st) {
       constexpr int F = decltype(first)::value;
@@ -946,13 +957,20 @@ __device__ __forceinline__ void nn_slice_body(cx<TAcc>* cs, const cx<TIn>* __res
         if (u < 3) loadc(first, c[(u + 1) & 1], 4 * g + u + 1);
 #pragma unroll
         for (int q = 0; q < XB; ++q) {
-          const TAcc xr = (TAcc)x[u][q].x, xi = (TAcc)x[u][q].y, xs = xr + xi;
+          const TAcc xr = (TAcc)x[u][q].x, xi = (TAcc)x[u][q].y;
+          const TAcc x3 = MUL == 3 ? xr + xi : -xi;
 #pragma unroll
           for (int y = F; y < NBB; ++y) {
             const cx<TAcc> cv = c[u & 1][y];
             p1[q][y] = mfma4(cv.x, xr, p1[q][y]);
-            p2[q][y] = mfma4(cv.y, xi, p2[q][y]);
-            p3[q][y] = mfma4(cv.x + cv.y, xs, p3[q][y]);
+            if constexpr (MUL == 3) {
+              p2[q][y] = mfma4(cv.y, xi, p2[q][y]);
+              p3[q][y] = mfma4(cv.x + cv.y, x3, p3[q][y]);
+            } else {
+              p2[q][y] = mfma4(cv.x, xi, p2[q][y]);
+              p1[q][y] = mfma4(cv.y, x3, p1[q][y]);
+              p2[q][y] = mfma4(cv.y, xr, p2[q][y]);
+            }
           }
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -977,9 +995,12 @@ __device__ __forceinline__ void nn_slice_body(cx<TAcc>* cs, const cx<TIn>* __res
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           const int b = b0 + 16 * y + mfma_row<TAcc>(lane, v);
-          if (b < nb && in)
-            Y[(size_t)b * ldy + row[q]] = {(TIn)(p1[q][y][v] - p2[q][y][v]),
-                                           (TIn)(p3[q][y][v] - p1[q][y][v] - p2[q][y][v])};
+          TAcc re = p1[q][y][v], im = p2[q][y][v];
+          if constexpr (MUL == 3) {
+            re = p1[q][y][v] - p2[q][y][v];
+            im = p3[q][y][v] - p1[q][y][v] - p2[q][y][v];
+          }
+          if (b < nb && in) Y[(size_t)b * ldy + row[q]] = {(TIn)re, (TIn)im};
         }
       row[q] = row_next[q];
     }
@@ -987,7 +1008,7 @@ __device__ __forceinline__ void nn_slice_body(cx<TAcc>* cs, const cx<TIn>* __res
   }
 }
 
-template <typename TIn, typename TAcc>
+template <typename TIn, typename TAcc, int MUL>
 __global__ __launch_bounds__(512) void k_nn_slices(const cx<TIn>* __restrict__ A, long lda, int na,
                                                 const cx<double>* __restrict__ C, int ldc,
                                                 cx<TIn>* __restrict__ Y, long ldy, long K,
@@ -998,7 +1019,7 @@ __global__ __launch_bounds__(512) void k_nn_slices(const cx<TIn>* __restrict__ A
   const int wg = (int)blockIdx.x - sl.wg0[q], nwg = sl.wg0[q + 1] - sl.wg0[q];
   const int b0 = sl.b0[q], nb = sl.b0[q + 1];
 #define ACE_BODY(NBBV)                                                                     \
-  nn_slice_body<TIn, TAcc, NBBV>(cs, A, lda, na, C, ldc, b0, nb, Y, ldy, K, upper, wg, nwg)
+  nn_slice_body<TIn, TAcc, NBBV, MUL>(cs, A, lda, na, C, ldc, b0, nb, Y, ldy, K, upper, wg, nwg)
   switch ((nb - b0 + 15) / 16) {
     case 1: ACE_BODY(1); break;
     case 2: ACE_BODY(2); break;
@@ -1011,7 +1032,7 @@ __global__ __launch_bounds__(512) void k_nn_slices(const cx<TIn>* __restrict__ A
 
 }  // namespace
 
-// Column slices of an expansion product in FP64 and the workgroups of each;
+// Column slices of an expansion product and the workgroups of each;
 // false when n_a is too large for a slice of 16 columns in LDS or the slices
 // are too many.
 static bool nn_slices(int na, int nb, long K, size_t acc_bytes, bool upper, NnSlices* s,
@@ -1299,16 +1320,24 @@ static ace_status nn_dispatch(ace_ctx c, const char* name, const cx<TIn>* A, lon
                               long K, bool c_upper) {
   // Slices of C in LDS, up to 608 orbitals (1,216 in FP32) and 32 slices; past
   // that C is staged chunk by chunk.  Up to 16 columns, and up to 32 of a short
-  // product, keep the other forms, whose workgroups are smaller and whose loads
+  // product, take the other forms, whose workgroups are smaller and whose loads
   // run further ahead: in FP64 64 orbitals and 8 columns at 24^3 23 against 32
   // us, 128 and 8 at 32^3 45 against 55 us, 4 and 4 at 48^3 32.4 against 33.3 us
   // (whole calls).
   {
     NnSlices sl;
     unsigned grid;
-    if ((nb > 32 || (nb > 16 && K > 65536)) && nn_slices(na, nb, K, sizeof(cx<TAcc>), c_upper, &sl, &grid))
-      return launch(c, name, k_nn_slices<TIn, TAcc>, dim3(grid), dim3(512), 0, A, lda, na, C, ldc, Y, ldy,
-                    K, c_upper ? 1 : 0, sl);
+    if ((nb > 32 || (nb > 16 && K > 65536)) &&
+        nn_slices(na, nb, K, sizeof(cx<TAcc>), c_upper, &sl, &grid)) {
+      const auto run = [&](auto mul) {
+        return launch(c, name, k_nn_slices<TIn, TAcc, decltype(mul)::value>, dim3(grid), dim3(512),
+                      0, A, lda, na, C, ldc, Y, ldy, K, c_upper ? 1 : 0, sl);
+      };
+      // where three products lose nothing (see k_nn_slices)
+      const bool three = sizeof(TAcc) > sizeof(TIn) || na <= kNnResA ||
+                         (sizeof(TAcc) == 4 && na <= kNnResA2 && (nb <= 64 || nb > 80));
+      return three ? run(std::integral_constant<int, 3>{}) : run(std::integral_constant<int, 4>{});
+    }
   }
   const int nbb = nb <= 16 ? 1 : nb <= 32 ? 2 : nb <= 48 ? 3 : nb <= 80 && nb > 64 ? 5 : 4;
   const dim3 block(256);

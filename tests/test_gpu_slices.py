@@ -183,3 +183,33 @@ def test_small_imaginary_parts(prec, nb, nx):
     # rounding, K g.dV eps, is 1e8 and 1e4 times the terms')
     bound = 10 * np.sqrt(128) * eps * 3 * small * K * g.dV
     assert np.max(np.abs(Y.imag - ref)) <= bound
+
+
+@pytest.mark.parametrize("prec,nb,nx", [("fp64", 96, 48), ("fp32", 272, 48), ("fp32", 96, 72)])
+def test_small_imaginary_parts_expanded(prec, nb, nx):
+    """The same for the expansion by slices, more orbitals than three products
+    are taken for: Im Y is as exact as its own terms."""
+    from paper_1601_07159_amd import ace
+    n = 24
+    print(f"small imaginary parts, expanded prec={prec} nb={nb} nx={nx}", flush=True)
+    L, K = 0.43 * n, n ** 3
+    g = ogrid(n, L)
+    small, eps = (1e-8, 1.1e-16) if prec == "fp64" else (1e-6, 6e-8)
+    t = 2 * np.pi * np.arange(K) / K
+    kx, ky = np.arange(nb)[:, None], np.arange(nx)[:, None]
+    xi = 1 + 0.4 * np.cos((kx % 17 + 1) * t) + 1j * small * np.sin((kx % 13 + 1) * t)
+    X = 1 + 0.4 * np.cos((ky + 2) * t) + 1j * small * np.cos((ky + 5) * t)
+    dt = np.complex128 if prec == "fp64" else np.complex64
+    xi, X = xi.astype(dt), X.astype(dt)
+    Y = to_np(ace.apply(to_gpu(xi.reshape(nb, n, n, n), prec), to_gpu(X.reshape(nx, n, n, n), prec),
+                        ggrid(n, L), prec)).reshape(nx, -1)
+    ld = np.longdouble
+    xr, xm, Xr, Xm = (v.astype(ld) for v in (xi.real, xi.imag, X.real, X.imag))
+    cr, cm = -(xr @ Xr.T + xm @ Xm.T), -(xr @ Xm.T - xm @ Xr.T)
+    at = np.random.default_rng(nx).integers(0, K, 48)
+    ref = ld(g.dV) * (xr[:, at].T @ cm + xm[:, at].T @ cr).T
+    # terms xi_r C_m and xi_m C_r of at most 1.4 * 3 small K dV and small * 2 K dV,
+    # nb of each; a random walk of the reduction's chains (128 terms) and of the
+    # expansion's (2 nb), times ten
+    bound = 10 * (np.sqrt(128) + np.sqrt(2 * nb)) * eps * nb * 6.2 * small * K * g.dV
+    assert np.max(np.abs(Y[:, at].imag - ref)) <= bound
