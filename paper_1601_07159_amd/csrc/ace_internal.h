@@ -325,11 +325,11 @@ ace_status gemm_cn(ace_ctx c, const cx<T>* A, long lda, int na, const cx<T>* B, 
                    long K, double alpha, cx<double>* C, int ldc, CnMode mode,
                    bool real_part = false, bool herm = false);
 // Y_b[r] = sum_a A_a[r] C[a + b*ldc]      (r < K); c_upper: C is upper
-// triangular and its zero blocks are skipped
+// triangular and its zero blocks are skipped; c_real: C's imaginary parts are 0
 template <typename T>
 ace_status gemm_nn(ace_ctx c, const cx<T>* A, long lda, int na, const cx<double>* C, int ldc,
                    int nb, cx<T>* Y, long ldy, long K, bool fp64_accumulate,
-                   bool c_upper = false);
+                   bool c_upper = false, bool c_real = false);
 // Fused: A = s (M + M^H)/2, A = L L^H, Lout = L (nullable), C = L^{-H}.
 // scratch: chol_scratch_elems(n) complex128 (used when n > 88).  info_dev gets
 // 0 or the first failing pivot; a nonzero *prior (nullable) is propagated.

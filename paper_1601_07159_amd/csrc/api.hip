@@ -298,7 +298,7 @@ ace_status compress_impl(ace_ctx c, const GridInfo& g, const cx<T>* psi, long ld
   // -M made exactly Hermitian, -M = L L^H, C = L^{-H}
   ACE_TRY(chol_inv(c, M, nb, -1.0, L_out, C, X, info, nullptr, real));
   ACE_TRY(gemm_nn<T>(c, W, ldW, nb, C, nb, nb, alias ? tmp : xi, alias ? g.ng : ldxi, g.ng, true,
-                     true));
+                     true, real));
   if (alias) {
     const hipError_t e = hipMemcpy2DAsync(xi, (size_t)ldxi * sizeof(cx<T>), tmp,
                                           (size_t)g.ng * sizeof(cx<T>), (size_t)g.ng * sizeof(cx<T>),
@@ -325,7 +325,7 @@ static ace_status apply_t(ace_ctx c, const GridInfo& g, const cx<T>* xi, int nb,
   cx<double>* C = (cx<double>*)ws_take(c, mat, &st);
   if (!C) return st;
   ACE_TRY(gemm_cn<T>(c, xi, ldxi, nb, X, ldx, nx, g.ng, -g.dV, C, nb, kFp32Chunks, real));
-  return gemm_nn<T>(c, xi, ldxi, nb, C, nb, nx, Y, ldy, g.ng, false);
+  return gemm_nn<T>(c, xi, ldxi, nb, C, nb, nx, Y, ldy, g.ng, false, false, real);
 }
 
 template <typename T>
@@ -359,11 +359,11 @@ static ace_status orth_t(ace_ctx c, const GridInfo& g, const cx<T>* X, int n, lo
   // first pass: Y = X R1^{-1}, S = dV X^H X = R1^H R1 with R1 = L^H
   ACE_TRY(gemm_cn<T>(c, X, ldx, n, X, ldx, n, g.ng, g.dV, S, n, mode, real, true));
   ACE_TRY(chol_inv(c, S, n, 1.0, nullptr, C, Xs, info1, nullptr, real));
-  ACE_TRY(gemm_nn<T>(c, X, ldx, n, C, n, n, Y, g.ng, g.ng, true, true));
+  ACE_TRY(gemm_nn<T>(c, X, ldx, n, C, n, n, Y, g.ng, g.ng, true, true, real));
   // the second pass on Y restores orthogonality lost to rounding in the first
   ACE_TRY(gemm_cn<T>(c, Y, g.ng, n, Y, g.ng, n, g.ng, g.dV, S, n, mode, real, true));
   ACE_TRY(chol_inv(c, S, n, 1.0, nullptr, C, Xs, info2, info1, real));
-  ACE_TRY(gemm_nn<T>(c, Y, g.ng, n, C, n, n, Q, ldq, g.ng, true, true));
+  ACE_TRY(gemm_nn<T>(c, Y, g.ng, n, C, n, n, Q, ldq, g.ng, true, true, real));
   return finish_info(c, info2, info_dev);
 }
 

@@ -855,7 +855,11 @@ __global__ __launch_bounds__(512) void k_nn_mfma_res(const cx<TIn>* __restrict__
 // Im (smooth orbitals: 14 to 17 times), at all sizes.  FP64 sums of FP32 data
 // take three: the stored FP32 value is the same to all digits measured.  So do
 // up to 80 orbitals, and up to 256 in FP32 (but for 65 to 80 columns of more than
-// 80), as k_nn_mfma_res does; the others take four, as k_nn_mfma does.
+// 80), as k_nn_mfma_res does; the others take four, as k_nn_mfma does.  Real
+// orbitals, seen as complex pairs of grid values, have a real C and take two:
+// with three the second value of a pair would take its neighbour's rounding (1.4
+// to 1.75 times the error).  FP64, 136 x 48^3 149 -> 109 us, 256 x 48^3 390 -> 293,
+// FP32 256 x 48^3 241 -> 176.
 //
 // Bound by the matrix cores (FP64: 64 cycles an MFMA), busy 70 % of the time;
 // k_nn_mfma stages C again for every 64 rows.  Against k_nn_mfma (four
@@ -876,7 +880,8 @@ struct NnSlices {
 
 // XB tiles of 16 grid rows at a time: narrow slices take several, so that the
 // loads of three steps ahead cover the memory latency.
-// MUL real products per complex one: 3 (Gauss) or 4.
+// MUL real products per complex one: 3 (Gauss) or 4; 2 where C is real (xr c
+// and xi c: real orbitals in pairs of grid values).
 template <typename TIn, typename TAcc, int NBB, int MUL>
 __device__ __forceinline__ void nn_slice_body(cx<TAcc>* cs, const cx<TIn>* __restrict__ A, long lda,
                                               int na, const cx<double>* __restrict__ C, int ldc,
@@ -968,8 +973,10 @@ __device__ __forceinline__ void nn_slice_body(cx<TAcc>* cs, const cx<TIn>* __res
               p3[q][y] = mfma4(cv.x + cv.y, x3, p3[q][y]);
             } else {
               p2[q][y] = mfma4(cv.x, xi, p2[q][y]);
-              p1[q][y] = mfma4(cv.y, x3, p1[q][y]);
-              p2[q][y] = mfma4(cv.y, xr, p2[q][y]);
+              if constexpr (MUL == 4) {
+                p1[q][y] = mfma4(cv.y, x3, p1[q][y]);
+                p2[q][y] = mfma4(cv.y, xr, p2[q][y]);
+              }
             }
           }
         }
@@ -1317,7 +1324,7 @@ ace_status gemm_cn(ace_ctx c, const cx<T>* A, long lda, int na, const cx<T>* B, 
 template <typename TIn, typename TAcc>
 static ace_status nn_dispatch(ace_ctx c, const char* name, const cx<TIn>* A, long lda, int na,
                               const cx<double>* C, int ldc, int nb, cx<TIn>* Y, long ldy,
-                              long K, bool c_upper) {
+                              long K, bool c_upper, bool c_real) {
   // Slices of C in LDS, up to 608 orbitals (1,216 in FP32) and 32 slices; past
   // that C is staged chunk by chunk.  Up to 16 columns, and up to 32 of a short
   // product, take the other forms, whose workgroups are smaller and whose loads
@@ -1336,7 +1343,9 @@ static ace_status nn_dispatch(ace_ctx c, const char* name, const cx<TIn>* A, lon
       // where three products lose nothing (see k_nn_slices)
       const bool three = sizeof(TAcc) > sizeof(TIn) || na <= kNnResA ||
                          (sizeof(TAcc) == 4 && na <= kNnResA2 && (nb <= 64 || nb > 80));
-      return three ? run(std::integral_constant<int, 3>{}) : run(std::integral_constant<int, 4>{});
+      return c_real  ? run(std::integral_constant<int, 2>{})
+             : three ? run(std::integral_constant<int, 3>{})
+                     : run(std::integral_constant<int, 4>{});
     }
   }
   const int nbb = nb <= 16 ? 1 : nb <= 32 ? 2 : nb <= 48 ? 3 : nb <= 80 && nb > 64 ? 5 : 4;
@@ -1379,13 +1388,14 @@ static ace_status nn_dispatch(ace_ctx c, const char* name, const cx<TIn>* A, lon
 
 template <typename T>
 ace_status gemm_nn(ace_ctx c, const cx<T>* A, long lda, int na, const cx<double>* C, int ldc,
-                   int nb, cx<T>* Y, long ldy, long K, bool fp64_accumulate, bool c_upper) {
-  if constexpr (std::is_same<T, double>::value)
-    return nn_dispatch<T, double>(c, "nn_mfma_f64", A, lda, na, C, ldc, nb, Y, ldy, K, c_upper);
-  else if (fp64_accumulate)
-    return nn_dispatch<T, double>(c, "nn_mfma_f64", A, lda, na, C, ldc, nb, Y, ldy, K, c_upper);
-  else
-    return nn_dispatch<T, float>(c, "nn_mfma_f32", A, lda, na, C, ldc, nb, Y, ldy, K, c_upper);
+                   int nb, cx<T>* Y, long ldy, long K, bool fp64_accumulate, bool c_upper,
+                   bool c_real) {
+  if constexpr (std::is_same<T, float>::value)
+    if (!fp64_accumulate)
+      return nn_dispatch<T, float>(c, "nn_mfma_f32", A, lda, na, C, ldc, nb, Y, ldy, K, c_upper,
+                                   c_real);
+  return nn_dispatch<T, double>(c, "nn_mfma_f64", A, lda, na, C, ldc, nb, Y, ldy, K, c_upper,
+                                c_real);
 }
 
 template ace_status gemm_cn<float>(ace_ctx, const cx<float>*, long, int, const cx<float>*, long,
@@ -1393,8 +1403,8 @@ template ace_status gemm_cn<float>(ace_ctx, const cx<float>*, long, int, const c
 template ace_status gemm_cn<double>(ace_ctx, const cx<double>*, long, int, const cx<double>*, long,
                                     int, long, double, cx<double>*, int, CnMode, bool, bool);
 template ace_status gemm_nn<float>(ace_ctx, const cx<float>*, long, int, const cx<double>*, int,
-                                   int, cx<float>*, long, long, bool, bool);
+                                   int, cx<float>*, long, long, bool, bool, bool);
 template ace_status gemm_nn<double>(ace_ctx, const cx<double>*, long, int, const cx<double>*, int,
-                                    int, cx<double>*, long, long, bool, bool);
+                                    int, cx<double>*, long, long, bool, bool, bool);
 
 }  // namespace ace

@@ -213,3 +213,30 @@ def test_small_imaginary_parts_expanded(prec, nb, nx):
     # expansion's (2 nb), times ten
     bound = 10 * (np.sqrt(128) + np.sqrt(2 * nb)) * eps * nb * 6.2 * small * K * g.dV
     assert np.max(np.abs(Y[:, at].imag - ref)) <= bound
+
+
+@pytest.mark.parametrize("prec,nb,nx", [("real64", 96, 48), ("real64", 161, 33), ("real32", 272, 48)])
+def test_real_neighbours(prec, nb, nx):
+    """Real orbitals go through the products as pairs of grid values: the small
+    value of a pair is as exact as its own terms, whatever its neighbour."""
+    from paper_1601_07159_amd import ace
+    n = 24
+    print(f"real neighbours prec={prec} nb={nb} nx={nx}", flush=True)
+    L, K = 0.43 * n, n ** 3
+    g = ogrid(n, L)
+    small, eps, dt = (1e-8, 1.1e-16, np.float64) if prec == "real64" else (1e-6, 6e-8, np.float32)
+    t = 2 * np.pi * np.arange(K) / K
+    xi = 1 + 0.4 * np.cos((np.arange(nb)[:, None] % 17 + 1) * t)
+    X = (1 + 0.4 * np.cos((np.arange(nx)[:, None] + 2) * t)).astype(dt)
+    xi[:, 1::2] *= small
+    xi = xi.astype(dt)
+    Y = to_np(ace.apply(to_gpu(xi.reshape(nb, n, n, n), prec), to_gpu(X.reshape(nx, n, n, n), prec),
+                        ggrid(n, L), prec)).real.reshape(nx, -1)
+    ld = np.longdouble
+    xi, X = xi.astype(ld), X.astype(ld)
+    at = 2 * np.random.default_rng(nx).integers(0, K // 2, 48) + 1
+    ref = -ld(g.dV) * (xi[:, at].T @ (xi @ X.T)).T
+    # nb terms of at most 1.4 small times 2 K dV; a random walk of the reduction's
+    # chains (128 terms) and of the expansion's (nb), times ten
+    bound = 10 * (np.sqrt(128) + np.sqrt(nb)) * eps * nb * 2.8 * small * K * g.dV
+    assert np.max(np.abs(Y[:, at] - ref)) <= bound
