@@ -45,7 +45,16 @@
  *         an earlier uncaptured call of the same sizes).  A call that would
  *         have to grow the workspace, or synchronise (info_dev == NULL), on a
  *         capturing stream returns ACE_E_CAPTURE before it enqueues anything
- *         and leaves the capture and the workspace intact.
+ *         and leaves the capture and the workspace intact.  A graph holds the
+ *         workspace's address: it may be replayed until a later call needs a
+ *         larger workspace than there is.
+ * Copies. On larger grids (FP64 from 40^3, FP32 at 72^3) builds and direct
+ *         energies of many pairs work on transposed copies of the orbitals in
+ *         the workspace (up to n_occ + n_band of them; ace_reserve counts
+ *         them).  Where memory, a capture or a workspace that a captured graph
+ *         uses has no room for these, the calls do without and take longer:
+ *         FP32 results are the same, FP64 results agree to rounding.  Memory
+ *         that was refused for copies is asked for again after ace_reserve.
  */
 #ifndef ACE_H
 #define ACE_H

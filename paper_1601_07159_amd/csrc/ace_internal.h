@@ -60,6 +60,8 @@ struct ace_ctx_s {
   // Bytes at the start of the workspace that ws_begin / ws_take skip (a piece
   // one entry point keeps alive across an inner call that carves its own).
   size_t ws_prefix = 0;
+  bool ws_captured = false;  // a call under stream capture used this workspace
+  size_t ws_refused = 0;     // smallest optional size that memory had no room for (0: none)
   // Sub-arena (batched builds): while sub_base is set, ws_begin/ws_take carve
   // from [sub_base, sub_base + sub_bytes) and never reallocate.
   char* sub_base = nullptr;
@@ -167,6 +169,12 @@ struct GridInfo {
 // then ws_take hands out 256-byte aligned pieces.  ws_take returns nullptr and
 // sets *st if a piece exceeds what ws_begin reserved.
 ace_status ws_begin(ace_ctx c, size_t total_bytes);
+// The same for more than the `need` bytes that a call cannot do without: false,
+// without an error, where they cannot be had (then ws_begin(need) follows).  A
+// workspace that holds `need` is then left as it is; it is never moved for
+// optional bytes once a captured graph holds its address, nor is an allocation
+// that memory refused asked for again before the next ace_reserve.
+bool ws_try(ace_ctx c, size_t need, size_t total);
 void* ws_take(ace_ctx c, size_t bytes, ace_status* st);
 // Scratch bytes gemm_cn takes from the workspace for these sizes (the most
 // over every arithmetic and the Hermitian shapes).

@@ -58,6 +58,41 @@ bool stream_capturing(ace_ctx c) {
   return cs != hipStreamCaptureStatusNone;
 }
 
+// Starts carving if the workspace holds `total` bytes; notes a capture's use.
+static bool ws_fits(ace_ctx c, size_t total) {
+  c->ws_used = c->ws_prefix;
+  if (c->ws_prefix + total > c->ws_bytes) return false;
+  if (!c->ws_captured) c->ws_captured = stream_capturing(c);
+  return true;
+}
+
+// Frees the workspace, which queued kernels of earlier calls may still use:
+// every call of the context is ordered on its stream (ace_set_stream chains a
+// new stream after the old one), so waiting for that stream suffices.
+static hipError_t ws_free(ace_ctx c) {
+  if (!c->ws) return hipSuccess;
+  hipError_t e = hipStreamSynchronize(c->stream);
+  if (e == hipSuccess) e = hipFree(c->ws);
+  if (e != hipSuccess) return e;
+  c->ws = nullptr;
+  c->ws_bytes = 0;
+  return hipSuccess;
+}
+
+static bool ws_alloc(void** p, size_t total) {
+  *p = nullptr;
+  if (hipMalloc(p, total) == hipSuccess && *p) return true;
+  (void)hipGetLastError();
+  return false;
+}
+
+static void ws_set(ace_ctx c, void* p, size_t total) {
+  c->ws = p;
+  c->ws_bytes = total;
+  c->ws_captured = false;
+  log_line(c, "workspace grown to %.1f MiB", total / 1048576.0);
+}
+
 ace_status ws_begin(ace_ctx c, size_t total) {
   total = align_up(total ? total : 256, 256);
   if (c->sub_base) {
@@ -65,8 +100,7 @@ ace_status ws_begin(ace_ctx c, size_t total) {
     if (total > c->sub_bytes) return fail(c, ACE_E_NOMEM, "internal: batched workspace plan");
     return ACE_OK;
   }
-  c->ws_used = c->ws_prefix;
-  if (c->ws_prefix + total <= c->ws_bytes) return ACE_OK;
+  if (ws_fits(c, total)) return ACE_OK;
   if (c->ws_prefix) return fail(c, ACE_E_NOMEM, "internal: workspace plan with a kept prefix");
   // Growing synchronises and allocates, neither of which a stream capture
   // allows: refuse before touching the capture or the current buffer.
@@ -74,29 +108,45 @@ ace_status ws_begin(ace_ctx c, size_t total) {
     return fail(c, ACE_E_CAPTURE,
                 "the workspace must grow, which is not possible while the stream is captured "
                 "(call ace_reserve, or the same call once, before capturing)");
-  if (c->ws) {
-    // queued kernels of earlier calls may still use the old buffer; every call
-    // of the context is ordered on its stream (ace_set_stream chains a new
-    // stream after the old one), so waiting for that stream suffices
-    hipError_t e = hipStreamSynchronize(c->stream);
-    if (e != hipSuccess) return hip_fail(c, e, "hipStreamSynchronize(workspace)");
-    e = hipFree(c->ws);
-    if (e != hipSuccess) return hip_fail(c, e, "hipFree(workspace)");
-    c->ws = nullptr;
-    c->ws_bytes = 0;
-  }
-  void* p = nullptr;
-  hipError_t e = hipMalloc(&p, total);
-  if (e != hipSuccess || !p) {
-    (void)hipGetLastError();
+  const hipError_t e = ws_free(c);
+  if (e != hipSuccess) return hip_fail(c, e, "freeing the workspace");
+  void* p;
+  if (!ws_alloc(&p, total)) {
     char buf[128];
     snprintf(buf, sizeof buf, "workspace allocation of %zu bytes failed", total);
     return fail(c, ACE_E_NOMEM, buf);
   }
-  c->ws = p;
-  c->ws_bytes = total;
-  log_line(c, "workspace grown to %.1f MiB", total / 1048576.0);
+  ws_set(c, p, total);
   return ACE_OK;
+}
+
+bool ws_try(ace_ctx c, size_t need, size_t total) {
+  total = align_up(total ? total : 256, 256);
+  if (c->sub_base) {
+    c->ws_used = 0;
+    return total <= c->sub_bytes;
+  }
+  if (ws_fits(c, total)) return true;
+  if (c->ws_prefix || stream_capturing(c)) return false;
+  if (c->ws_refused && total >= c->ws_refused) return false;
+  const bool enough = c->ws && need <= c->ws_bytes;
+  // a workspace that does for the call stays until a larger one is there, and
+  // for good once a captured graph holds its address
+  if (enough && c->ws_captured) return false;
+  if (!enough && ws_free(c) != hipSuccess) return false;  // the call itself reports it
+  void* p;
+  if (!ws_alloc(&p, total)) {
+    c->ws_refused = total;
+    log_line(c, "no memory for a workspace of %.1f MiB, which is optional", total / 1048576.0);
+    return false;
+  }
+  if (ws_free(c) != hipSuccess) {
+    (void)hipFree(p);
+    return false;
+  }
+  ws_set(c, p, total);
+  c->ws_used = 0;
+  return true;
 }
 
 void* ws_take(ace_ctx c, size_t bytes, ace_status* st) {
@@ -555,6 +605,7 @@ ACE_EXPORT ace_status ace_reserve(ace_ctx c, const ace_grid* grid, ace_prec prec
   ACE_TRY(check_grid(c, grid, prec, &g));
   if (max_nocc < 1 || max_nband < 1 || max_nx < 0) return fail(c, ACE_E_ARG, "sizes");
   const size_t eb = elem_bytes(prec);
+  c->ws_refused = 0;  // memory may have become free
   // the largest workspace any call with these sizes takes (so that later
   // calls, also under graph capture, need no allocation)
   const int nmax = std::max(max_nband, std::max(max_nx, max_nocc));

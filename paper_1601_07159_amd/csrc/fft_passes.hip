@@ -883,12 +883,8 @@ bool split_allowed(ace_ctx c, int n, size_t eb) {
 // used (*split) and can be had: where the device memory, or a workspace that
 // may not grow, has no room for them the pass does without.
 ace_status split_ws_begin(ace_ctx c, size_t bytes, size_t copies, bool* split) {
-  if (*split) {
-    const ace_status st = ws_begin(c, bytes + copies);
-    if (st == ACE_OK || (st != ACE_E_NOMEM && st != ACE_E_CAPTURE)) return st;
-    *split = false;
-  }
-  return ws_begin(c, bytes);
+  if (*split) *split = ws_try(c, bytes, bytes + copies);
+  return *split ? ACE_OK : ws_begin(c, bytes);
 }
 
 }  // namespace

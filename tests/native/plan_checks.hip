@@ -26,7 +26,7 @@ namespace {
 
 struct Device {
   size_t free_bytes = (size_t)1 << 40;
-  std::map<char*, size_t> live;
+  std::map<char*, size_t> live;  // allocations
   char* next = (char*)0x100000000000;
   int mallocs = 0, refused = 0;
   bool capturing = false;
@@ -336,12 +336,92 @@ void fewer_bands_than_orbitals() {
         }
 }
 
+// The optional copies of the split-line passes: what a call does where memory,
+// a capture or a captured graph leaves no room for them.
+void optional_copies() {
+  const int n = 48, nocc = 20, nband = 24;
+  const ace_grid g = cubic(n);
+  const long ng = (long)n * n * n;
+  const size_t everything = dev.free_bytes;
+  int copies = 0;
+  const auto build = [&](ace_ctx c, int bands) {
+    copies = 0;
+    on_launch = [&](const Launch& l) { copies += l.is("k_orbital_transpose"); };
+    const ace_status st = ace_build_W(c, &g, ACE_FP64, array_at(0), nocc, ng, array_at(0), bands,
+                                      ng, array_at(1), ng, 1.0);
+    on_launch = nullptr;
+    return st;
+  };
+  const auto fresh = [&](bool sized) {
+    ace_ctx c = nullptr;
+    EXPECT(ace_create(&c, nullptr, nullptr) == ACE_OK);
+    if (sized) {  // a workspace for the build without copies
+      ace_set_tuning(c, ACE_TUNE_FFT_SHAPE, 4);
+      EXPECT(build(c, nband) == ACE_OK && copies == 0);
+      ace_set_tuning(c, ACE_TUNE_FFT_SHAPE, 0);
+    }
+    return c;
+  };
+  {
+    g_case = "memory for the workspace, none for copies";
+    ace_ctx c = fresh(true);
+    void* ws = c->ws;
+    dev.free_bytes = 1 << 20;
+    dev.mallocs = 0;
+    EXPECT(build(c, nband) == ACE_OK && copies == 0);
+    EXPECT(c->ws == ws && dev.live.count((char*)ws) == 1);
+    EXPECT(dev.mallocs == 1);
+    EXPECT(std::strlen(ace_last_error(c)) == 0);
+    EXPECT(build(c, nband) == ACE_OK && dev.mallocs == 1);  // not asked for again
+    double* e = (double*)array_at(2);
+    EXPECT(ace_exchange_energy(c, &g, ACE_FP64, array_at(0), nocc, ng, nullptr, 0, 0, e) == ACE_OK);
+    EXPECT(c->ws == ws && std::strlen(ace_last_error(c)) == 0);
+    dev.free_bytes = everything;
+    EXPECT(ace_reserve(c, &g, ACE_FP64, nocc, nband, 1) == ACE_OK);
+    EXPECT(build(c, nband) == ACE_OK && copies == 1);
+    ace_destroy(c);
+  }
+  {
+    g_case = "the first call, memory for the workspace alone";
+    ace_ctx c = fresh(true);
+    const size_t bytes = c->ws_bytes;
+    ace_destroy(c);
+    EXPECT(dev.live.empty());
+    dev.free_bytes = bytes;
+    c = fresh(false);
+    EXPECT(build(c, nband) == ACE_OK && copies == 0);
+    EXPECT(c->ws_bytes == bytes && std::strlen(ace_last_error(c)) == 0);
+    ace_destroy(c);
+    dev.free_bytes = everything;
+  }
+  {
+    g_case = "under capture, and after it";
+    ace_ctx c = fresh(true);
+    void* ws = c->ws;
+    dev.capturing = true;
+    EXPECT(build(c, nband) == ACE_OK && copies == 0);
+    EXPECT(std::strlen(ace_last_error(c)) == 0);
+    dev.capturing = false;
+    EXPECT(build(c, nband) == ACE_OK && c->ws == ws);  // the graph holds its address
+    ace_destroy(c);
+  }
+  {
+    g_case = "room: the copies are used, the old buffer goes";
+    ace_ctx c = fresh(true);
+    EXPECT(build(c, nband) == ACE_OK && copies == 1);
+    EXPECT(dev.live.size() == 1 && dev.live.count((char*)c->ws) == 1);
+    ace_destroy(c);
+  }
+  EXPECT(dev.live.empty() && dev.free_bytes == everything);
+}
+
 }  // namespace
 
 int main() {
   setvbuf(stdout, nullptr, _IOLBF, 0);
   shared_orbitals_on_split_lines();
   fewer_bands_than_orbitals();
+  optional_copies();
   std::printf("plan checks: %d checks, %d failures\n", g_checks, g_failures);
   return g_failures ? 1 : 0;
 }
