@@ -191,12 +191,14 @@ struct BuildPlan {
   size_t pairs_alloc;
   size_t orb_bytes;  // transposed orbitals of a slab pass on split lines, or 0
   size_t bytes;      // of everything
+  size_t size(bool copies) const { return copies ? bytes : bytes - orb_bytes; }
 };
 BuildPlan plan_build(ace_ctx c, const GridInfo& g, size_t elem_bytes, int nocc, int nband,
                      bool one_array);
 // Workspace of ace_apply_h for n_x vectors (exchange from n_xi projection
-// vectors or n_phi orbitals; 0 for none).
-size_t hamiltonian_ws_bytes(ace_ctx c, const GridInfo& g, size_t eb, int nx, int nxi, int nphi);
+// vectors or n_phi orbitals; 0 for none), with or without the optional copies.
+size_t hamiltonian_ws_bytes(ace_ctx c, const GridInfo& g, size_t eb, int nx, int nxi, int nphi,
+                            bool copies);
 // Workspace of the Rayleigh-Ritz step on n vectors.
 size_t ritz_ws_bytes(int n, long ng);
 // Workspace the compression takes for n_band vectors; alias_eb > 0 adds the
@@ -206,7 +208,7 @@ size_t compress_ws_bytes(int nb, long ng, size_t alias_eb = 0);
 size_t orth_ws_bytes(int n, long ng, size_t eb);
 // Direct exchange energy: pairs per chunk and workspace.
 long energy_chunk(ace_ctx c, const GridInfo& g, size_t eb, int nocc);
-size_t energy_direct_ws_bytes(ace_ctx c, const GridInfo& g, size_t eb, int nocc);
+size_t energy_direct_ws_bytes(ace_ctx c, const GridInfo& g, size_t eb, int nocc, bool copies);
 size_t default_pair_budget_bytes();
 
 // Profiling hooks around one launch.

@@ -623,18 +623,23 @@ ACE_EXPORT ace_status ace_reserve(ace_ctx c, const ace_grid* grid, ace_prec prec
     need = std::max(need, mat + gemm_cn_scratch_bytes(max_nband, max_nocc, gh.ng));
     return ws_begin(c, need);
   }
-  size_t need = std::max(plan_build(c, g, eb, max_nocc, max_nband, true).bytes,
-                         plan_build(c, g, eb, max_nocc, max_nband, false).bytes);
-  need = std::max(need, plan_build(c, g, eb, max_nocc, max_nocc, true).bytes);
-  need = std::max(need, compress_ws_bytes(max_nband, g.ng, eb));
-  need = std::max(need, orth_ws_bytes(nmax, g.ng, eb));
-  need = std::max(need, mat + gemm_cn_scratch_bytes(max_nband, std::max(max_nx, 1), g.ng));
-  need = std::max(need, mat + gemm_cn_scratch_bytes(max_nband, max_nocc, g.ng));
-  need = std::max(need, energy_direct_ws_bytes(c, g, eb, max_nocc));
-  // ace_apply_h (exchange from xi or from the occupied orbitals) and the
-  // Rayleigh-Ritz step of the eigensolver on up to max(n_band, n_x) vectors
-  need = std::max(need, hamiltonian_ws_bytes(c, g, eb, std::max(max_nx, 1), max_nband, max_nocc));
-  need = std::max(need, ritz_ws_bytes(std::min(nmax, 512), g.ng));
+  const auto need_of = [&](bool copies) {
+    size_t need = std::max(plan_build(c, g, eb, max_nocc, max_nband, true).size(copies),
+                           plan_build(c, g, eb, max_nocc, max_nband, false).size(copies));
+    need = std::max(need, plan_build(c, g, eb, max_nocc, max_nocc, true).size(copies));
+    need = std::max(need, compress_ws_bytes(max_nband, g.ng, eb));
+    need = std::max(need, orth_ws_bytes(nmax, g.ng, eb));
+    need = std::max(need, mat + gemm_cn_scratch_bytes(max_nband, std::max(max_nx, 1), g.ng));
+    need = std::max(need, mat + gemm_cn_scratch_bytes(max_nband, max_nocc, g.ng));
+    need = std::max(need, energy_direct_ws_bytes(c, g, eb, max_nocc, copies));
+    // ace_apply_h (exchange from xi or from the occupied orbitals) and the
+    // Rayleigh-Ritz step of the eigensolver on up to max(n_band, n_x) vectors
+    need = std::max(need, hamiltonian_ws_bytes(c, g, eb, std::max(max_nx, 1), max_nband, max_nocc,
+                                               copies));
+    return std::max(need, ritz_ws_bytes(std::min(nmax, 512), g.ng));
+  };
+  const size_t need = need_of(false);
+  if (ws_try(c, need, need_of(true))) return ACE_OK;  // else without the optional copies
   return ws_begin(c, need);
 }
 

@@ -24,7 +24,7 @@ constexpr int kDefaultBatchForm = 1;
 
 struct Planned {
   GridInfo g;
-  size_t bytes;
+  size_t bytes, copies;  // the call's workspace, and what optional copies add to it
   double cost;
   int branch;
 };
@@ -168,17 +168,22 @@ ace_status record_instance(ace_ctx c, const ace_instance& in, const GridInfo& g)
 ace_status batched_launches(ace_ctx c, int n_inst, const ace_instance* inst,
                             std::vector<Planned>& plan) {
   const int nbr = std::min(c->branches, n_inst);
-  std::vector<char> all(n_inst, 1);
-  std::vector<size_t> bytes(n_inst);
-  for (int k = 0; k < n_inst; ++k) bytes[k] = plan[k].bytes;
-  const std::vector<size_t> bbytes = assign_branches(plan, all, bytes, nbr);
-  std::vector<size_t> boff(nbr, 0);
-  size_t total = 0;
-  for (int b = 0; b < nbr; ++b) {
-    boff[b] = total;
-    total += bbytes[b];
-  }
-  ACE_TRY(ws_begin(c, total));  // grows the workspace before any capture
+  const std::vector<char> all(n_inst, 1);
+  std::vector<size_t> bbytes, boff(nbr);
+  // slices of the branches, with or without room for the optional copies
+  const auto slices = [&](bool copies) {
+    std::vector<size_t> bytes(n_inst);
+    for (int k = 0; k < n_inst; ++k) bytes[k] = plan[k].bytes + (copies ? plan[k].copies : 0);
+    bbytes = assign_branches(plan, all, bytes, nbr);
+    size_t total = 0;
+    for (int b = 0; b < nbr; ++b) {
+      boff[b] = total;
+      total += bbytes[b];
+    }
+    return total;
+  };
+  const size_t need = slices(false);
+  if (!ws_try(c, need, slices(true))) ACE_TRY(ws_begin(c, slices(false)));
   ACE_TRY(ensure_branches(c, nbr));
   std::vector<unsigned char> key = make_key(c, n_inst, inst, nbr, 1);
   if (c->graph_exec && key == c->graph_key) {
@@ -313,7 +318,7 @@ ace_status batched_persistent(ace_ctx c, int n_inst, const ace_instance* inst,
       const BuildPlan bp = plan_build(c, plan[k].g, ebs[k], in.n_occ, in.n_band,
                                       in.psi == in.phi && in.ld_psi == in.ld_phi);
       bk.off.push_back(bk.total);
-      bk.bytes.push_back(align_up(bp.bytes - bp.orb_bytes, 256));
+      bk.bytes.push_back(align_up(bp.size(false), 256));
       bk.total += bk.bytes.back();
     }
     c->budget_cap = 0;
@@ -491,7 +496,9 @@ ACE_EXPORT ace_status ace_build_W_batched(ace_ctx c, int n_inst, const ace_insta
     }
     const BuildPlan bp = plan_build(c, g, eb, in.n_occ, in.n_band,
                                     in.psi == in.phi && in.ld_psi == in.ld_phi);
-    plan[k].bytes = std::max(bp.bytes, in.xi ? compress_ws_bytes(in.n_band, g.ng) : (size_t)0);
+    const size_t after = in.xi ? compress_ws_bytes(in.n_band, g.ng) : 0;
+    plan[k].bytes = std::max(bp.size(false), after);
+    plan[k].copies = std::max(bp.bytes, after) - plan[k].bytes;
     plan[k].cost = (double)in.n_occ * in.n_band * (double)g.ng;
   }
   // Instances run concurrently: no instance's output may overlap another

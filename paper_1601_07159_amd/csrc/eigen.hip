@@ -532,14 +532,15 @@ ace_status hamiltonian_t(ace_ctx c, const GridInfo& g, const T* vloc, const cx<T
   return ACE_OK;
 }
 
-size_t hamiltonian_ws_bytes(ace_ctx c, const GridInfo& g, size_t eb, int nx, int nxi, int nphi) {
+size_t hamiltonian_ws_bytes(ace_ctx c, const GridInfo& g, size_t eb, int nx, int nxi, int nphi,
+                            bool copies) {
   GridInfo gk = g;
   gk.kind = kKindKinetic;
   size_t need = align_up((size_t)g.ng * eb, 256) + plan_build(c, gk, eb, 1, nx, false).bytes;
   if (nxi > 0)
     need = std::max(need, align_up((size_t)nxi * nx * sizeof(cx<double>), 256) +
                               gemm_cn_partial_bytes(nxi, nx, g.ng, eb, kFp32Chunks, false));
-  if (nphi > 0) need = std::max(need, plan_build(c, g, eb, nphi, nx, false).bytes);
+  if (nphi > 0) need = std::max(need, plan_build(c, g, eb, nphi, nx, false).size(copies));
   return need;
 }
 

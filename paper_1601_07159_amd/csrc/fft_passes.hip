@@ -899,10 +899,10 @@ long energy_chunk(ace_ctx c, const GridInfo& g, size_t eb, int nocc) {
   return std::min(chunk, total);
 }
 
-size_t energy_direct_ws_bytes(ace_ctx c, const GridInfo& g, size_t eb, int nocc) {
+size_t energy_direct_ws_bytes(ace_ctx c, const GridInfo& g, size_t eb, int nocc, bool copies) {
   const long total = (long)nocc * (nocc + 1) / 2;
   const long tiles = ((long)g.n * g.n + 63) / 64;
-  return slab_split_bytes(g, eb, total, nocc) +
+  return (copies ? slab_split_bytes(g, eb, total, nocc) : 0) +
          align_up(((size_t)total * tiles + kSumBlocks) * sizeof(double), 256) +
          align_up((size_t)energy_chunk(c, g, eb, nocc) * g.ng * eb, 256);
 }
@@ -1350,7 +1350,7 @@ ace_status energy_direct_n(ace_ctx c, const GridInfo& g, const cx<T>* phi, int n
   ace_status st;
   const size_t copies = slab_split_bytes(g, sizeof(cx<T>), total, nocc);
   bool split = copies && split_allowed(c, N, sizeof(cx<T>));
-  if ((st = split_ws_begin(c, energy_direct_ws_bytes(c, g, sizeof(cx<T>), nocc) - copies, copies,
+  if ((st = split_ws_begin(c, energy_direct_ws_bytes(c, g, sizeof(cx<T>), nocc, false), copies,
                            &split)) != ACE_OK)
     return st;
   double* partial = (double*)ws_take(c, part_bytes, &st);

@@ -412,6 +412,42 @@ void optional_copies() {
     EXPECT(dev.live.size() == 1 && dev.live.count((char*)c->ws) == 1);
     ace_destroy(c);
   }
+  {
+    g_case = "a reservation, memory for all but the copies";
+    ace_ctx c = fresh(false);
+    EXPECT(ace_reserve(c, &g, ACE_FP64, nocc, nband, nband) == ACE_OK);
+    const size_t all = c->ws_bytes;
+    ace_destroy(c);
+    c = fresh(false);
+    dev.free_bytes = all - 1;
+    EXPECT(ace_reserve(c, &g, ACE_FP64, nocc, nband, nband) == ACE_OK);
+    EXPECT(c->ws_bytes < all && std::strlen(ace_last_error(c)) == 0);
+    dev.mallocs = 0;
+    EXPECT(build(c, nband) == ACE_OK && dev.mallocs == 0);
+    ace_destroy(c);
+    dev.free_bytes = everything;
+  }
+  {
+    g_case = "a batch, memory for all but the copies";
+    std::vector<ace_instance> inst(3);
+    for (int k = 0; k < 3; ++k) {
+      inst[k] = ace_instance{g, ACE_FP64, array_at(4 * k), nocc, ng, array_at(4 * k), nband, ng,
+                             array_at(4 * k + 1), ng, array_at(4 * k + 2), ng,
+                             (int*)array_at(4 * k + 3), 1.0};
+    }
+    ace_ctx c = fresh(false);
+    EXPECT(ace_build_W_batched(c, 3, inst.data()) == ACE_OK);
+    const size_t all = c->ws_bytes;
+    ace_destroy(c);
+    c = fresh(false);
+    dev.free_bytes = all - 1;
+    EXPECT(ace_build_W_batched(c, 3, inst.data()) == ACE_OK);
+    EXPECT(c->ws_bytes < all && std::strlen(ace_last_error(c)) == 0);
+    dev.mallocs = 0;
+    EXPECT(ace_build_W_batched(c, 3, inst.data()) == ACE_OK && dev.mallocs == 0);
+    ace_destroy(c);
+    dev.free_bytes = everything;
+  }
   EXPECT(dev.live.empty() && dev.free_bytes == everything);
 }
 
