@@ -188,6 +188,7 @@ struct BuildPlan {
   bool sym;       // i <-> j symmetry on the occupied block
   int symblk;     // 0: the whole occupied triangle is one chunk; else block size
   bool merged;    // triangle and the extra bands' rectangle form one chunk
+  long pairs;     // transformed by the whole build
   size_t pairs_alloc;
   size_t orb_bytes;  // transposed orbitals of a slab pass on split lines, or 0
   size_t bytes;      // of everything

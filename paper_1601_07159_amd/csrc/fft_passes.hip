@@ -853,8 +853,8 @@ int line_shape(ace_ctx c, int n, int eb) {
 // pass at N = 72 (quads: 1,512 -> 1,267 us at 24 orbitals).  Below, one thread
 // per line runs at the copy rate already.  (kSplitSlabN, kSplitPlaneN)
 
-// FP64 passes over at most so many planes (slabs) run on quads, whose waves are
-// four times as many: below some ten planes per CU a pass lasts as long as one
+// FP64 builds of at most so many planes (slabs) in all run on quads, whose waves
+// are four times as many: below some ten planes per CU a pass lasts as long as one
 // plane takes.  Builds of 8 to 24 orbitals against the forms for more planes:
 // 24^3 31.1 -> 28.6 us (36 pairs), 43.3 -> 42.0 (105), but 46.8 -> 53.7 (136);
 // 32^3 98.4 -> 83.1 (136), 159 -> 145 (300), 265 -> 257 (528); 40^3 65.6 -> 60.4
@@ -968,10 +968,10 @@ BuildPlan plan_build(ace_ctx c, const GridInfo& g, size_t eb, int nocc, int nban
   pl.B = B;
   pl.A = (int)std::max<long>(1, std::min<long>(nocc, maxpairs / B));
   pl.pairs_alloc = std::max<size_t>((size_t)pl.A * pl.B, (size_t)sym_alloc);
+  pl.pairs = pl.sym ? tri + (long)nocc * (nband - nocc) : (long)nocc * nband;
   // transposed copies: of the one array's orbitals, or of both arrays'
-  pl.orb_bytes = slab_split_bytes(
-      g, eb, pl.sym ? tri + (long)nocc * (nband - nocc) : (long)nocc * nband,
-      one_array ? std::max(nocc, nband) : (long)nocc + nband);
+  pl.orb_bytes = slab_split_bytes(g, eb, pl.pairs,
+                                  one_array ? std::max(nocc, nband) : (long)nocc + nband);
   pl.bytes = align_up(pl.pairs_alloc * pair_bytes, 256) + pl.orb_bytes;
   return pl;
 }
@@ -1005,6 +1005,7 @@ BuildPlan plan_build_real(ace_ctx c, const GridInfo& g, size_t cx_bytes, int noc
     pl.merged = true;
     pl.A = nocc;
     pl.B = nband;
+    pl.pairs = sym_units;
     pl.pairs_alloc = (size_t)sym_units;
   } else {
     int B = jblock > 0 ? (int)std::min<long>(nband, jblock) : nband;
@@ -1013,6 +1014,7 @@ BuildPlan plan_build_real(ace_ctx c, const GridInfo& g, size_t cx_bytes, int noc
     pl.B = B;
     pl.A = (int)std::min<long>(nocc, 2 * am);
     pl.sym = false;
+    pl.pairs = (long)((nocc + 1) / 2) * nband;
     pl.pairs_alloc = (size_t)((pl.A + 1) / 2) * pl.B;
   }
   pl.bytes = align_up(pl.pairs_alloc * unit_bytes, 256);
@@ -1046,16 +1048,18 @@ template <int N, typename T>
 constexpr bool kOctOk = N % 8 == 0 && N >= 16;
 
 // Form of the slab pass on natural orbitals (plane_pass false) or of the plane
-// pass: 1, 2 (plane pass), 4, 8 or 16 as above.  The plane pass on split lines
+// pass: 1, 2 (plane pass), 4, 8 or 16 as above, for a build (or energy) of `all`
+// pairs: the same for its every chunk, so that results do not depend on how a
+// pair budget or a band block cuts it.  The plane pass on split lines
 // against the former defaults: 72^3 FP32 1.79 against 2.39 ms (quads) per 1,146
 // pairs, 64^3 FP32 1.31 against 1.37 ms per 1,800; 40^3 FP64 0.55 against
 // 0.80 ms (one thread per line) per 1,353 pairs.
 template <int N, typename T>
-int pass_form(ace_ctx c, bool plane_pass, long np) {
+int pass_form(ace_ctx c, bool plane_pass, long all) {
   const int sh = line_shape(c, N, (int)sizeof(cx<T>));
   if (sh == 8) return kOctOk<N, T> ? 8 : 4;
   if (sh == 1 || sh == 4 || sh == 16) return sh;
-  if (np * N <= quad_planes(N, sizeof(cx<T>))) return 4;
+  if (all * N <= quad_planes(N, sizeof(cx<T>))) return 4;
   if (plane_pass) return N >= kSplitPlaneN<T> ? 2 : 1;
   return N >= (sizeof(T) == 8 ? 64 : 72) ? 4 : 1;
 }
@@ -1067,7 +1071,7 @@ int pass_form(ace_ctx c, bool plane_pass, long np) {
 // of the plane's column loads cost more than the full waves gain.
 template <int N, typename T>
 ace_status fwd_slab(ace_ctx c, const cx<T>* phi, long ldphi, const cx<T>* psi, long ldpsi,
-                    cx<T>* buf, int mode, int i0, int A, int j0, long p0, int np) {
+                    cx<T>* buf, int mode, int i0, int A, int j0, long p0, int np, long all) {
   if (c->record) {
     // the persistent kernel runs the one-thread-per-line form
     ace_plaunch l{};
@@ -1088,7 +1092,7 @@ ace_status fwd_slab(ace_ctx c, const cx<T>* phi, long ldphi, const cx<T>* psi, l
     return ACE_OK;
   }
   const dim3 grid(xcd_pad((long)N * np));
-  const int form = pass_form<N, T>(c, false, np);
+  const int form = pass_form<N, T>(c, false, all);
   if constexpr (kOctOk<N, T>)
     if (form == 8)
       return launch(c, "pair_fwd_slab", k_pair_fwd_slab_oct<N, T>, grid, dim3(8 * N), 0, phi,
@@ -1106,7 +1110,7 @@ ace_status fwd_slab(ace_ctx c, const cx<T>* phi, long ldphi, const cx<T>* psi, l
 }
 
 template <int N, typename T>
-ace_status plane(ace_ctx c, cx<T>* buf, const ace_kspec& ks, int np) {
+ace_status plane(ace_ctx c, cx<T>* buf, const ace_kspec& ks, int np, long all) {
   if (c->record) {
     ace_plaunch l{};
     l.kind = kPassPlane;
@@ -1118,7 +1122,7 @@ ace_status plane(ace_ctx c, cx<T>* buf, const ace_kspec& ks, int np) {
     return ACE_OK;
   }
   const dim3 grid(xcd_pad((long)N * np));
-  const int form = pass_form<N, T>(c, true, np);
+  const int form = pass_form<N, T>(c, true, all);
   if constexpr (N >= kSplitPlaneN<T>)
     if (form == 2) return split_plane<T>(c, N, buf, ks, np);
   if constexpr (kOctOk<N, T>)
@@ -1224,13 +1228,13 @@ ace_status build_W_n(ace_ctx c, const GridInfo& g, const cx<T>* phi, int nocc, l
     if (split)
       return split_slab<T>(c, N, phi_t, own ? psi_t : phi_t, buf, mode, i0, Ac, j0, 0L, np);
     return fwd_slab<N, T>(c, phi, ldphi, own ? psi : phi, own ? ldpsi : ldphi, buf, mode, i0, Ac, j0,
-                          0L, np);
+                          0L, np, pl.pairs);
   };
   int jstart = 0;
   if (pl.merged) {
     const long all = (long)nocc * (nocc + 1) / 2 + (long)nocc * (nband - nocc);
     if ((st = slab(true, 3, 0, nocc, nocc, (int)all)) != ACE_OK) return st;
-    if ((st = plane<N, T>(c, buf, ks, (int)all)) != ACE_OK) return st;
+    if ((st = plane<N, T>(c, buf, ks, (int)all, pl.pairs)) != ACE_OK) return st;
     return accum<N, T>(c, phi, ldphi, buf, W, ldW, 0, nocc, 0, nband, acc0, 3);
   }
   if (sym && pl.symblk == 0) {
@@ -1238,7 +1242,7 @@ ace_status build_W_n(ace_ctx c, const GridInfo& g, const cx<T>* phi, int nocc, l
     // accumulates all i from it (u_ij = conj(u_ji))
     const long tri = (long)nocc * (nocc + 1) / 2;
     if ((st = slab(false, 1, 0, 1, 0, (int)tri)) != ACE_OK) return st;
-    if ((st = plane<N, T>(c, buf, ks, (int)tri)) != ACE_OK) return st;
+    if ((st = plane<N, T>(c, buf, ks, (int)tri, pl.pairs)) != ACE_OK) return st;
     if ((st = accum<N, T>(c, phi, ldphi, buf, W, ldW, 0, nocc, 0, nocc, acc0, 1)) != ACE_OK)
       return st;
     jstart = nocc;
@@ -1254,7 +1258,7 @@ ace_status build_W_n(ace_ctx c, const GridInfo& g, const cx<T>* phi, int nocc, l
         if (I == J) {
           const int np = ni * (ni + 1) / 2;
           if ((st = slab(false, 1, i0, 1, i0, np)) != ACE_OK) return st;
-          if ((st = plane<N, T>(c, buf, ks, np)) != ACE_OK) return st;
+          if ((st = plane<N, T>(c, buf, ks, np, pl.pairs)) != ACE_OK) return st;
           if ((st = accum<N, T>(c, phi, ldphi, buf, W, ldW, i0, ni, i0, ni, (int)started[I], 1)) !=
               ACE_OK)
             return st;
@@ -1262,7 +1266,7 @@ ace_status build_W_n(ace_ctx c, const GridInfo& g, const cx<T>* phi, int nocc, l
         } else {
           const int np = ni * nj;
           if ((st = slab(false, 0, i0, ni, j0, np)) != ACE_OK) return st;
-          if ((st = plane<N, T>(c, buf, ks, np)) != ACE_OK) return st;
+          if ((st = plane<N, T>(c, buf, ks, np, pl.pairs)) != ACE_OK) return st;
           // bands of J from the orbitals of I, then bands of I from those of J
           if ((st = accum<N, T>(c, phi, ldphi, buf, W, ldW, i0, ni, j0, nj, (int)started[J], 0)) !=
               ACE_OK)
@@ -1282,7 +1286,7 @@ ace_status build_W_n(ace_ctx c, const GridInfo& g, const cx<T>* phi, int nocc, l
       const int Ac = std::min(A, nocc - i0);
       const int np = Ac * Bc;
       if ((st = slab(true, 0, i0, Ac, j0, np)) != ACE_OK) return st;
-      if ((st = plane<N, T>(c, buf, ks, np)) != ACE_OK) return st;
+      if ((st = plane<N, T>(c, buf, ks, np, pl.pairs)) != ACE_OK) return st;
       if ((st = accum<N, T>(c, phi, ldphi, buf, W, ldW, i0, Ac, j0, Bc, (i0 > 0 || accumulate) ? 1 : 0, 0)) !=
           ACE_OK)
         return st;
@@ -1312,7 +1316,7 @@ ace_status build_W_real_n(ace_ctx c, const GridInfo& g, const T* phi, int nocc, 
     if ((st = launch(c, "pair_fwd_real", k_pair_fwd_real_t1<N, T>, dim3(xcd_pad((long)N * nu)),
                      dim3(N), 0, phi, ldphi, psi, ldpsi, buf, 0, nocc, G, nocc, nu, 1)) != ACE_OK)
       return st;
-    if ((st = plane<N, T>(c, buf, ks, nu)) != ACE_OK) return st;
+    if ((st = plane<N, T>(c, buf, ks, nu, pl.pairs)) != ACE_OK) return st;
     const int nrows = G + (nband - nocc);
     return launch(c, "pencil_accum_real", k_pencil_accum_real_sym<N, T>,
                   dim3(xcd_pad((long)TILES * nrows)), dim3(64), 0, phi, ldphi, (const cx<T>*)buf,
@@ -1328,7 +1332,7 @@ ace_status build_W_real_n(ace_ctx c, const GridInfo& g, const T* phi, int nocc, 
                        dim3(xcd_pad((long)N * nu)), dim3(N), 0, phi, ldphi, psi, ldpsi, buf, i0,
                        Ac, Am, j0, nu, 0)) != ACE_OK)
         return st;
-      if ((st = plane<N, T>(c, buf, ks, nu)) != ACE_OK) return st;
+      if ((st = plane<N, T>(c, buf, ks, nu, pl.pairs)) != ACE_OK) return st;
       if ((st = launch(c, "pencil_accum_real", k_pencil_accum_real<N, T>,
                        dim3(xcd_pad((long)TILES * Bc)), dim3(64), 0, phi, ldphi,
                        (const cx<T>*)buf, W, ldW, i0, Ac, Am, j0, Bc, i0 > 0 ? 1 : 0)) != ACE_OK)
@@ -1366,7 +1370,7 @@ ace_status energy_direct_n(ace_ctx c, const GridInfo& g, const cx<T>* phi, int n
   for (long p0 = 0; p0 < total; p0 += chunk) {
     const int np = (int)std::min(chunk, total - p0);
     st = orb ? split_slab<T>(c, N, orb, orb, buf, 1, 0, 1, 0, p0, np)
-             : fwd_slab<N, T>(c, phi, ldphi, phi, ldphi, buf, 1, 0, 1, 0, p0, np);
+             : fwd_slab<N, T>(c, phi, ldphi, phi, ldphi, buf, 1, 0, 1, 0, p0, np, total);
     if (st != ACE_OK) return st;
     if ((st = launch(c, "pencil_energy", k_pencil_energy<N, T>, dim3(np * TILES), dim3(256), 0,
                      (const cx<T>*)buf, ks, p0, partial)) != ACE_OK)

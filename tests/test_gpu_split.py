@@ -126,3 +126,23 @@ def test_captured_after_reserve(n, prec, nocc, nband):
     del graph
     ctx.close()
     ref.close()
+
+
+@pytest.mark.parametrize("n,nocc,nband", [(24, 10, 40), (32, 12, 40), (40, 10, 30)])
+def test_chunks_take_the_form_of_the_build(n, nocc, nband):
+    """FP64 builds of many pairs cut into bands blocks of few: the same lines, so
+    the same results bit for bit (every band's orbitals stay in one chunk); the
+    direct energy in chunks of pairs likewise."""
+    import torch
+    from paper_1601_07159_amd import ace
+    print(f"band blocks n={n} nocc={nocc} nband={nband}", flush=True)
+    gg = ggrid(n, 0.43 * n, "erfc", 0.2)
+    x = to_gpu(synth.smooth_orbitals(n, 0.43 * n, nband, seed=n), "fp64")
+    phi = x[:nocc].clone()
+    ctx = ace.Context()
+    W, e = ctx.build_W(phi, x, gg, "fp64"), ctx.exchange_energy(x, gg, "fp64")
+    ctx.set_tuning("jblock", 8)
+    assert torch.equal(ctx.build_W(phi, x, gg, "fp64"), W)
+    ctx.set_pair_budget(50 * n ** 3 * 16)
+    assert torch.equal(ctx.exchange_energy(x, gg, "fp64"), e)
+    ctx.close()
