@@ -146,3 +146,28 @@ def test_chunks_take_the_form_of_the_build(n, nocc, nband):
     ctx.set_pair_budget(50 * n ** 3 * 16)
     assert torch.equal(ctx.exchange_energy(x, gg, "fp64"), e)
     ctx.close()
+
+
+@pytest.mark.parametrize("n,prec,nocc,nband", [
+    (64, "real32", 17, 20), (64, "real32", 9, 9), (72, "real32", 12, 13),  # plane pass alone
+    (72, "fp32", 22, 25), (72, "fp32", 9, 9)])                             # slab and plane
+def test_fp32_split_lines_are_the_quads_bit_for_bit(n, prec, nocc, nband):
+    """FP32 lines round every product as the quad forms do."""
+    import torch
+    from paper_1601_07159_amd import ace
+    print(f"fp32 split lines n={n} prec={prec} nocc={nocc} nband={nband}", flush=True)
+    for kind, mu in (("coulomb", 0.0), ("erfc", 0.2)):
+        gg = ggrid(n, 0.43 * n, kind, mu)
+        x = to_gpu(synth.smooth_orbitals(n, 0.43 * n, nband, seed=n + nocc), prec)
+        gen = torch.Generator(device="cuda").manual_seed(n)
+        x += 1e-3 * torch.randn(x.shape, dtype=x.dtype, device="cuda", generator=gen)
+        out = []
+        for shape in (0, 4):
+            ctx = ace.Context()
+            ctx.set_tuning("fft_shape", shape)
+            out.append([ctx.build_W(x[:nocc], x, gg, prec), ctx.build_W(x[:nocc].clone(), x, gg, prec)])
+            if prec == "fp32":
+                out[-1].append(ctx.exchange_energy(x[:nocc].contiguous(), gg, prec))
+            ctx.close()
+        for a, b in zip(*out):
+            assert torch.equal(a, b)
