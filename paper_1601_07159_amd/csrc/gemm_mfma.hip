@@ -1238,35 +1238,50 @@ size_t gemm_cn_scratch_bytes(int na, int nb, long K) {
   return align_up(b32 > b64 ? b32 : b64, 256);
 }
 
+// What a reduction product's data type and mode decide.
+struct CnForm {
+  bool f64, bf16_split;  // FP64 sums; BF16 halves
+  bool blocks;           // may take k_cn_blocks
+  int max_waves, cu_waves;
+  size_t acc_bytes;
+};
+
+static CnForm cn_form(size_t data_bytes, CnMode mode) {
+  CnForm f;
+  const bool cx64 = data_bytes == sizeof(cx<double>);
+  f.f64 = cx64 || mode == kFp64 || mode == kFp64Tiles;
+  f.bf16_split = !cx64 && mode == kBf16Split;
+  f.blocks = mode == kFp32Chunks || (f.f64 && mode != kFp64Tiles);
+  f.max_waves = f.f64 ? 8 : f.bf16_split ? kBf16Waves : 16;
+  f.cu_waves = f.f64 ? 12 : f.bf16_split ? kBf16Waves : 16;
+  f.acc_bytes = f.f64 ? sizeof(cx<double>) : sizeof(cx<float>);
+  return f;
+}
+
 size_t gemm_cn_partial_bytes(int na, int nb, long K, size_t data_bytes, CnMode mode, bool herm) {
-  const bool bf16_split = data_bytes == sizeof(cx<float>) && mode == kBf16Split;
-  const bool f64 = data_bytes == sizeof(cx<double>) || mode == kFp64;
-  const int max_waves = f64 ? 8 : bf16_split ? kBf16Waves : 16;
-  const int cu_waves = f64 ? 12 : bf16_split ? kBf16Waves : 16;
-  CnShape s = cn_shape(na, nb, K, max_waves, cu_waves);
-  if (herm && na == nb) herm_shape(na, K, max_waves, cu_waves, &s);
-  if (f64 || mode == kFp32Chunks)
-    s.ks = std::max(s.ks, gram_splits(na, nb, K, data_bytes, f64 ? 16 : 8, herm && na == nb));
-  const size_t part_eb = f64 ? sizeof(cx<double>) : sizeof(cx<float>);
-  return align_up((size_t)s.ks * na * nb * part_eb, 256);
+  const CnForm f = cn_form(data_bytes, mode);
+  CnShape s = cn_shape(na, nb, K, f.max_waves, f.cu_waves);
+  herm = herm && na == nb;
+  if (herm) herm_shape(na, K, f.max_waves, f.cu_waves, &s);
+  if (f.blocks) s.ks = std::max(s.ks, gram_splits(na, nb, K, data_bytes, f.acc_bytes, herm));
+  return align_up((size_t)s.ks * na * nb * f.acc_bytes, 256);
 }
 
 template <typename T>
 ace_status gemm_cn(ace_ctx c, const cx<T>* A, long lda, int na, const cx<T>* B, long ldb, int nb,
                    long K, double alpha, cx<double>* C, int ldc, CnMode mode,
                    bool real_part, bool herm) {
-  const bool bf16_split = std::is_same<T, float>::value && mode == kBf16Split;
-  const bool f64 = sizeof(T) == 8 || mode == kFp64 || mode == kFp64Tiles;
+  const CnForm f = cn_form(sizeof(cx<T>), mode);
   // the BF16-split kernel addresses a tile's 32 rows through a buffer
   // resource with 32-bit byte offsets
-  if (bf16_split && (lda > (1L << 31) / 256 || ldb > (1L << 31) / 256))
+  if (f.bf16_split && (lda > (1L << 31) / 256 || ldb > (1L << 31) / 256))
     return fail(c, ACE_E_UNSUPPORTED, "leading dimension too large for the BF16-split product");
   // Loads of 16 bytes: rows must start at multiples of that.
   GramShape gs;
   const bool aligned = ((uintptr_t)A | (uintptr_t)B | (uintptr_t)(lda * sizeof(cx<T>)) |
                         (uintptr_t)(ldb * sizeof(cx<T>))) % 16 == 0;
-  if (((f64 && mode != kFp64Tiles) || mode == kFp32Chunks) && aligned &&
-      gram_shape(na, nb, K, sizeof(cx<T>), f64 ? 16 : 8, A == B && lda == ldb && na == nb,
+  if (f.blocks && aligned &&
+      gram_shape(na, nb, K, sizeof(cx<T>), f.acc_bytes, A == B && lda == ldb && na == nb,
                  herm && na == nb, &gs)) {
     auto run = [&](auto acc, const char* name) -> ace_status {
       typedef decltype(acc) TAcc;
@@ -1281,25 +1296,22 @@ ace_status gemm_cn(ace_ctx c, const cx<T>* A, long lda, int na, const cx<T>* B, 
                     real_part ? 1 : 0, gs.herm ? 4 : 0);
     };
     if constexpr (sizeof(T) == 8) return run(double(0), "cn_mfma_f64");
-    else return f64 ? run(double(0), "cn_mfma_f32in_f64") : run(float(0), "cn_mfma_f32");
+    else return f.f64 ? run(double(0), "cn_mfma_f32in_f64") : run(float(0), "cn_mfma_f32");
   }
-  const int max_waves = f64 ? 8 : bf16_split ? kBf16Waves : 16;
-  const int cu_waves = f64 ? 12 : bf16_split ? kBf16Waves : 16;
-  CnShape s = cn_shape(na, nb, K, max_waves, cu_waves);
-  herm = herm && na == nb && herm_shape(na, K, max_waves, cu_waves, &s);
+  CnShape s = cn_shape(na, nb, K, f.max_waves, f.cu_waves);
+  herm = herm && na == nb && herm_shape(na, K, f.max_waves, f.cu_waves, &s);
   const int hm = herm ? 5 : 0;  // log2 of a tile's side
   ace_status st;
-  const size_t part_eb = f64 ? sizeof(cx<double>) : sizeof(cx<float>);
-  void* partial = ws_take(c, (size_t)s.ks * na * nb * part_eb, &st);
+  void* partial = ws_take(c, (size_t)s.ks * na * nb * f.acc_bytes, &st);
   if (!partial) return st;
   const dim3 grid((unsigned)s.gx, (unsigned)s.gy, (unsigned)s.ks);
   const dim3 block(64 * s.ta, s.tb);
   if constexpr (std::is_same<T, float>::value) {
-    if (bf16_split) {
+    if (f.bf16_split) {
       if ((st = launch(c, "cn_mfma_bf16x3", k_cn_mfma_bf16x3, grid, block, 0, A, lda, na, B, ldb,
                        nb, K, s.kchunk, (cx<float>*)partial, hm)) != ACE_OK)
         return st;
-    } else if (f64) {
+    } else if (f.f64) {
       if ((st = launch(c, "cn_mfma_f32in_f64", k_cn_mfma<float, double>, grid, block, 0, A, lda,
                        na, B, ldb, nb, K, s.kchunk, (cx<double>*)partial, hm)) != ACE_OK)
         return st;
@@ -1312,7 +1324,7 @@ ace_status gemm_cn(ace_ctx c, const cx<T>* A, long lda, int na, const cx<T>* B, 
                      ldb, nb, K, s.kchunk, (cx<double>*)partial, hm)) != ACE_OK)
       return st;
   }
-  if (f64)
+  if (f.f64)
     return launch(c, "reduce_partials", k_reduce_partials2<double>, dim3((na * nb + 63) / 64),
                   dim3(1024), 0, (const cx<double>*)partial, (int)s.ks, na, nb, alpha, C, ldc,
                   real_part ? 1 : 0, hm);

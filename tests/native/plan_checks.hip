@@ -451,6 +451,35 @@ void optional_copies() {
   EXPECT(dev.live.empty() && dev.free_bytes == everything);
 }
 
+// A reduction product fits the scratch that is stated for it, in every mode.
+template <typename T>
+void reduction_scratch() {
+  using namespace ace;
+  for (CnMode mode : {kNative, kBf16Split, kFp64, kFp64Tiles, kFp32Chunks})
+    for (long K : {512L, 13824L, 262144L})
+      for (int na : {1, 31, 48, 64, 81, 136, 161, 257, 600})
+        for (int nb : {1, 33, 64, 136, 257})
+          for (bool herm : {false, true}) {
+            if (sizeof(T) == 8 && mode == kBf16Split) continue;
+            const int n2 = herm ? na : nb;
+            g_case = "mode " + std::to_string(mode) + " K " + std::to_string(K) + " " +
+                     std::to_string(na) + " x " + std::to_string(n2);
+            ace_ctx c = nullptr;
+            EXPECT(ace_create(&c, nullptr, nullptr) == ACE_OK);
+            const cx<T>* A = (const cx<T>*)array_at(0);
+            const cx<T>* B = (const cx<T>*)array_at(1);
+            for (const cx<T>* second : {A, B}) {
+              const size_t part = gemm_cn_partial_bytes(na, n2, K, sizeof(cx<T>), mode, herm);
+              EXPECT(part <= gemm_cn_scratch_bytes(na, n2, K));
+              EXPECT(ws_begin(c, part) == ACE_OK);
+              EXPECT(gemm_cn<T>(c, A, K, na, second, K, n2, K, 1.0, (cx<double>*)array_at(2), na,
+                                mode, false, herm) == ACE_OK);
+              EXPECT(c->ws_used <= align_up(part, 256));
+            }
+            ace_destroy(c);
+          }
+}
+
 }  // namespace
 
 int main() {
@@ -458,6 +487,8 @@ int main() {
   shared_orbitals_on_split_lines();
   fewer_bands_than_orbitals();
   optional_copies();
+  reduction_scratch<float>();
+  reduction_scratch<double>();
   std::printf("plan checks: %d checks, %d failures\n", g_checks, g_failures);
   return g_failures ? 1 : 0;
 }
