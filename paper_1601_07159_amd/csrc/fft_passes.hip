@@ -854,11 +854,16 @@ int line_shape(ace_ctx c, int n, int eb) {
 // per line runs at the copy rate already.  (kSplitSlabN, kSplitPlaneN)
 
 // FP64 builds of at most so many planes (slabs) in all run on quads, whose waves
-// are four times as many: below some ten planes per CU a pass lasts as long as one
-// plane takes.  Builds of 8 to 24 orbitals against the forms for more planes:
-// 24^3 31.1 -> 28.6 us (36 pairs), 43.3 -> 42.0 (105), but 46.8 -> 53.7 (136);
-// 32^3 98.4 -> 83.1 (136), 159 -> 145 (300), 265 -> 257 (528); 40^3 65.6 -> 60.4
-// (36), 127 -> 118 (105), 333 -> 335 (300).  No gain at 16^3, none from 48^3.
+// are four times as many: while a CU has few planes, a pass lasts as long as one
+// plane takes.  How far that reaches depends on how full the waves of either form
+// are (one thread per line fills 24 or 32 lanes of 64, at 40^3 the other form is
+// the split line), so each size has its own line, where the gain ends.  Whole
+// builds, the other form against quads: 24^3 1.02 to 1.12 up to 105 pairs, 0.86 at
+// 136, 0.94 to 1.04 beyond (36 pairs 30.8 -> 28.6 us); 32^3 1.06 to 1.17 up to 406
+// (0.92 at 55), 1.00 to 1.02 beyond (136 pairs 97.8 -> 83.5 us); 40^3 1.06 to 1.10
+// up to 136, 0.94 to 1.05 beyond (105 pairs 129 -> 120 us).  16^3 0.92 to 1.04
+// throughout, 48^3 0.85 to 1.01.  (One line in planes per CU, ten, for all sizes
+// would give back the 10 to 17 % between 80 and 400 pairs at 32^3.)
 constexpr long quad_planes(int n, size_t eb) {
   if (eb != sizeof(cx<double>)) return 0;
   return n == 24 ? 24 * 105L : n == 32 ? 32 * 400L : n == 40 ? 40 * 128L : 0L;
@@ -866,11 +871,16 @@ constexpr long quad_planes(int n, size_t eb) {
 
 // Bytes of the transposed orbitals that a slab pass over `pairs` pairs takes on
 // split lines; 0: another form is used, because of the size or because the
-// copies (8 to 16 us at the smallest sizes) outweigh the pairs.
+// copies (8 to 16 us at the smallest sizes) outweigh the pairs: below four pairs
+// per orbital, in FP64 from 64^3 below six (whole calls without and with the
+// copies: energy 72^3, 4.5 per orbital, 163 and 177 us, 6.5 per orbital 348 and
+// 327; build 64^3, 5.2 per orbital, 252 and 265, 6.8 per orbital 434 and 416; but
+// 48^3, 5.2 per orbital, 107 and 104; FP32 72^3, 4.5 per orbital, 98 and 94).
 size_t slab_split_bytes(const GridInfo& g, size_t eb, long pairs, long orbitals) {
   if (g.n < (eb == sizeof(cx<double>) ? kSplitSlabN<double> : kSplitSlabN<float>)) return 0;
   if (pairs * g.n <= quad_planes(g.n, eb)) return 0;
-  return pairs >= 4 * orbitals ? align_up((size_t)orbitals * g.ng * eb, 256) : 0;
+  const long least = eb == sizeof(cx<double>) && g.n >= 64 ? 6 : 4;
+  return pairs >= least * orbitals ? align_up((size_t)orbitals * g.ng * eb, 256) : 0;
 }
 
 // Whether split lines may be used: no other line shape is asked for, and the

@@ -451,6 +451,33 @@ void optional_copies() {
   EXPECT(dev.live.empty() && dev.free_bytes == everything);
 }
 
+// Direct energies of few pairs per orbital take no transposed copies.
+void copies_by_pairs() {
+  struct Case {
+    int n;
+    ace_prec prec;
+    int nocc;
+    bool copies;
+  };
+  for (const Case& k : {Case{48, ACE_FP64, 7, true}, Case{48, ACE_FP64, 6, false},
+                        Case{64, ACE_FP64, 10, false}, Case{64, ACE_FP64, 11, true},
+                        Case{72, ACE_FP64, 8, false}, Case{72, ACE_FP64, 11, true},
+                        Case{72, ACE_FP32, 6, false}, Case{72, ACE_FP32, 7, true}}) {
+    g_case = "copies " + std::to_string(k.n) + "^3, precision " + std::to_string(k.prec) + ", " +
+             std::to_string(k.nocc) + " orbitals";
+    ace_ctx c = nullptr;
+    EXPECT(ace_create(&c, nullptr, nullptr) == ACE_OK);
+    const ace_grid g = cubic(k.n);
+    int copies = 0;
+    on_launch = [&](const Launch& l) { copies += l.is("k_orbital_transpose"); };
+    EXPECT(ace_exchange_energy(c, &g, k.prec, array_at(0), k.nocc, (long)k.n * k.n * k.n, nullptr, 0,
+                               0, (double*)array_at(1)) == ACE_OK);
+    on_launch = nullptr;
+    EXPECT((copies > 0) == k.copies);
+    ace_destroy(c);
+  }
+}
+
 // A reduction product fits the scratch that is stated for it, in every mode.
 template <typename T>
 void reduction_scratch() {
@@ -487,6 +514,7 @@ int main() {
   shared_orbitals_on_split_lines();
   fewer_bands_than_orbitals();
   optional_copies();
+  copies_by_pairs();
   reduction_scratch<float>();
   reduction_scratch<double>();
   std::printf("plan checks: %d checks, %d failures\n", g_checks, g_failures);
