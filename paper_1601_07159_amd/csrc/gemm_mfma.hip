@@ -1342,19 +1342,27 @@ static ace_status nn_dispatch(ace_ctx c, const char* name, const cx<TIn>* A, lon
   // product, take the other forms, whose workgroups are smaller and whose loads
   // run further ahead: in FP64 64 orbitals and 8 columns at 24^3 23 against 32
   // us, 128 and 8 at 32^3 45 against 55 us, 4 and 4 at 48^3 32.4 against 33.3 us
-  // (whole calls).
+  // (whole calls).  17 to 32 columns, V_ACE of 64 and of 256 orbitals, slices
+  // against the others: FP32 K = 64,000 1.10 to 1.23 times the time, 110,592 0.91
+  // to 0.97, real orbitals 55,296 (48^3) 1.02 to 1.10, 131,072 0.84 to 0.86; FP64
+  // gains sooner, complex from 64,000 (0.79 to 0.95), real from 32,000.
+  // Short FP64 products of more than 80 orbitals, which take four real products
+  // in either form, stage C for too few tiles: V_ACE of 100 x 100, 200 x 200 and
+  // 256 x 256, slices against k_nn_mfma, K = 512 to 4,096 1.09 to 1.13 times the
+  // time, 13,824 0.91 to 0.99 (but 128 x 48 and 256 x 64 1.10 and 1.06).
   {
+    // where three products lose nothing (see k_nn_slices)
+    const bool three = sizeof(TAcc) > sizeof(TIn) || na <= kNnResA ||
+                       (sizeof(TAcc) == 4 && na <= kNnResA2 && (nb <= 64 || nb > 80));
+    const bool tiny = sizeof(TAcc) == 8 && !three && !c_real && K <= 8192;
     NnSlices sl;
     unsigned grid;
-    if ((nb > 32 || (nb > 16 && K > 65536)) &&
+    if (!tiny && (nb > 32 || (nb > 16 && K > 65536)) &&
         nn_slices(na, nb, K, sizeof(cx<TAcc>), c_upper, &sl, &grid)) {
       const auto run = [&](auto mul) {
         return launch(c, name, k_nn_slices<TIn, TAcc, decltype(mul)::value>, dim3(grid), dim3(512),
                       0, A, lda, na, C, ldc, Y, ldy, K, c_upper ? 1 : 0, sl);
       };
-      // where three products lose nothing (see k_nn_slices)
-      const bool three = sizeof(TAcc) > sizeof(TIn) || na <= kNnResA ||
-                         (sizeof(TAcc) == 4 && na <= kNnResA2 && (nb <= 64 || nb > 80));
       return c_real  ? run(std::integral_constant<int, 2>{})
              : three ? run(std::integral_constant<int, 3>{})
                      : run(std::integral_constant<int, 4>{});

@@ -478,6 +478,42 @@ void copies_by_pairs() {
   }
 }
 
+// The kernels of one V_ACE apply (reduction, expansion) in FP64.
+struct Route {
+  ace_prec prec;
+  int n, nb, nx;
+  const char *reduction, *expansion;
+};
+void apply_routes(std::initializer_list<Route> routes) {
+  for (const Route& r : routes) {
+    g_case = "apply " + std::to_string(r.nb) + " x " + std::to_string(r.nx) + " at " +
+             std::to_string(r.n) + "^3, precision " + std::to_string(r.prec);
+    ace_ctx c = nullptr;
+    EXPECT(ace_create(&c, nullptr, nullptr) == ACE_OK);
+    const ace_grid g = cubic(r.n);
+    const long ng = (long)r.n * r.n * r.n;
+    std::vector<std::string> names;
+    on_launch = [&](const Launch& l) { names.push_back(l.name); };
+    EXPECT(ace_apply(c, &g, r.prec, array_at(0), r.nb, ng, array_at(1), r.nx, ng, array_at(2), ng) ==
+           ACE_OK);
+    on_launch = nullptr;
+    EXPECT(names.size() == 3 && names[0].find(r.reduction) != std::string::npos &&
+           names[2].find(r.expansion) != std::string::npos);
+    ace_destroy(c);
+  }
+}
+
+// Expansions by slices of C where they gain: not for few grid points in FP64
+// with four real products.
+void expansion_routes() {
+  apply_routes({{ACE_FP64, 16, 80, 48, "k_cn", "k_nn_slices"},
+                {ACE_FP64, 16, 81, 48, "k_cn", "k_nn_mfma"},
+                {ACE_FP64, 16, 256, 256, "k_cn", "k_nn_mfma"},
+                {ACE_FP64, 24, 81, 48, "k_cn", "k_nn_slices"},
+                {ACE_REAL64, 16, 256, 256, "k_cn", "k_nn_slices"},
+                {ACE_FP32, 16, 256, 256, "k_cn", "k_nn_slices"}});
+}
+
 // A reduction product fits the scratch that is stated for it, in every mode.
 template <typename T>
 void reduction_scratch() {
@@ -515,6 +551,7 @@ int main() {
   fewer_bands_than_orbitals();
   optional_copies();
   copies_by_pairs();
+  expansion_routes();
   reduction_scratch<float>();
   reduction_scratch<double>();
   std::printf("plan checks: %d checks, %d failures\n", g_checks, g_failures);

@@ -34,6 +34,26 @@ def test_apply_products(n, nb, nx):
     assert np.max(np.abs(Y - ref)) <= 1.5e-13 * np.max(np.abs(ref))
 
 
+@pytest.mark.parametrize("nb,nx", [(97, 48), (136, 64), (145, 96), (256, 70), (304, 40), (608, 33),
+                                   (609, 33)])
+def test_apply_products_by_slices(nb, nx):
+    """The same on a grid of enough points for slices of more than 80 orbitals."""
+    from paper_1601_07159_amd import ace
+    n = 24
+    print(f"expansion by slices nb={nb} nx={nx}", flush=True)
+    L = 0.43 * n
+    g = ogrid(n, L)
+    rng = np.random.default_rng(nb)
+    xi = rng.standard_normal((nb, n ** 3)) + 1j * rng.standard_normal((nb, n ** 3))
+    X = rng.standard_normal((nx, n ** 3)) + 1j * rng.standard_normal((nx, n ** 3))
+    Y = to_np(ace.apply(to_gpu(xi.reshape(nb, n, n, n), "fp64"), to_gpu(X.reshape(nx, n, n, n), "fp64"),
+                        ggrid(n, L), "fp64")).reshape(nx, -1)
+    ref = -g.dV * (xi.conj() @ X.T).T @ xi
+    # sums over N_g and then nb: sqrt(13824 + 609) eps = 2.7e-14 of the largest
+    # value, ten times that
+    assert np.max(np.abs(Y - ref)) <= 2.7e-13 * np.max(np.abs(ref))
+
+
 @pytest.mark.parametrize("n,nb", [(8, 1), (12, 15), (16, 80), (16, 81), (16, 136), (16, 257)])
 def test_triangular_products(n, nb):
     from paper_1601_07159_amd import ace
