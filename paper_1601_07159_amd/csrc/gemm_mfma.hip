@@ -1219,6 +1219,23 @@ static ace_status launch_gram(ace_ctx c, const char* name, const GramShape& g, c
   return fail(c, ACE_E_ARG, "internal: blocks per wave");
 }
 
+// Whether tiles of 32 do an FP64 product of two operands sooner than blocks,
+// both in four real products.  The matrix cores set the time of either while the
+// operands come from the caches, so the slots count that waves have for blocks of
+// 16 x 16 (cut tiles and unevenly dealt blocks leave some empty): V_ACE by tiles
+// against blocks, whole calls, 24^3 to 40^3, more than 7/8 as many slots for blocks:
+// 250 and 256 vectors 0.85 to 0.98 of the time, 256 x 128 0.85 to 0.92, 100, 112 and
+// 128 vectors 0.92 to 0.97; fewer: 224 0.99 to 1.02, 192 1.01 to 1.03, 96 1.10 to
+// 1.16.  Up to 16^3 the sums of the splits weigh more, and only 128 blocks and more
+// take tiles (256 x 256 0.87 to 0.93, 100 x 100 1.07 to 1.09); from 48^3 on the
+// operands come from memory (48^3 0.86 to 1.22, 64^3 1.05 to 1.65).
+static bool tiles_sooner(int na, int nb, long K, const GramShape& g) {
+  const long total = (long)((na + 15) / 16) * ((nb + 15) / 16);
+  if (total < (K <= 8192 ? 128 : 32) || K > 65536) return false;
+  const CnShape t = cn_shape(na, nb, K, 8, 12);
+  return 8L * (8 * g.gx * ((g.per + 7) / 8)) > 7L * (4 * t.ta * t.tb * t.gx * t.gy);
+}
+
 size_t gemm_cn_scratch_bytes(int na, int nb, long K) {
   CnShape s32 = cn_shape(na, nb, K, 16, 16), s16 = cn_shape(na, nb, K, kBf16Waves, kBf16Waves);
   CnShape s64 = cn_shape(na, nb, K, 8, 12);
@@ -1282,7 +1299,8 @@ ace_status gemm_cn(ace_ctx c, const cx<T>* A, long lda, int na, const cx<T>* B, 
                         (uintptr_t)(ldb * sizeof(cx<T>))) % 16 == 0;
   if (f.blocks && aligned &&
       gram_shape(na, nb, K, sizeof(cx<T>), f.acc_bytes, A == B && lda == ldb && na == nb,
-                 herm && na == nb, &gs)) {
+                 herm && na == nb, &gs) &&
+      !(sizeof(T) == 8 && !real_part && !gs.herm && tiles_sooner(na, nb, K, gs))) {
     auto run = [&](auto acc, const char* name) -> ace_status {
       typedef decltype(acc) TAcc;
       ace_status st;

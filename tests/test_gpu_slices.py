@@ -175,6 +175,36 @@ def test_noalloc_sizes(prec, nb, nx):
     ctx.close()
 
 
+@pytest.mark.parametrize("n,nb,nx", [(24, 96, 96), (24, 100, 100), (24, 256, 130), (16, 256, 250),
+                                     (48, 256, 256)])
+def test_reduction_forms(n, nb, nx):
+    """FP64 reductions on either side of the line between tiles of 32 and blocks
+    of 16 (the last by blocks with fewer splits, so that the partials fit the
+    allocation-free apply)."""
+    import ctypes
+    import torch
+    from paper_1601_07159_amd import _lib, ace
+    print(f"reduction forms n={n} nb={nb} nx={nx}", flush=True)
+    gg = ggrid(n, 0.43 * n)
+    gen = torch.Generator(device="cuda").manual_seed(nb)
+    xi = torch.randn(nb, n ** 3, dtype=torch.complex128, device="cuda", generator=gen)
+    X = torch.randn(nx, n ** 3, dtype=torch.complex128, device="cuda", generator=gen)
+    Y = torch.full_like(X, float("nan"))
+    ctx = ace.Context()
+    g = gg.as_c()
+    ctx._bind_stream()
+    st = _lib.load().ace_apply_noalloc(
+        ctx._h, ctypes.byref(g), ace._prec("fp64"), ctypes.c_void_p(xi.data_ptr()), nb, xi.stride(0),
+        ctypes.c_void_p(X.data_ptr()), nx, X.stride(0), ctypes.c_void_p(Y.data_ptr()), Y.stride(0))
+    assert st == 0
+    assert torch.equal(Y, ctx.apply(xi, X, gg, "fp64"))
+    ctx.close()
+    ref = -gg.dV * ((xi.conj() @ X.T.contiguous()).T.contiguous() @ xi)
+    # sums over N_g and then nb: sqrt(N_g + nb) eps of the largest value, ten times that
+    tol = 10 * np.sqrt(n ** 3 + nb) * 2.2e-16
+    assert float((Y - ref).abs().max()) <= tol * float(ref.abs().max())
+
+
 @pytest.mark.parametrize("prec,nb,nx", [("fp64", 96, 17), ("fp64", 161, 32), ("fp32", 272, 17)])
 def test_small_imaginary_parts(prec, nb, nx):
     """Orbitals that are all but real: the imaginary parts of <xi_a, X_b> are as
