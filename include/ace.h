@@ -382,7 +382,7 @@ ace_status ace_set_pair_budget(ace_ctx ctx, long bytes);
  *  ACE_TUNE_FFT_SHAPE    line FFTs of the slab and plane passes: 1 one thread
  *                        per line, 4 a lane quad per line, 8 an octet of lanes
  *                        per line (grids whose n is a multiple of 8 from 16;
- *                        quads otherwise), 16 a line split over four lanes 16
+ *                        quads otherwise), 16 a line over four lanes 16
  *                        apart, 0 (default) automatic
  *  ACE_TUNE_ACCUM_SHAPE  accumulate pass: 1 one thread per pencil (accumulator
  *                        in LDS), 16 a pencil split over four lanes 16 apart

@@ -90,7 +90,7 @@ struct ace_ctx_s {
   long jblock = 0;         // band block of the build; 0 = automatic
   bool use_symmetry = true;  // i <-> j pair symmetry on the occupied block
   int fft_shape = 0;         // slab/plane line shape: 0 auto, 1 thread, 4 quad, 8 octet, 16 split
-  int accum_shape = 0;       // accumulate pass: 0 auto, 1 thread per pencil, 16 split lines
+  int accum_shape = 0;       // accumulate pass: 0 auto, 1 thread per pencil, 16 pencils over four lanes
   int branches = 4;          // branch streams of the batched build
   int batch_form = 0;        // batched build: 0 default, 1 per-instance launches, 2 persistent
   // Batched build, persistent form: while `record` is set, the pass launchers

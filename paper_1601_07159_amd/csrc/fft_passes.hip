@@ -234,8 +234,9 @@ __global__ __launch_bounds__(4 * N) void k_plane_kernel(cx<T>* __restrict__ buf,
   }
 }
 
-// Split-line forms of the slab and plane passes: every line FFT is split over
-// 4 lanes 16 apart (fft_quad_* with lane distance 16: lane p + 16 h of wave w
+// Staged forms of the slab and plane passes (knob value 16; split lines,
+// split_passes.h, are another form): every line FFT runs over 4 lanes 16 apart
+// (fft_quad_* with lane distance 16: lane p + 16 h of wave w
 // holds part h of line l = 16 w + p), so 16 consecutive lanes hold the same
 // part of 16 consecutive lines and every global access of 16 lanes is one
 // contiguous row segment.  A workgroup of kRowWaves = ceil(N / 16) waves
@@ -483,7 +484,7 @@ __global__ __launch_bounds__(64) void k_pencil_accum(const cx<T>* __restrict__ p
                        accumulate, mode);
 }
 
-// Accumulate pass on split lines (accum_q_body), one wave per logical
+// Accumulate pass on divided pencils (accum_q_body), one wave per logical
 // workgroup.
 template <int N, typename T>
 __global__ __launch_bounds__(64) void k_pencil_accum_q(const cx<T>* __restrict__ phi, long ldphi,
@@ -769,8 +770,8 @@ __global__ __launch_bounds__(256) void k_pencil_energy(const cx<T>* __restrict__
   const int p = blockIdx.x / TILES;
   const int tile = blockIdx.x - p * TILES;
   const int t = threadIdx.x;
-  // pencil p_ + 16 (t >> 6) of the tile on lanes p_ + 16 h (split lines, 16
-  // consecutive pencils per row segment)
+  // pencil p_ + 16 (t >> 6) of the tile on lanes p_ + 16 h (16 consecutive
+  // pencils per row segment)
   const int h = (t >> 4) & 3;
   const int q = tile * 64 + ((t >> 6) << 4) + (t & 15);
   double sum = 0.0;
@@ -1049,9 +1050,10 @@ ace_kspec kspec_of(const GridInfo& g, double coef, const double* dscale = nullpt
 }
 
 // Line shape of the slab and plane passes: one thread per line (1), a lane
-// quad per line with DPP exchanges (4), an octet (8), a line split over lanes
-// 16 apart with permlane exchanges and staged rows (16), or split lines without
-// staging (2, split_passes.h; the slab pass takes it by slab_split).  The tuning
+// quad per line with DPP exchanges (4), an octet (8), the staged form over lanes
+// 16 apart with permlane exchanges (16), or split lines (2, split_passes.h; the
+// slab pass takes them where there are transposed copies).  16 was slower than
+// quads or one thread per line everywhere and is used only when asked for.  The tuning
 // knob ACE_TUNE_FFT_SHAPE (1, 4, 8, 16) overrides both passes, else an
 // autotuned shape for this grid size and element size.
 template <int N, typename T>
@@ -1150,11 +1152,11 @@ ace_status plane(ace_ctx c, cx<T>* buf, const ace_kspec& ks, int np, long all) {
 }
 
 // Form of the accumulate pass: one thread per pencil with the accumulator in
-// LDS (1), or pencils split over lanes 16 apart with register accumulators
-// (16).  Measured per build (FP32): 48^3 split 0.92 ms vs LDS 1.03 ms
+// LDS (1), or pencils divided over lanes 16 apart with register accumulators
+// (16).  Measured per build (FP32): 48^3 divided 0.92 ms vs LDS 1.03 ms
 // (5,120 pairs), 64^3 0.90 vs 0.90, 72^3 1.11 vs 0.95 ms per launch (the
-// split form needs 226 registers there, two waves per SIMD, and the permlane
-// exchanges add VALU work): split up to N = 64, LDS above.  The knob
+// divided form needs 226 registers there, two waves per SIMD, and the permlane
+// exchanges add VALU work): divided up to N = 64, LDS above.  The knob
 // ACE_TUNE_ACCUM_SHAPE overrides it, else an autotuned form.
 template <int N, typename T>
 int accum_form(ace_ctx c) {

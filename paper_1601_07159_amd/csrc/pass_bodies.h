@@ -401,8 +401,8 @@ __device__ __forceinline__ int tri_partner(int A, int b, int s) {
   return a == A ? b : a;
 }
 
-// Accumulate pass on split lines: every (x0, x2) pencil along axis 1 is split
-// over 4 lanes 16 apart (lane p + 16 h holds part h of pencil p: it loads rows
+// Accumulate pass on divided pencils: every (x0, x2) pencil along axis 1 lies
+// on 4 lanes 16 apart (lane p + 16 h holds part h of pencil p: it loads rows
 // h + 4 m and, after fft_quad_d2b, holds rows k + M kp(h)), 16 consecutive
 // pencils per one-wave workgroup, so every load and store of 16 lanes is one
 // contiguous row segment; one band per workgroup row of the grid.  The band's
