@@ -714,8 +714,8 @@ __global__ __launch_bounds__(256) void k_nn_mfma(const cx<TIn>* __restrict__ A, 
 // whole grid, so the staging is paid once per CU instead of once per tile.
 // The grid-row loads run R - 1 steps (4 orbitals each) ahead of the MFMAs.
 constexpr int kNnResA = 80;
-// Larger resident capacity for FP32 accumulation with up to 64 columns per
-// workgroup: 256 orbitals x 64 columns x 8 bytes = 128 KiB of LDS.
+// Larger resident capacity for FP32 accumulation: 256 orbitals x 32 columns x 8
+// bytes = 64 KiB of LDS.
 constexpr int kNnResA2 = 256;
 
 // upper: C is upper triangular (C[a][b] = 0 for a > b), so a step of four
