@@ -440,6 +440,9 @@ __global__ __launch_bounds__(1024) void k_reduce_partials2(const cx<P>* __restri
 // 0.30 of the error, 72 -> 74 us; 136 x 64^3 0.05, 594 -> 435 us; 256 x 72^3
 // 0.01, 2,081 -> 1,803 us; FP64 data 136 x 64^3 0.39, 828 -> 464 us; FP32 sums
 // 64 x 64 x 48^3 0.49, 63 -> 52 us, 256 x 256 x 72^3 0.004, 2,308 -> 1,728 us.
+// FP64 products of two operands from the caches that fill tiles of 32 are the ones
+// that lose time by it: V_ACE of 256 x 256 at 32^3 533 -> 628 us, 100 x 100 146 ->
+// 157, at 0.51 and 0.72 of the error (random orbitals); from 64^3 on they gain.
 //
 // Bound by the FP64 matrix cores and, for FP32 data, the conversions that share
 // the FP64 units with them, so a wave's blocks share a column of B where they
@@ -1219,23 +1222,6 @@ static ace_status launch_gram(ace_ctx c, const char* name, const GramShape& g, c
   return fail(c, ACE_E_ARG, "internal: blocks per wave");
 }
 
-// Whether tiles of 32 do an FP64 product of two operands sooner than blocks,
-// both in four real products.  The matrix cores set the time of either while the
-// operands come from the caches, so the slots count that waves have for blocks of
-// 16 x 16 (cut tiles and unevenly dealt blocks leave some empty): V_ACE by tiles
-// against blocks, whole calls, 24^3 to 40^3, more than 7/8 as many slots for blocks:
-// 250 and 256 vectors 0.85 to 0.98 of the time, 256 x 128 0.85 to 0.92, 100, 112 and
-// 128 vectors 0.92 to 0.97; fewer: 224 0.99 to 1.02, 192 1.01 to 1.03, 96 1.10 to
-// 1.16.  Up to 16^3 the sums of the splits weigh more, and only 128 blocks and more
-// take tiles (256 x 256 0.87 to 0.93, 100 x 100 1.07 to 1.09); from 48^3 on the
-// operands come from memory (48^3 0.86 to 1.22, 64^3 1.05 to 1.65).
-static bool tiles_sooner(int na, int nb, long K, const GramShape& g) {
-  const long total = (long)((na + 15) / 16) * ((nb + 15) / 16);
-  if (total < (K <= 8192 ? 128 : 32) || K > 65536) return false;
-  const CnShape t = cn_shape(na, nb, K, 8, 12);
-  return 8L * (8 * g.gx * ((g.per + 7) / 8)) > 7L * (4 * t.ta * t.tb * t.gx * t.gy);
-}
-
 size_t gemm_cn_scratch_bytes(int na, int nb, long K) {
   CnShape s32 = cn_shape(na, nb, K, 16, 16), s16 = cn_shape(na, nb, K, kBf16Waves, kBf16Waves);
   CnShape s64 = cn_shape(na, nb, K, 8, 12);
@@ -1299,8 +1285,7 @@ ace_status gemm_cn(ace_ctx c, const cx<T>* A, long lda, int na, const cx<T>* B, 
                         (uintptr_t)(ldb * sizeof(cx<T>))) % 16 == 0;
   if (f.blocks && aligned &&
       gram_shape(na, nb, K, sizeof(cx<T>), f.acc_bytes, A == B && lda == ldb && na == nb,
-                 herm && na == nb, &gs) &&
-      !(sizeof(T) == 8 && !real_part && !gs.herm && tiles_sooner(na, nb, K, gs))) {
+                 herm && na == nb, &gs)) {
     auto run = [&](auto acc, const char* name) -> ace_status {
       typedef decltype(acc) TAcc;
       ace_status st;

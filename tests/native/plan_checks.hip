@@ -514,22 +514,6 @@ void expansion_routes() {
                 {ACE_FP32, 16, 256, 256, "k_cn", "k_nn_slices"}});
 }
 
-// Reductions by blocks where they gain over tiles of 32.
-void reduction_routes() {
-  const char *blocks = "k_cn_blocks", *tiles = "k_cn_mfma";
-  apply_routes({{ACE_FP64, 16, 256, 256, tiles, "k_nn"},
-                {ACE_FP64, 16, 100, 100, blocks, "k_nn"},
-                {ACE_FP64, 24, 256, 256, tiles, "k_nn"},
-                {ACE_FP64, 24, 100, 100, tiles, "k_nn"},
-                {ACE_FP64, 24, 96, 96, blocks, "k_nn"},
-                {ACE_FP64, 40, 240, 240, tiles, "k_nn"},
-                {ACE_FP64, 40, 224, 224, blocks, "k_nn"},
-                {ACE_FP64, 40, 64, 64, blocks, "k_nn"},
-                {ACE_FP64, 48, 256, 256, blocks, "k_nn"},
-                {ACE_REAL64, 40, 256, 256, blocks, "k_nn"},
-                {ACE_FP32, 40, 256, 256, blocks, "k_nn"}});
-}
-
 // A reduction product fits the scratch that is stated for it, in every mode.
 template <typename T>
 void reduction_scratch() {
@@ -568,7 +552,6 @@ int main() {
   optional_copies();
   copies_by_pairs();
   expansion_routes();
-  reduction_routes();
   reduction_scratch<float>();
   reduction_scratch<double>();
   std::printf("plan checks: %d checks, %d failures\n", g_checks, g_failures);

@@ -178,9 +178,9 @@ def test_noalloc_sizes(prec, nb, nx):
 @pytest.mark.parametrize("n,nb,nx", [(24, 96, 96), (24, 100, 100), (24, 256, 130), (16, 256, 250),
                                      (48, 256, 256)])
 def test_reduction_forms(n, nb, nx):
-    """FP64 reductions on either side of the line between tiles of 32 and blocks
-    of 16 (the last by blocks with fewer splits, so that the partials fit the
-    allocation-free apply)."""
+    """FP64 reductions by blocks that fill their waves and that do not, with few and
+    with many splits (256 x 256: fewer, so that the partials fit the allocation-free
+    apply)."""
     import ctypes
     import torch
     from paper_1601_07159_amd import _lib, ace
